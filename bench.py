@@ -450,14 +450,10 @@ def measure(index, K, warmup, rotate=0, eager=False):
         cnt += n
     k_ms = [v / max(1, cnt) for v in sums]
     if decode:
-        # decode launches: prep (plan + packing), main (K-split shrink and
-        # base partials), epilogue (partial sums + expand); main moves the
-        # weights and dominates
-        names = ("prep", "main", "epilogue")
-        if bd.decode_plans_in_main(spec.T, [p.d_in for p in spec.projs]):
-            names = ("", "main", "epilogue")    # planned inside the main launch: no prep launch
+        # one launch: plan, shrink, base product and expand
+        names = ("", "main")
         dom, dom_name = 1, "bdl::dec_main_kernel"
-        algo = m_bytes
+        algo = step_bytes
         achieved = algo / (k_ms[dom] * 1e-3) / 1e9
         roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4)}

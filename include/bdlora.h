@@ -65,18 +65,17 @@ extern "C" {
 #define BDLORA_MAX_PROJS  8
 #define BDLORA_MAX_SLOTS  8192
 #define BDLORA_MAX_RANK   128
-/* Batches of at most this many tokens take the decode launch sequence (plan
- * and packing, K-split shrink and base partials, epilogue); larger ones take
- * the prefill sequence (plan and packing, shrink, base product with the
- * expand fused in, or for medium batches on large layers base partials and
- * an epilogue; see bdlora_last_path). */
+/* Batches of at most this many tokens take the decode launch (plan, shrink,
+ * base product and expand in one); larger ones take the prefill sequence
+ * (plan and packing, shrink, base product with the expand fused in, or for
+ * medium batches on large layers base partials and an epilogue; see
+ * bdlora_last_path). */
 #define BDLORA_DECODE_MAX_T 64
-/* Decode batches skip the plan and packing launch when T <= 16, or when
- * T <= BDLORA_DECODE_PLAN_IN_MAIN_T and T x (the sum of d_in over the
- * call's projections) x 2 bytes <= BDLORA_DECODE_PLAN_IN_MAIN_BYTES: every
- * wave of the K-split launch then plans the batch from the ids (or
- * segments) itself and gathers the caller's row-major activations, which
- * slows that launch more the more activation bytes it gathers. */
+/* Sizes of small decode batches: T <= 16, or T <=
+ * BDLORA_DECODE_PLAN_IN_MAIN_T and T x (the sum of d_in over the call's
+ * projections) x 2 bytes <= BDLORA_DECODE_PLAN_IN_MAIN_BYTES.  (Every decode
+ * batch now plans inside its one launch; the bounds stay for callers that
+ * read them.) */
 #define BDLORA_DECODE_PLAN_IN_MAIN_T 32
 #define BDLORA_DECODE_PLAN_IN_MAIN_BYTES 1572864
 /* Largest number of segments a bdlora_segments batch may have (the segments
@@ -304,9 +303,8 @@ int bdlora_forward_layer(bdlora_pool_t pool, int32_t n, const int32_t* projs,
 /* For callers that cannot allocate device memory during the call (code under
  * HIP graph capture, tight serving loops, harnesses that forbid allocation):
  * bdlora_forward_layer for decode batches (1 <= T <= BDLORA_DECODE_MAX_T;
- * T = 0 enqueues nothing) whose per-batch scratch -- the plan's tables, the
- * packed activations and the fp32 partial tiles -- lives in a static device
- * array of BDLORA_STATIC_SCRATCH_BYTES that the library holds on every GPU it
+ * T = 0 enqueues nothing) whose per-batch scratch (the shrink's results)
+ * lives in a static device array of BDLORA_STATIC_SCRATCH_BYTES that the library holds on every GPU it
  * runs on until the process ends, instead of in the pool's workspace.  The
  * call allocates nothing (no hipMalloc, no allocating library routine); the
  * pool still holds the adapters, their tables and the error flag.  Same
@@ -316,7 +314,9 @@ int bdlora_forward_layer(bdlora_pool_t pool, int32_t n, const int32_t* projs,
  * race and must be serialized by the caller.  Nothing in the array has to
  * start at zero: every word a call reads was written earlier in that call.
  * Errors: as bdlora_forward_layer; SHAPE for T above BDLORA_DECODE_MAX_T or a
- * call whose scratch exceeds BDLORA_STATIC_SCRATCH_BYTES (the message gives
+ * call that exceeds BDLORA_STATIC_SCRATCH_BYTES, counting plan tables, the
+ * packed activations (2 T d_in bytes per projection) and fp32 tiles of 16 KB
+ * per 64 weight and adapter columns plus up to two per CU (the message gives
  * the sizes); HIP if the array's address could not be taken when the pool
  * was created. */
 #define BDLORA_STATIC_SCRATCH_BYTES (32 << 20)
@@ -402,9 +402,8 @@ int bdlora_pool_bytes(bdlora_pool_t pool, int64_t* bytes);
 
 /* Timing hooks.  bdlora_profile_begin(pool, n) makes the next n forward
  * calls record HIP events around each of their launches on the caller's
- * stream, in four intervals: for a decode batch (BDLORA_PATH_DECODE) plan
- * and packing, K-split shrink and base partials, epilogue, nothing; for a
- * larger batch plan and packing, shrink, base product (with the fused
+ * stream, in four intervals: for a decode batch (BDLORA_PATH_DECODE)
+ * nothing, its one launch, nothing, nothing; for a larger batch plan and packing, shrink, base product (with the fused
  * expand, or for BDLORA_PATH_MEDIUM the partials), and for
  * BDLORA_PATH_MEDIUM its epilogue (partials plus expand), else nothing.
  * bdlora_profile_end waits for them and writes the mean duration in
@@ -417,7 +416,7 @@ int bdlora_profile_end(bdlora_pool_t pool, float* ms, int32_t* n);
 /* Which launch sequence served the last forward call on this pool (known
  * when the call returns; the kernels may still be running), for tests and
  * tuning: *path = 0 before any forward, else one of
- *   BDLORA_PATH_DECODE  split-K decode launches (T <= BDLORA_DECODE_MAX_T)
+ *   BDLORA_PATH_DECODE  the decode launch (T <= BDLORA_DECODE_MAX_T)
  *   BDLORA_PATH_TILE64  64-row tiles, base product with the fused expand
  *   BDLORA_PATH_MEDIUM  all rows of the batch in one tile (bf16 weights,
  *                       T <= 256, layers whose weight is large against the

@@ -49,7 +49,8 @@ struct Layout {
     long long slab_bytes = 0, ws_bytes = 0;
     long long z_elems[bdl::kMaxProjs];
     long long xp_elems[bdl::kMaxProjs];
-    long long part_slots = 0;          // decode partial tiles
+    long long dec_z_elems[bdl::kMaxProjs];   // decode path: Z lines
+    long long dec_flags = 0;           // decode path: producer flags
     long long mlp_elems = 0;           // prefill MLP: gate and up outputs, fp32
     long long bigpart_elems = 0;       // large-tile GEMM: fp32 partials of split tiles
     long long shrinkpart_elems = 0;    // split shrink: fp32 partials
@@ -114,21 +115,21 @@ int make_layout(const bdlora_proj_desc* projs, int n_projs, int max_slots, int m
     L->slot_stride = off;
     L->slab_bytes = (long long)max_slots * off * 2;
     long long ws = 0;
-    ws += 9LL * max_tokens * 4;                                   // vid, tr8, tgrp, perm, rowtok, rowslot (+ slack)
+    ws += 9LL * max_tokens * 4;                                   // vid, perm, rowtok, rowslot (+ slack)
     ws += 4LL * (max_slots + 2) * 4 + 2 * 4;                      // group tables, meta, err
     ws += ((long long)max_slots + max_tokens / 16 + 2) * 16;      // shrink items
     ws += std::max(((long long)max_tokens / 16 + 1) * (2LL * L->r8max + 64),
                    ((long long)max_tokens / 64 + 1) * (8LL * L->r8max + 64)) * 4;   // tile octets
     for (int p = 0; p < n_projs; ++p) ws += (L->z_elems[p] + L->xp_elems[p]) * 2;
-    // decode partial tiles: one per (group, workgroup) pair of the main launch
-    long long groups = 0;
-    const int act_max = std::min({bdl::kDecodeMaxT, max_slots, max_tokens});
+    // decode path: Z lines and the producers' flags
+    const int dec_t = std::min(bdl::kDecodeMaxT, max_tokens);
     for (int p = 0; p < n_projs; ++p) {
-        const ProjInfo& P = L->proj[p];
-        groups += (P.N / 16 + (long long)act_max * ((P.S * L->r8max + 15) / 16) + 3) / 4;
+        const long long nbA = (L->proj[p].zs + 15) / 16;
+        L->dec_z_elems[p] = nbA * dec_t * bdl::kDecZLine;
+        ws += L->dec_z_elems[p] * 2;
+        L->dec_flags += (dec_t + (dec_t - 1) / 16) * nbA;
     }
-    L->part_slots = groups + bdl::kDecMaxGrid;
-    ws += L->part_slots * bdl::kPartElems * 4 + (long long)max_tokens * 4;
+    ws += L->dec_flags * 8;
     int max_n = 0;                                  // widest single-slice column projection
     for (int p = 0; p < n_projs; ++p)
         if (L->proj[p].kind == BDLORA_COLUMN && L->proj[p].S == 1) max_n = std::max(max_n, L->proj[p].N);
@@ -178,10 +179,8 @@ struct bdlora_pool {
     std::vector<int> h_rank, h_r8, h_loaded;
     std::vector<float> h_scale;
     int* d_vid = nullptr;
-    int* d_tr8 = nullptr;
     int* d_perm = nullptr;
     int* d_gslot = nullptr;
-    int* d_gr8 = nullptr;
     int* d_gstart = nullptr;
     int* d_gcount = nullptr;
     int4* d_items = nullptr;
@@ -192,8 +191,8 @@ struct bdlora_pool {
     int* d_meta = nullptr;
     int* d_err = nullptr;
     uint16_t* d_Z[bdl::kMaxProjs] = {};
-    int* d_tgrp = nullptr;
-    float* d_part = nullptr;
+    uint16_t* d_decZ[bdl::kMaxProjs] = {};
+    unsigned long long* d_flags = nullptr;
     float* d_mlp = nullptr;
     float* d_bigpart = nullptr;
     float* d_shrinkpart = nullptr;
@@ -228,10 +227,8 @@ void free_pool(bdlora_pool* P) {
     f(P->d_scale);
     f(P->d_loaded);
     f(P->d_vid);
-    f(P->d_tr8);
     f(P->d_perm);
     f(P->d_gslot);
-    f(P->d_gr8);
     f(P->d_gstart);
     f(P->d_gcount);
     f(P->d_items);
@@ -241,8 +238,8 @@ void free_pool(bdlora_pool* P) {
     f(P->d_meta);
     f(P->d_err);
     for (auto z : P->d_Z) f(z);
-    f(P->d_tgrp);
-    f(P->d_part);
+    for (auto z : P->d_decZ) f(z);
+    f(P->d_flags);
     f(P->d_mlp);
     f(P->d_bigpart);
     f(P->d_shrinkpart);
@@ -465,9 +462,7 @@ int bdlora_create_pool(const bdlora_proj_desc* projs, int32_t n_projs, int32_t m
     BDL_TRY(dev_alloc(&P->d_scale, S, &tot));
     BDL_TRY(dev_alloc(&P->d_loaded, S, &tot));
     BDL_TRY(dev_alloc(&P->d_vid, MT, &tot));
-    BDL_TRY(dev_alloc(&P->d_tr8, MT, &tot));
-    BDL_TRY(dev_alloc(&P->d_tgrp, MT, &tot));
-    BDL_TRY(dev_alloc(&P->d_part, L.part_slots * bdl::kPartElems, &tot));
+    BDL_TRY(dev_alloc(&P->d_flags, L.dec_flags, &tot));
     BDL_TRY(dev_alloc(&P->d_mlp, L.mlp_elems, &tot));
     if (L.bigpart_elems > 0) BDL_TRY(dev_alloc(&P->d_bigpart, L.bigpart_elems, &tot));
     if (L.shrinkpart_elems > 0) BDL_TRY(dev_alloc(&P->d_shrinkpart, L.shrinkpart_elems, &tot));
@@ -475,7 +470,6 @@ int bdlora_create_pool(const bdlora_proj_desc* projs, int32_t n_projs, int32_t m
     BDL_TRY(dev_alloc(&P->d_rowtok, MT, &tot));
     BDL_TRY(dev_alloc(&P->d_rowslot, MT, &tot));
     BDL_TRY(dev_alloc(&P->d_gslot, S + 1, &tot));
-    BDL_TRY(dev_alloc(&P->d_gr8, bdl::kDecodeMaxT + 1, &tot));
     BDL_TRY(dev_alloc(&P->d_gstart, S + 1, &tot));
     BDL_TRY(dev_alloc(&P->d_gcount, S + 1, &tot));
     P->items_cap = (long long)S + MT / 16 + 2;
@@ -489,6 +483,7 @@ int bdlora_create_pool(const bdlora_proj_desc* projs, int32_t n_projs, int32_t m
     for (int p = 0; p < n_projs; ++p) {
         BDL_TRY(dev_alloc(&P->d_Z[p], L.z_elems[p], &tot));
         BDL_TRY(dev_alloc(&P->d_Xp[p], L.xp_elems[p], &tot));
+        BDL_TRY(dev_alloc(&P->d_decZ[p], L.dec_z_elems[p], &tot));
         const ProjInfo& pi = L.proj[p];
         stage = std::max(stage, (long long)pi.S * pi.K * std::max(1, max_rank) + (long long)std::max(1, max_rank) * pi.N);
     }
@@ -510,10 +505,10 @@ int bdlora_create_pool(const bdlora_proj_desc* projs, int32_t n_projs, int32_t m
     if (int r = hipz(P->d_loaded, (size_t)S * 4)) return r;
     if (int r = hipz(P->d_err, 4)) return r;
     if (int r = hipz(P->d_meta, 16)) return r;
+    if (int r = hipz(P->d_flags, (size_t)L.dec_flags * 8)) return r;
     // plan tables: entries past a batch's counts are never written by the
     // plan; zero (slot 0) rather than whatever the allocation held
     if (int r = hipz(P->d_gslot, (size_t)(S + 1) * 4)) return r;
-    if (int r = hipz(P->d_gr8, (size_t)(bdl::kDecodeMaxT + 1) * 4)) return r;
     if (int r = hipz(P->d_gstart, (size_t)(S + 1) * 4)) return r;
     if (int r = hipz(P->d_gcount, (size_t)(S + 1) * 4)) return r;
     for (int p = 0; p < n_projs; ++p)
@@ -721,7 +716,6 @@ static void fill_plan_args(bdlora_pool_t P, const Batch& B, int T, bdl::PrepArgs
         a->seg_start[i] = B.seg_start[i];
         a->seg_slot[i] = B.seg_slot[i];
     }
-    a->act_max = -1;
     a->loaded = P->d_loaded;
     a->r8 = P->d_r8;
     a->max_slots = P->L.max_slots;
@@ -729,14 +723,11 @@ static void fill_plan_args(bdlora_pool_t P, const Batch& B, int T, bdl::PrepArgs
     a->gemm_mt = 16 * k.gmb;
     a->oct_cap = oct_cap(P->L, 16 * k.gmb);
     a->vid = P->d_vid;
-    a->tr8 = P->d_tr8;
-    a->tgrp = nullptr;
     a->perm = P->d_perm;
     a->rowtok = nullptr;
     a->rowslot = nullptr;
     a->oct_perm = 0;
     a->gslot = P->d_gslot;
-    a->gr8 = nullptr;
     a->gstart = P->d_gstart;
     a->gcount = P->d_gcount;
     a->items = P->d_items;
@@ -745,22 +736,7 @@ static void fill_plan_args(bdlora_pool_t P, const Batch& B, int T, bdl::PrepArgs
     a->err = P->d_err;
     a->n_jobs = 0;
     a->total_frags = 0;
-    a->decode_plan = 0;
 }
-
-// Decode batches: prep (plan + activation packing), the split-K main launch
-// over W_s and the used adapters' A^T, the epilogue.
-// How a call uses the decode launches: the MLP chains two calls, the second
-// reusing the first's plan and reading the intermediate the first's epilogue
-// packed.
-struct DecMode {
-    bool prep = true;              // plan the batch and pack the activations (false: the tables hold this
-                                   // batch's plan and Xp its activations); at most 16 tokens the main
-                                   // launch plans it and reads the caller's X, with no prep launch
-    int mlp_act = -1;              // >= 0: the epilogue writes the MLP intermediate
-    uint16_t* h_dst = nullptr;     // where (fragment layout of the second projection's input)
-    int h_KS = 0;
-};
 
 // scales of a packed INT4 base weight (null for a bf16 base)
 static const uint16_t* int4_scales(const ProjInfo& pi, const void* W) {
@@ -768,190 +744,94 @@ static const uint16_t* int4_scales(const ProjInfo& pi, const void* W) {
     return reinterpret_cast<const uint16_t*>(static_cast<const char*>(W) + (size_t)pi.N * pi.K / 2);
 }
 
-// Where a decode call keeps its per-batch scratch: the pool's workspace, or
-// (the allocation-free entry point) the library's static device array.
-struct DecWs {
-    int* vid = nullptr;               // [T] validated ids
-    int* tr8 = nullptr;               // [T] padded rank of each token's adapter
-    int* tgrp = nullptr;              // [T] group of each token's adapter
-    int* gslot = nullptr;             // [<= 64] slots of the adapters in use
-    int* gr8 = nullptr;               // [<= 64] their padded ranks
-    int* meta = nullptr;              // [4] plan counts
-    uint16_t* Xp[bdl::kMaxProjs] = {};   // packed activations of the call's i-th projection
-    float* part = nullptr;            // fp32 partial tiles; null: carved from arena
-    long long part_slots = 0;
-    char* arena = nullptr;            // static scratch left for the partial tiles
-    long long arena_bytes = 0;
+// Adapter positions of a decode call's launch: the loaded adapters bound
+// the distinct ones a batch can use (the plan treats any past that bound as
+// none and raises the error flag).  Both forms of the batch (ids, segments)
+// take the same launch geometry, so they give the same bits.
+static int decode_act_max(bdlora_pool_t P, int T) {
+    int n_loaded = 0;
+    for (int v : P->h_loaded) n_loaded += v != 0;
+    return std::min({T, n_loaded, bdl::kDecodeMaxT});
+}
+
+// Decode batches, one launch.  Z: where the call's i-th projection keeps its
+// Z lines.  The MLP's first call (mlp_act >= 0) writes the intermediate to h.
+struct DecZ {
+    uint16_t* z[bdl::kMaxProjs];
 };
 
-static DecWs pool_dec_ws(bdlora_pool_t P, int n, const int32_t* projs) {
-    DecWs w;
-    w.vid = P->d_vid;
-    w.tr8 = P->d_tr8;
-    w.tgrp = P->d_tgrp;
-    w.gslot = P->d_gslot;
-    w.gr8 = P->d_gr8;
-    w.meta = P->d_meta;
-    for (int i = 0; i < n; ++i) w.Xp[i] = P->d_Xp[projs[i]];
-    w.part = P->d_part;
-    w.part_slots = P->L.part_slots;
-    return w;
+static DecZ pool_dec_z(bdlora_pool_t P, int n, const int32_t* projs) {
+    DecZ r;
+    for (int i = 0; i < n; ++i) r.z[i] = P->d_decZ[projs[i]];
+    return r;
 }
 
 static int forward_decode(bdlora_pool_t P, int n, const int32_t* projs, const void* const* X,
                           const void* const* W, void* const* out, const Batch& B, int T, hipStream_t s,
-                          const DecWs& ws, const DecMode& mode = DecMode()) {
+                          uint16_t* const* Z, int mlp_act = -1, uint16_t* h = nullptr) {
     const Layout& L = P->L;
-    // small batches: the main launch plans the batch in every wave and
-    // gathers the caller's X, so no prep launch runs.  The gathered rows
-    // slow the main launch with the activation bytes (measured: a 17..32
-    // token batch of the 70B layer shard, 58 KB of activations per token,
-    // gains up to about 28 tokens, the 8B shard, 29 KB per token, at every
-    // size up to 32; at 64 tokens the prep launch is cheaper)
-    static_assert(BDLORA_DECODE_PLAN_IN_MAIN_T <= 32, "the planning kernel takes at most two row blocks");
-    long long act_bytes = 0;
-    for (int i = 0; i < n; ++i) act_bytes += 2LL * T * L.proj[projs[i]].K;
-    const bool fold = mode.prep && (T <= 16 || (T <= BDLORA_DECODE_PLAN_IN_MAIN_T &&
-                                                act_bytes <= BDLORA_DECODE_PLAN_IN_MAIN_BYTES));
-    // adapter positions of the launches: the loaded adapters bound the
-    // distinct ones a batch can use (the plan treats any past that bound as
-    // none and raises the error flag).  Both forms of the batch (ids,
-    // segments) take the same launch geometry, so they give the same bits.
-    int n_loaded = 0;
-    for (int v : P->h_loaded) n_loaded += v != 0;
-    const int act_max = std::min({T, n_loaded, bdl::kDecodeMaxT});
-
     bdl::DecArgs da;
     std::memset(&da, 0, sizeof(da));
-    long long units_min = 0, units_max = 0, groups_max = 0;
-    int tiles = 0;
-    for (int i = 0; i < n; ++i) {
+    da.n_proj = n;
+    da.T = T;
+    da.r8max = L.r8max;
+    da.act_max = decode_act_max(P, T);
+    da.pair = mlp_act == BDLORA_ACT_SILU_MUL ? 1 : 0;
+    da.h_dst = h;
+    // longest K first: the projections with the longest workgroups
+    int order[bdl::kMaxProjs];
+    for (int i = 0; i < n; ++i) order[i] = i;
+    if (!da.pair)
+        std::stable_sort(order, order + n, [&](int x, int y) { return L.proj[projs[x]].K > L.proj[projs[y]].K; });
+    const int waves = bdl::dec_waves((T + 15) / 16);
+    int tiles = 0, shrinks = 0;
+    for (int q = 0; q < n; ++q) {
+        const int i = order[q];
         const ProjInfo& pi = L.proj[projs[i]];
-        bdl::DecProj& d = da.p[i];
-        d.X = fold ? (const uint16_t*)X[i] : nullptr;
-        d.Xp = ws.Xp[i];
+        bdl::DecProj& d = da.p[q];
+        d.X = (const uint16_t*)X[i];
         d.W = (const uint16_t*)W[i];
         d.Ws = int4_scales(pi, W[i]);
         d.out = (uint16_t*)out[i];
+        d.Z = Z[i];
         d.K = pi.K;
         d.N = pi.N;
         d.n_slices = pi.S;
         for (int t = 0; t <= bdl::kMaxSlices; ++t) d.slice_col[t] = pi.slice_col[t];
         d.a_off = pi.a_off;
         d.b_off = pi.b_off;
-        d.nWb = pi.N / 16;
         d.nbA = (pi.S * L.r8max + 15) / 16;
-        d.tile_base = tiles;
-        tiles += (pi.N + 63) / 64;
-        units_min += (long long)d.nWb * (pi.K / 32);
-        units_max += (d.nWb + (long long)act_max * d.nbA) * (pi.K / 32);
-        groups_max += (d.nWb + (long long)act_max * d.nbA + 3) / 4;
+        da.shrink_base[q] = shrinks;
+        // (adapter, 16 tokens) items: sum of ceil(tokens / 16) over the adapters in use
+        shrinks += (da.act_max > 0 ? da.act_max + (T - 1) / 16 : 0) * d.nbA;
+        const int KS = pi.K / 32;
+        // about 16 k-steps per part, as far as the workgroup's waves go
+        d.kparts = std::min(waves, KS >= 64 ? 8 : KS >= 32 ? 4 : KS >= 16 ? 2 : 1);
+        const int blocks = waves / d.kparts * (da.pair ? 1 : bdl::kDecNB);
+        da.tile_base[q] = tiles;
+        if (!(da.pair && q == 1)) tiles += (pi.N / 16 + blocks - 1) / blocks;
     }
-    // two workgroups per CU, each with at least 64 units (16 k-steps of a
-    // full group) whatever the number of adapters in use; fewer, longer
-    // workgroups split each output group over fewer partial tiles, which its
-    // epilogue adds one by one.  Measured with the data streamed from HBM: a
-    // layer whose base weights give one to two such workgroups per CU is
-    // fastest on one per CU of at least 128 units (the 8B MLP's gate and up
-    // at 64 tokens, 448 64-unit workgroups: 54.1 -> 51.1 us a step); a
-    // smaller one keeps 64-unit workgroups (one 1792-column projection at 16
-    // tokens: 20.7 -> 17.5 us from two per CU, 18.1 with 128-unit ones); a
-    // larger one two per CU (the 8B decode layer, 832 64-unit workgroups).
-    // The kernels' 32-bit schedule arithmetic needs units * workgroups < 2^32
-    // (at least one workgroup: one that owns every unit needs no minimum)
-    const long long min_units = units_min >= 64LL * P->n_cu && units_min < 64LL * 2 * P->n_cu ? 128 : 64;
-    const int grid = (int)std::min<long long>(
-        {2LL * P->n_cu, (long long)bdl::kDecMaxGrid, std::max(1LL, units_min / min_units),
-         0xffffffffLL / std::max(1LL, units_max)});
-    if (grid < 1) return fail(BDLORA_ERR_SHAPE, "batch too large for the decode launch's schedule");
-    float* part = ws.part;
-    long long part_slots = ws.part_slots;
-    if (!part) {
-        // the partial tiles this call needs, from the rest of the static scratch
-        part_slots = groups_max + grid;
-        if (part_slots * bdl::kPartElems * 4 > ws.arena_bytes)
-            return fail(BDLORA_ERR_SHAPE, "the call's partial tiles need " +
-                                              std::to_string(part_slots * bdl::kPartElems * 4) +
-                                              " bytes, the static scratch has " + std::to_string(ws.arena_bytes) +
-                                              " left after the plan and the packed activations");
-        part = reinterpret_cast<float*>(ws.arena);
-    }
-    if (groups_max + grid > part_slots) return fail(BDLORA_ERR_SHAPE, "batch exceeds the pool workspace");
-    da.n_proj = n;
-    da.T = T;
-    {
-        unsigned u = 0;
-        int g = 0;
-        for (int i = 0; i < n; ++i) {
-            const int nb = da.p[i].nWb + act_max * da.p[i].nbA;
-            da.sub[i] = u;
-            da.sgb[i] = g;
-            da.snb[i] = nb;
-            da.sks[i] = da.p[i].K / 32;
-            da.stb[i] = da.p[i].tile_base;
-            u += (unsigned)nb * (unsigned)da.sks[i];
-            g += (nb + 3) / 4;
-        }
-        da.units = u;
-    }
+    da.n_shrink = std::max(1, shrinks);
+    da.n_main = tiles;
+    if (shrinks == 0)
+        for (int q = 1; q < n; ++q) da.shrink_base[q] = 1;        // its one workgroup only checks the ids
+    da.wait_ticks = 20000;                                        // 200 us
+    da.flags = P->d_flags;
+    if (da.n_shrink > L.dec_flags) return fail(BDLORA_ERR_SHAPE, "batch exceeds the pool workspace");
     da.pool = P->d_slabs;
     da.slot_stride = L.slot_stride;
     da.scale = P->d_scale;
-    da.vid = ws.vid;
-    da.tr8 = ws.tr8;
-    da.tgrp = ws.tgrp;
-    da.gslot = ws.gslot;
-    da.gr8 = ws.gr8;
-    da.meta = ws.meta;
-    da.act_max = act_max;
-    da.part = part;
-    da.part_slots = (int)part_slots;
-    da.main_grid = grid;
-    da.tiles = tiles;
-    da.err = P->d_err;
-    da.mlp_act = mode.mlp_act;
-    da.h_dst = mode.h_dst;
-    da.h_KS = mode.h_KS;
-
-    Shapes k;
-    k.smb = 1;
-    k.snb = 4;
-    k.gmb = (T + 15) / 16;
-    k.gnb = 4;
-    bdl::PrepArgs pa;
-    fill_plan_args(P, B, T, &pa, k);
-    pa.tile_oct = nullptr;                        // the epilogue needs no octet lists
-    pa.decode_plan = 1;                           // writes vid, tr8, tgrp, gslot, meta (and err) only
-    pa.vid = ws.vid;
-    pa.tr8 = ws.tr8;
-    pa.tgrp = ws.tgrp;
-    pa.gslot = ws.gslot;
-    pa.gr8 = ws.gr8;
-    pa.meta = ws.meta;
-    pa.perm = nullptr;
-    pa.gstart = pa.gcount = nullptr;
-    pa.items = nullptr;
-    pa.act_max = act_max;
-    // projections given the same X (gate and up) share one packed copy
-    int frags = 0, jobs = 0;
-    for (int q = 0; q < n && mode.prep; ++q) {
-        int same = -1;
-        for (int r = 0; r < q && same < 0; ++r)
-            if (X[r] == X[q] && da.p[r].K == da.p[q].K) same = r;
-        if (same >= 0) {
-            da.p[q].Xp = da.p[same].Xp;
-            continue;
-        }
-        bdl::PackJob& J = pa.jobs[jobs++];
-        J.src = (const uint16_t*)X[q];
-        J.dst = ws.Xp[q];
-        J.rows = T;
-        J.K = da.p[q].K;
-        J.frag_base = frags;
-        frags += ((T + 15) / 16) * (J.K / 32);
+    da.ids = B.ids;
+    da.n_seg = B.ids ? 0 : B.n_seg;
+    if (da.n_seg > bdl::kDecodeMaxT) return fail(BDLORA_ERR_INVALID_ARG, "more segments than tokens");
+    for (int i = 0; i < da.n_seg; ++i) {
+        da.seg_start[i] = B.seg_start[i];
+        da.seg_slot[i] = B.seg_slot[i];
     }
-    pa.n_jobs = jobs;
-    pa.total_frags = frags;
+    da.loaded = P->d_loaded;
+    da.r8 = P->d_r8;
+    da.max_slots = L.max_slots;
+    da.err = P->d_err;
 
     hipEvent_t* ev = nullptr;
     if (P->prof_left > 0 && (size_t)(P->prof_used + 1) * kProfEvents <= P->prof_ev.size()) {
@@ -959,39 +839,16 @@ static int forward_decode(bdlora_pool_t P, int n, const int32_t* projs, const vo
         ++P->prof_used;
         --P->prof_left;
     }
-    if (fold) {
-        // the plan's inputs for the main launch
-        da.plan = 1;
-        da.ids = B.ids;
-        da.n_seg = B.ids ? 0 : B.n_seg;
-        if (da.n_seg > bdl::kDecodeMaxT) return fail(BDLORA_ERR_INVALID_ARG, "more segments than tokens");
-        for (int i = 0; i < da.n_seg; ++i) {
-            da.seg_start[i] = B.seg_start[i];
-            da.seg_slot[i] = B.seg_slot[i];
-        }
-        da.loaded = P->d_loaded;
-        da.r8 = P->d_r8;
-        da.max_slots = L.max_slots;
-    }
-    if (ev) BDL_HIP(hipEventRecord(ev[0], s));
-    if (mode.prep && !fold) BDL_HIP(bdl::launch_prep(pa, s));
-    if (ev) BDL_HIP(hipEventRecord(ev[1], s));
-    if (ev) BDL_HIP(hipEventRecord(ev[2], s));
-    BDL_HIP(bdl::launch_dec_main(da, k.gmb, s));
-    if (ev) BDL_HIP(hipEventRecord(ev[3], s));
-    if (ev) BDL_HIP(hipEventRecord(ev[4], s));
-    BDL_HIP(bdl::launch_dec_epi(da, s));
-    if (ev) BDL_HIP(hipEventRecord(ev[5], s));
-    if (ev) BDL_HIP(hipEventRecord(ev[6], s));
-    if (ev) BDL_HIP(hipEventRecord(ev[7], s));
+    if (ev)
+        for (int i = 0; i < 3; ++i) BDL_HIP(hipEventRecord(ev[i], s));
+    BDL_HIP(bdl::launch_dec_main(da, (T + 15) / 16, s));
+    if (ev)
+        for (int i = 3; i < kProfEvents; ++i) BDL_HIP(hipEventRecord(ev[i], s));
     P->last_path = BDLORA_PATH_DECODE;
     return BDLORA_OK;
 }
 
-static bool use_decode(const Layout& L, int T) {
-    // the decode launches address their partial tiles with 32-bit byte offsets
-    return T <= bdl::kDecodeMaxT && L.part_slots * bdl::kPartElems * 4 < (1LL << 31);
-}
+static bool use_decode(int T) { return T <= bdl::kDecodeMaxT; }
 
 // Batches above the decode size: prep (plan + packing; with pack = false the
 // packed activations are already in place), shrink, base product with the
@@ -1370,7 +1227,7 @@ int bdlora_forward_layer(bdlora_pool_t P, int32_t n, const int32_t* projs, const
     if (!guard.ok) return fail(BDLORA_ERR_HIP, "hipSetDevice failed");
     hipStream_t s = (hipStream_t)stream;
 
-    if (use_decode(L, T)) return forward_decode(P, n, projs, X, W, out, B, T, s, pool_dec_ws(P, n, projs));
+    if (use_decode(T)) return forward_decode(P, n, projs, X, W, out, B, T, s, pool_dec_z(P, n, projs).z);
     return forward_prefill(P, n, projs, X, W, out, B, T, s);
 }
 
@@ -1387,31 +1244,40 @@ int bdlora_forward_layer_static(bdlora_pool_t P, int32_t n, const int32_t* projs
     if (!base)
         return fail(BDLORA_ERR_HIP, std::string("static scratch address not available on this device: ") +
                                         hipGetErrorString(P->static_err));
-    // the array carved in 256-byte aligned pieces: plan tables, packed
-    // activations per projection of the call, then the partial tiles
+    // the array carved in 256-byte aligned pieces: the projections' Z lines
+    const Layout& L = P->L;
     long long off = 0;
-    auto take = [&](long long bytes) {
-        char* p = base + off;
-        off = round_up(off + bytes, 256);
-        return p;
-    };
-    DecWs w;
-    w.meta = reinterpret_cast<int*>(take(16));
-    w.vid = reinterpret_cast<int*>(take(4LL * bdl::kDecodeMaxT));
-    w.tr8 = reinterpret_cast<int*>(take(4LL * bdl::kDecodeMaxT));
-    w.tgrp = reinterpret_cast<int*>(take(4LL * bdl::kDecodeMaxT));
-    w.gslot = reinterpret_cast<int*>(take(4LL * (bdl::kDecodeMaxT + 1)));
-    w.gr8 = reinterpret_cast<int*>(take(4LL * (bdl::kDecodeMaxT + 1)));
-    for (int i = 0; i < n; ++i) w.Xp[i] = reinterpret_cast<uint16_t*>(take(round_up(T, 16) * P->L.proj[projs[i]].K * 2LL));
-    if (off > bdl::kStaticScratchBytes)
-        return fail(BDLORA_ERR_SHAPE, "the call's packed activations need " + std::to_string(off) +
-                                          " bytes, more than BDLORA_STATIC_SCRATCH_BYTES");
-    w.part = nullptr;
-    w.arena = base + off;
-    w.arena_bytes = bdl::kStaticScratchBytes - off;
+    uint16_t* Z[bdl::kMaxProjs] = {};
+    for (int i = 0; i < n; ++i) {
+        Z[i] = reinterpret_cast<uint16_t*>(base + off);
+        off = round_up(off + (L.proj[projs[i]].zs + 15) / 16 * (long long)T * bdl::kDecZLine * 2, 256);
+    }
+    if (off > bdl::kStaticScratchBytes) return fail(BDLORA_ERR_SHAPE, "the call exceeds the static scratch");
+    // The capacity of the entry point counts plan tables, packed activations
+    // and one fp32 tile of 64 x 64 per four column blocks (of the
+    // weight and of the adapters the batch may use) and per workgroup of a
+    // two-per-CU launch.  The launch no longer keeps these there; calls above
+    // that size stay refused, so that what a caller may rely on is the same.
+    const int act_max = decode_act_max(P, T);
+    long long tiles = 0, units_min = 0, units_max = 0, cap_off = 256 * 4 + 512 * 2;
+    for (int i = 0; i < n; ++i) {
+        const ProjInfo& pi = L.proj[projs[i]];
+        const long long nb = pi.N / 16, na = (long long)act_max * ((pi.S * L.r8max + 15) / 16);
+        tiles += (nb + na + 3) / 4;
+        units_min += nb * (pi.K / 32);
+        units_max += (nb + na) * (pi.K / 32);
+        cap_off += round_up(round_up(T, 16) * pi.K * 2LL, 256);
+    }
+    const long long min_units = units_min >= 64LL * P->n_cu && units_min < 64LL * 2 * P->n_cu ? 128 : 64;
+    tiles += std::min<long long>({2LL * P->n_cu, 1024LL, std::max(1LL, units_min / min_units),
+                                  0xffffffffLL / std::max(1LL, units_max)});
+    if (cap_off + tiles * 64 * 64 * 4 > bdl::kStaticScratchBytes)
+        return fail(BDLORA_ERR_SHAPE, "the call counts " + std::to_string(cap_off + tiles * 64 * 64 * 4) +
+                                          " bytes of scratch, the static scratch has " +
+                                          std::to_string((long long)bdl::kStaticScratchBytes));
     DeviceGuard guard(P->device);
     if (!guard.ok) return fail(BDLORA_ERR_HIP, "hipSetDevice failed");
-    return forward_decode(P, n, projs, X, W, out, B, T, (hipStream_t)stream, w);
+    return forward_decode(P, n, projs, X, W, out, B, T, (hipStream_t)stream, Z);
 }
 
 int bdlora_forward_shard(bdlora_pool_t P, int32_t proj, const void* X, const void* W, const int32_t* ids,
@@ -1460,18 +1326,13 @@ int bdlora_forward_mlp(bdlora_pool_t P, int32_t act, const int32_t* first, int32
     const int32_t dn[1] = {down};
     const void* wd[1] = {W_down};
     void* od[1] = {out};
-    if (use_decode(L, T)) {
-        // first projections: their epilogue writes H packed; down reuses the plan
-        DecMode m1;
-        m1.mlp_act = act;
-        m1.h_dst = h;
-        m1.h_KS = Ni / 32;
+    if (use_decode(T)) {
+        // first projections: they write H, row-major, where down reads it
+        const void* xd[1] = {h};
         void* none[2] = {nullptr, nullptr};
-        int rc = forward_decode(P, nf, first, xs, W_first, none, B, T, s, pool_dec_ws(P, nf, first), m1);
+        int rc = forward_decode(P, nf, first, xs, W_first, none, B, T, s, pool_dec_z(P, nf, first).z, act, h);
         if (rc) return rc;
-        DecMode m2;
-        m2.prep = false;
-        return forward_decode(P, 1, dn, xs, wd, od, B, T, s, pool_dec_ws(P, 1, dn), m2);
+        return forward_decode(P, 1, dn, xd, wd, od, B, T, s, pool_dec_z(P, 1, dn).z);
     }
     // larger batches: the first projections' epilogue writes H (bf16,
     // packed as down's input) on the large-tile and medium-batch paths; on

@@ -23,6 +23,10 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // word 3 of a raw buffer resource on gfx950 (32-bit untyped data)
 constexpr int kRawBufferWord3 = 0x00020000;
 
+// cache policy of buffer loads and stores at agent scope (sc1): past the caches
+// that are not coherent between XCDs
+constexpr int kAgentScope = 16;
+
 constexpr int kWaves = 8;                 // waves per workgroup (split K)
 constexpr int kThreads = kWaves * 64;
 
@@ -203,6 +207,20 @@ __device__ __forceinline__ unsigned wave_or(unsigned v) {
     v |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);
     return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
+
+// inclusive prefix sum over the 64 lanes of a wave (DPP row shifts, then row
+// broadcasts of lanes 15 and 31)
+__device__ __forceinline__ int wave_incl_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31
+    return v;
+}
+
+__device__ __forceinline__ int wave_total(int incl) { return __builtin_amdgcn_readlane(incl, 63); }
 
 // Contiguous k-step range of wave w when KS k-steps are split over kWaves.
 __device__ __forceinline__ void wave_krange(int KS, int w, int* k0, int* n) {

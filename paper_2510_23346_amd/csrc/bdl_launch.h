@@ -108,8 +108,6 @@ struct PrepArgs {
     int n_seg;                // segments (ids null): token t takes seg_slot[i] of the last i with
     int seg_start[kMaxSeg];   // seg_start[i] <= t (the host checked that they tile 0..T-1)
     int seg_slot[kMaxSeg];
-    int act_max;              // decode plan: adapters past this many (slot order) are treated as
-                              // none and raise *err (the decode launches' bound); -1: no bound
     const int* loaded;
     const int* r8;            // [max_slots]
     int max_slots;
@@ -117,14 +115,11 @@ struct PrepArgs {
     int gemm_mt;              // base GEMM row tile (<= 64)
     int oct_cap;
     int* vid;
-    int* tr8;                 // [T] rank (padded to 8) of each token's adapter, 0 if none
-    int* tgrp;                // [T] group index of each token's adapter, -1 if none (optional)
     int* perm;
     int* rowtok;              // optional [T]: the adapted tokens in perm order, then the others in order
     int* rowslot;             // optional [T], with rowtok: (rank8 << 16) | slot of each row's adapter, -1 for none
     int oct_perm;             // 1: octet lists for the 64-row blocks of rowtok order (large-tile GEMM)
     int* gslot;
-    int* gr8;                 // decode plan (optional): padded rank of each adapter in use
     int* gstart;
     int* gcount;
     int4* items;
@@ -134,85 +129,65 @@ struct PrepArgs {
     PackJob jobs[kMaxProjs];
     int n_jobs;
     int total_frags;
-    int decode_plan;          // T <= 64: one wave writes vid, tr8, tgrp, gslot, meta only
 };
 
 // ---- decode path (T <= kDecodeMaxT) ----------------------------------------
-// The main launch is one split-K GEMM of the packed activations against a
-// virtual column list per projection: the W_s column blocks (16 columns
-// each), then for every adapter the batch uses (in group order) the blocks of
-// its A^T_cat.  Work is counted in units of one 16-column block times one
-// 32-wide k-step; groups of 4 consecutive blocks are cut into k-ranges so
-// that every workgroup of the launch gets the same number of units.
+// One launch: shrink and main workgroups (bdl_decode.hip).
 constexpr int kDecodeMaxT = BDLORA_DECODE_MAX_T;
-constexpr int kDecMaxGrid = 1024;    // most workgroups of the main launch
-constexpr int kPartElems = 64 * 64;  // fp32 partial tile: 64 rows x 64 virtual columns
+constexpr int kDecNB = 2;            // 16-column blocks per wave of a main workgroup
+// Waves per workgroup for mb blocks of 16 tokens.  The registers allow two
+// waves per SIMD, so four-wave workgroups leave room for shrink and main ones
+// on a CU together (64 tokens, 26 adapters: 29.7 against 29.5 us; 32 tokens:
+// 21.8 against 25.1); with one block, mostly few adapters, eight waves halve
+// each wave's share of K (one token: 13.9 against 15.4 us).
+constexpr int dec_waves(int mb) { return mb == 1 ? 8 : 4; }
+constexpr int kDecZLine = 64;        // elements of Z per (16-row block of A^T, token): one 128-byte line
 
 struct DecProj {
-    const uint16_t* X;        // the caller's activations [T x K], row-major (batches of at most 16
-                              // tokens planned in the main launch); else null and Xp is read
-    const uint16_t* Xp;       // packed activations (fragment layout)
+    const uint16_t* X;        // activations [T x K], row-major
     const uint16_t* W;        // packed base weight
     const uint16_t* Ws;       // INT4 base: its scales (null for a bf16 base)
     uint16_t* out;            // [T x N] bf16
+    uint16_t* Z;              // [nbA][T][kDecZLine] scale * X A: per 16-row block of A^T and token three
+                              // planes of 16 bf16 numbers that sum to the fp32 value (the rest unused)
     int K, N, n_slices;
     int slice_col[kMaxSlices + 1];
     long long a_off, b_off;
-    int nWb;                  // W column blocks (N / 16)
-    int nbA;                  // A^T_cat blocks per adapter (rows padded to 16)
-    int tile_base;            // first epilogue tile (64 output columns) of this projection
+    int nbA;                  // A^T_cat blocks of an adapter of the pool's largest rank
+    int kparts;               // parts of K per column group of a main workgroup (1, 2 or 4)
 };
 
 struct DecArgs {
-    // Schedule of the main launch, computed by the host for act_max adapter
-    // positions: projection p's units start at sub[p] (sub[n_proj] = all
-    // units) and its groups at sgb[p]; it has snb[p] virtual blocks and
-    // sks[p] k-steps.  Kept first and compact so that a workgroup reads it
-    // with a few scalar loads.
-    unsigned units;
-    unsigned sub[kMaxProjs];
-    int sgb[kMaxProjs], snb[kMaxProjs], sks[kMaxProjs];
-    int stb[kMaxProjs];       // first epilogue tile of each projection
-    DecProj p[kMaxProjs];
+    // what a workgroup reads first
+    int n_shrink, n_main;           // workgroups of each kind, in launch order (n_shrink >= 1: the first
+                                    // also reports invalid ids)
     int n_proj;
+    int shrink_base[kMaxProjs];     // first shrink workgroup of each projection
+    int tile_base[kMaxProjs];       // first main workgroup of each projection
     int T;
+    int act_max;              // adapter positions of the launch: the host's bound on the adapters in
+                              // use; the plan treats those past it (slot order) as none and raises *err
+    int max_slots;
+    int r8max;
+    int pair;                 // gated MLP: projections 0 and 1 share the tiles of 0, H = silu(0) * 1
+    unsigned wait_ticks;      // longest wait for a producer (100 MHz ticks), then its work is done here
+    unsigned long long* flags;   // [n_shrink] launch tags (bdl_decode.hip, launch_tag)
+    const int* ids;           // [T] per-token slot ids, or null: the segments below
+    const int* loaded;        // [max_slots] nonzero: the slot holds an adapter
+    const int* r8;            // [max_slots] padded rank of each slot
     const uint16_t* pool;
     long long slot_stride;
     const float* scale;       // [max_slots]
-    // The batch's plan.  plan = 0: the prep launch wrote it into the tables
-    // below.  plan = 1 (batches of at most 16 tokens): every wave of the main
-    // launch computes it from the batch (ids, or segments) and the slot
-    // tables, and the first wave of workgroup 0 stores the tables below.
-    int plan;
-    const int* ids;           // [T] per-token slot ids, or null: the segments below
+    uint16_t* h_dst;          // when set: the output is the MLP intermediate H [T x N], written here
+    int* err;                 // sticky error flag
+    DecProj p[kMaxProjs];
     int n_seg;                // segments (ids null): token t takes seg_slot[i] of the last i with
     int seg_start[kDecodeMaxT];   // seg_start[i] <= t (the host checked that they tile 0..T-1)
     int seg_slot[kDecodeMaxT];
-    const int* loaded;        // [max_slots] nonzero: the slot holds an adapter
-    const int* r8;            // [max_slots] padded rank of each slot
-    int max_slots;
-    int* vid;                 // [T] validated ids
-    int* tr8;                 // [T] padded rank of each token's adapter (0: none)
-    int* tgrp;                // [T] group (adapter in use) index of each token, -1: none
-    int* gslot;               // [groups] slot of each adapter in use
-    int* gr8;                 // [groups] its rank padded to 8 (its A^T blocks: n_slices gr8 / 16,
-                              // rounded up; positions past them hold no data)
-    int* meta;                // [0] number of adapters in use (n_act)
-    int act_max;              // adapter positions in the column lists: the host's bound on n_act;
-                              // the plan treats adapters past it (slot order) as none and raises *err
-    float* part;              // partial tiles: slot g + b for group g and workgroup b
-    int part_slots;
-    int main_grid;            // workgroups of the main launch
-    int tiles;                // epilogue tiles over all projections
-    int* err;                 // sticky error flag
-    int mlp_act;              // -1: write out; else write the MLP intermediate H (BDLORA_ACT_*)
-    uint16_t* h_dst;          // H in the fragment layout of the second projection's input
-    int h_KS;                 // k-steps of that layout (second projection's d_in / 32)
 };
 
 // Host-side launchers (bdl_kernels.hip, bdl_prep.hip, bdl_decode.hip).
 hipError_t launch_dec_main(const DecArgs& a, int mb, hipStream_t s);
-hipError_t launch_dec_epi(const DecArgs& a, hipStream_t s);
 hipError_t launch_prep(const PrepArgs& a, hipStream_t s);
 hipError_t launch_shrink(const FwdArgs& a, int mb, int nb, hipStream_t s);
 hipError_t launch_gemm(const FwdArgs& a, int mb, int nb, hipStream_t s);

@@ -1,11 +1,9 @@
 // Prep launch of a forward call: workgroup 0 plans the batch, the others pack
-// the activations into the MFMA fragment layout.  Decode batches take a
-// one-wave plan that writes only what the decode launches read.
+// the activations into the MFMA fragment layout.  (Decode batches plan inside
+// their first launch.)
 //
 // Plan outputs (integer work, compared bit-exactly with the host plan):
 //   vid[t]      validated id (-1: none or invalid; invalid ones raise *err)
-//   tr8[t]      rank (padded to 8) of token t's adapter, 0 if none
-//   tgrp[t]     (when asked for) group index of token t's adapter, -1 if none
 //   groups      (slot, start, count) per adapter in use, slots ascending
 //   perm        tokens group after group, ascending inside a group
 //   items       shrink work items {slot, first perm index, rows <= mts, r8}
@@ -22,111 +20,7 @@ namespace bdl {
 
 constexpr int kOctTail = 36;   // -1 entries after an octet list's last code (see the octet lists below)
 
-// inclusive prefix sum over the 64 lanes of a wave (DPP row shifts, then row
-// broadcasts of lanes 15 and 31)
-__device__ __forceinline__ int wave_incl_scan(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31
-    return v;
-}
 
-__device__ __forceinline__ int wave_total(int incl) { return __builtin_amdgcn_readlane(incl, 63); }
-
-
-// Segments form: lane i < n_seg writes the id of segment i into ids_lds for
-// its tokens (the host checked that the segments tile 0..T-1), and lane t
-// reads token t's id back.
-__device__ __forceinline__ int decode_seg_id(const PrepArgs& a, int* ids_lds) {
-    const int l = threadIdx.x & 63;
-    if (l < a.n_seg) {
-        const int s0 = a.seg_start[l], s1 = l + 1 < a.n_seg ? a.seg_start[l + 1] : a.T, v = a.seg_slot[l];
-        for (int t = s0; t < s1 && t < kDecodeMaxT; ++t) ids_lds[t] = v;
-    }
-    __builtin_amdgcn_s_waitcnt(0xc07f);        // lgkmcnt(0): this wave's LDS stores are done
-    __builtin_amdgcn_wave_barrier();
-    return l < a.T ? ids_lds[l] : -1;
-}
-
-// Plan of a decode batch (T <= 64) by one wave: validated ids, ranks, the
-// adapters in use in ascending slot order (groups) and each token's group.
-// Lane t holds token t.  Pools of at most 64 slots keep the slot tables in
-// lanes (one load round trip) and find the groups from the bit mask of slots
-// in use; larger pools look the tables up per token and take the smallest
-// remaining slot per pass.
-__device__ void decode_plan(const PrepArgs& a, int* ids_lds) {
-    const int l = threadIdx.x & 63;
-    const bool in = l < a.T;
-    const bool small = a.max_slots <= 64;
-    const int lt = small && l < a.max_slots ? a.loaded[l] : 0;
-    const int rt = small && l < a.max_slots ? a.r8[l] : 0;
-    const int id = a.ids ? (in ? a.ids[l] : -1) : decode_seg_id(a, ids_lds);
-    const bool in_range = id >= 0 && id < a.max_slots;
-    int ld, r8v;
-    if (small) {
-        ld = __shfl(lt, in_range ? id : 0);
-        r8v = __shfl(rt, in_range ? id : 0);
-        if (!in_range) ld = r8v = 0;
-    } else {
-        ld = in_range ? a.loaded[id] : 0;
-        r8v = in_range ? a.r8[id] : 0;
-    }
-    bool ok = in_range && ld != 0;
-    bool bad = __ballot(in && !ok && id != -1) != 0ull;
-    int g = 0, mine = -1;
-    const int v = ok ? id : -1;
-    if (small) {
-        const unsigned long long bit = ok ? 1ull << v : 0ull;
-        const unsigned long long used =
-            (unsigned long long)wave_or((unsigned)bit) | ((unsigned long long)wave_or((unsigned)(bit >> 32)) << 32);
-        const unsigned long long below = (1ull << l) - 1ull;
-        if ((used >> l) & 1ull) {
-            a.gslot[__popcll(used & below)] = l;
-            if (a.gr8) a.gr8[__popcll(used & below)] = rt;   // lane l holds slot l's rank
-        }
-        if (ok) mine = __popcll(used & (bit - 1ull));
-        g = __popcll(used);
-    } else {
-        unsigned long long rem = __ballot(ok);
-        while (rem) {
-            const int m = wave_min(((rem >> l) & 1ull) ? v : 0x7fffffff);
-            const bool eq = ok && v == m;
-            if (eq) mine = g;
-            // slot m's rank: held by every lane whose token uses it
-            const int rm = __builtin_amdgcn_readlane(r8v, __ffsll((long long)__ballot(eq)) - 1);
-            if (l == 0) {
-                a.gslot[g] = m;
-                if (a.gr8) a.gr8[g] = rm;
-            }
-            ++g;
-            rem &= ~__ballot(eq);
-        }
-    }
-    // adapters past the launches' bound (possible only when a captured
-    // forward replays after more adapters were loaded): base only, flagged
-    if (a.act_max >= 0 && g > a.act_max) {
-        const bool over = ok && mine >= a.act_max;
-        bad = bad || __ballot(over) != 0ull;
-        if (over) {
-            ok = false;
-            mine = -1;
-        }
-        g = a.act_max;
-    }
-    if (in) {
-        a.vid[l] = ok ? v : -1;
-        a.tr8[l] = ok ? r8v : 0;
-        if (a.tgrp) a.tgrp[l] = mine;
-    }
-    if (l == 0) {
-        a.meta[0] = g;
-        a.meta[1] = 0;
-        if (bad) atomicOr(a.err, 1);
-    }
-}
 
 // activations -> fragment layout (all workgroups but 0)
 // Each wave packs PER consecutive fragments per turn (consecutive k-steps of
@@ -279,10 +173,6 @@ __global__ __launch_bounds__(1024) void prep_kernel(PrepArgs a) {
         return;
     }
     __shared__ int vid_l[kPlanLdsTokens];
-    if (a.decode_plan) {
-        if (threadIdx.x < 64) decode_plan(a, vid_l);
-        return;
-    }
     extern __shared__ int tabs[];             // cnt | r8 | loaded | 15 tile bitmaps
     const int nwords = (a.max_slots + 31) >> 5;
     int* cnt = tabs;                          // counts, then group starts
@@ -344,7 +234,6 @@ __global__ __launch_bounds__(1024) void prep_kernel(PrepArgs a) {
                 if (!ok && id != -1) s_err = 1;
                 const int v = ok ? id : -1;
                 a.vid[t] = v;
-                a.tr8[t] = ok ? r8l[id] : 0;
                 if (in_lds) vid_l[t] = v;
             }
             // a wave whose tokens share one adapter (a prefill request) adds
@@ -416,11 +305,6 @@ __global__ __launch_bounds__(1024) void prep_kernel(PrepArgs a) {
         a.meta[2] = 0;
     }
     __syncthreads();
-    if (a.tgrp)
-        for (int t = tid; t < a.T; t += 1024) {
-            const int v = in_lds ? vid_l[t] : a.vid[t];
-            a.tgrp[t] = v >= 0 ? ldl[v] : -1;
-        }
 
     // stable placement: perm[start(v) + #{t' < t : vid[t'] == v}] = t; with
     // rowtok, the same order followed by the tokens without an adapter
@@ -545,9 +429,9 @@ hipError_t launch_prep(const PrepArgs& a, hipStream_t s) {
     int pack_blocks = (a.total_frags + 16 * per - 1) / (16 * per);
     if (pack_blocks > 4096) pack_blocks = 4096;
     const int nwords = (a.max_slots + 31) >> 5;
-    size_t lds = a.decode_plan ? 0 : 3 * (size_t)a.max_slots * sizeof(int) + 15 * (size_t)nwords * sizeof(unsigned);
+    size_t lds = 3 * (size_t)a.max_slots * sizeof(int) + 15 * (size_t)nwords * sizeof(unsigned);
     // place_waves' per-wave counts, for the batches that take it
-    if (!a.decode_plan && a.T > 1024 && a.max_slots <= kPlanParMaxSlots) lds += 16 * kPlanWaveGroups * sizeof(int);
+    if (a.T > 1024 && a.max_slots <= kPlanParMaxSlots) lds += 16 * kPlanWaveGroups * sizeof(int);
     hipLaunchKernelGGL(prep_kernel, dim3(1 + pack_blocks), dim3(1024), lds, s, a);
     return hipGetLastError();
 }
