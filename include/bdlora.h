@@ -66,7 +66,8 @@ extern "C" {
 #define BDLORA_MAX_SLOTS  8192
 #define BDLORA_MAX_RANK   128
 /* Batches of at most this many tokens take the decode launch (plan, shrink,
- * base product and expand in one); larger ones take the prefill sequence
+ * base product and expand in one), as do some up to 256 tokens, in row
+ * groups; larger ones take the prefill sequence
  * (plan and packing, shrink, base product with the expand fused in, or for
  * medium batches on large layers base partials and an epilogue; see
  * bdlora_last_path). */
@@ -390,8 +391,7 @@ int bdlora_adapter_elems(const bdlora_proj_desc* projs, int32_t n_projs, int32_t
  * (every slot sized for max_rank, ranks padded to multiples of 8) and the
  * per-batch workspace (when max_tokens is above BDLORA_DECODE_MAX_T it
  * includes a fixed 64 MiB of fp32 partial tiles for the medium-batch base
- * product and the large-tile GEMM's split tiles, and 32 MiB for the split
- * shrink's partials).  Pure host function; validates the arguments as
+ * product and the large-tile GEMM's split tiles).  Pure host function; validates the arguments as
  * bdlora_create_pool does (except the device). */
 int bdlora_pool_size(const bdlora_proj_desc* projs, int32_t n_projs, int32_t max_slots,
                      int32_t max_rank, int32_t max_tokens, int64_t* slab_bytes,
@@ -403,7 +403,8 @@ int bdlora_pool_bytes(bdlora_pool_t pool, int64_t* bytes);
 /* Timing hooks.  bdlora_profile_begin(pool, n) makes the next n forward
  * calls record HIP events around each of their launches on the caller's
  * stream, in four intervals: for a decode batch (BDLORA_PATH_DECODE)
- * nothing, its one launch, nothing, nothing; for a larger batch plan and packing, shrink, base product (with the fused
+ * nothing, its one launch, nothing, nothing; for a larger batch plan and
+ * packing, shrink, base product (with the fused
  * expand, or for BDLORA_PATH_MEDIUM the partials), and for
  * BDLORA_PATH_MEDIUM its epilogue (partials plus expand), else nothing.
  * bdlora_profile_end waits for them and writes the mean duration in
@@ -417,7 +418,10 @@ int bdlora_profile_end(bdlora_pool_t pool, float* ms, int32_t* n);
  * when the call returns; the kernels may still be running), for tests and
  * tuning: *path = 0 before any forward, else one of
  *   BDLORA_PATH_DECODE  the decode launch (T <= BDLORA_DECODE_MAX_T)
- *   BDLORA_PATH_TILE64  64-row tiles, base product with the fused expand
+ *   BDLORA_PATH_TILE64  64-row tiles, base product with the fused expand: up
+ *                       to 256 tokens the decode launch over row groups of up
+ *                       to 64 tokens, above (INT4 weights, or operands too
+ *                       large for the large tiles) a 64-row GEMM
  *   BDLORA_PATH_MEDIUM  all rows of the batch in one tile (bf16 weights,
  *                       T <= 256, layers whose weight is large against the
  *                       fp32 partials or batches of at most 8 tokens per

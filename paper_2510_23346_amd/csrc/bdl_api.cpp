@@ -53,7 +53,6 @@ struct Layout {
     long long dec_flags = 0;           // decode path: producer flags
     long long mlp_elems = 0;           // prefill MLP: gate and up outputs, fp32
     long long bigpart_elems = 0;       // large-tile GEMM: fp32 partials of split tiles
-    long long shrinkpart_elems = 0;    // split shrink: fp32 partials
 };
 
 // Validates the pool arguments and computes the memory layout.
@@ -122,12 +121,13 @@ int make_layout(const bdlora_proj_desc* projs, int n_projs, int max_slots, int m
                    ((long long)max_tokens / 64 + 1) * (8LL * L->r8max + 64)) * 4;   // tile octets
     for (int p = 0; p < n_projs; ++p) ws += (L->z_elems[p] + L->xp_elems[p]) * 2;
     // decode path: Z lines and the producers' flags
-    const int dec_t = std::min(bdl::kDecodeMaxT, max_tokens);
+    // (above the decode size in row groups of up to 64 tokens)
+    const int dec_t = std::min(bdl::kRowsMaxT, (int)round_up(max_tokens, max_tokens > bdl::kDecodeMaxT ? 64 : 1));
     for (int p = 0; p < n_projs; ++p) {
         const long long nbA = (L->proj[p].zs + 15) / 16;
         L->dec_z_elems[p] = nbA * dec_t * bdl::kDecZLine;
         ws += L->dec_z_elems[p] * 2;
-        L->dec_flags += (dec_t + (dec_t - 1) / 16) * nbA;
+        L->dec_flags += (dec_t + dec_t / 16) * nbA;
     }
     ws += L->dec_flags * 8;
     int max_n = 0;                                  // widest single-slice column projection
@@ -139,9 +139,6 @@ int make_layout(const bdlora_proj_desc* projs, int n_projs, int max_slots, int m
     // above the decode size)
     L->bigpart_elems = max_tokens > bdl::kDecodeMaxT ? (long long)bdl::kBigPartSlots * bdl::kBigPartElems : 0;
     ws += L->bigpart_elems * 4;
-    // and of the split shrink (which can run beside the base product)
-    L->shrinkpart_elems = max_tokens > bdl::kDecodeMaxT ? bdl::kShrinkPartElems : 0;
-    ws += L->shrinkpart_elems * 4;
     ws += max_slots * 12LL;                                       // slot tables
     L->ws_bytes = ws;
     return BDLORA_OK;
@@ -195,7 +192,6 @@ struct bdlora_pool {
     unsigned long long* d_flags = nullptr;
     float* d_mlp = nullptr;
     float* d_bigpart = nullptr;
-    float* d_shrinkpart = nullptr;
     // medium batches: the shrink runs on side_stream, forked from the
     // caller's stream after the prep launch and joined back before the
     // epilogue
@@ -242,7 +238,6 @@ void free_pool(bdlora_pool* P) {
     f(P->d_flags);
     f(P->d_mlp);
     f(P->d_bigpart);
-    f(P->d_shrinkpart);
     for (auto x : P->d_Xp) f(x);
     f(P->d_stage);
     for (auto e : P->prof_ev) (void)hipEventDestroy(e);
@@ -465,7 +460,6 @@ int bdlora_create_pool(const bdlora_proj_desc* projs, int32_t n_projs, int32_t m
     BDL_TRY(dev_alloc(&P->d_flags, L.dec_flags, &tot));
     BDL_TRY(dev_alloc(&P->d_mlp, L.mlp_elems, &tot));
     if (L.bigpart_elems > 0) BDL_TRY(dev_alloc(&P->d_bigpart, L.bigpart_elems, &tot));
-    if (L.shrinkpart_elems > 0) BDL_TRY(dev_alloc(&P->d_shrinkpart, L.shrinkpart_elems, &tot));
     BDL_TRY(dev_alloc(&P->d_perm, MT, &tot));
     BDL_TRY(dev_alloc(&P->d_rowtok, MT, &tot));
     BDL_TRY(dev_alloc(&P->d_rowslot, MT, &tot));
@@ -694,11 +688,11 @@ struct Shapes {
 // activations) that still leaves enough workgroups to occupy the chip.
 static Shapes pick_shapes(int T, long long col_blocks = 0, int r8max = bdl::kMaxRank8) {
     Shapes k;
-    // prefill shrink items: 64 rows x 64 rank columns; when no adapter is
-    // wider than rank 32, 32 rows x 96 columns, so that the three slices of
-    // a q/k/v projection come out of one pass over its rows of X
-    k.smb = T <= 512 ? 1 : (r8max <= 32 ? 2 : 4);
-    k.snb = T <= 512 ? 1 : (r8max <= 32 ? 6 : 4);
+    // Shrink items: BDL_SH rows x the columns of a projection's slices at the
+    // pool's rank
+    const bool wide = T > 512;
+    k.snb = r8max <= 16 ? 3 : r8max <= 32 ? 6 : 4;
+    k.smb = !wide ? 1 : r8max > 32 && T > 512 ? 4 : 2;
     k.gmb = T <= 16 ? 1 : (T <= 32 ? 2 : 4);
     const long long row_tiles = (T + 16 * k.gmb - 1) / (16 * k.gmb);
     const long long blocks = col_blocks * row_tiles;
@@ -744,18 +738,23 @@ static const uint16_t* int4_scales(const ProjInfo& pi, const void* W) {
     return reinterpret_cast<const uint16_t*>(static_cast<const char*>(W) + (size_t)pi.N * pi.K / 2);
 }
 
+static int loaded_adapters(bdlora_pool_t P) {
+    int n = 0;
+    for (int v : P->h_loaded) n += v != 0;
+    return n;
+}
+
+// Row groups of a batch in the decode launch: the fewest, of nearly equal size.
+static int dec_groups(int T) { return (T + bdl::kDecodeMaxT - 1) / bdl::kDecodeMaxT; }
+
 // Adapter positions of a decode call's launch: the loaded adapters bound
 // the distinct ones a batch can use (the plan treats any past that bound as
 // none and raises the error flag).  Both forms of the batch (ids, segments)
 // take the same launch geometry, so they give the same bits.
 static int decode_act_max(bdlora_pool_t P, int T) {
-    int n_loaded = 0;
-    for (int v : P->h_loaded) n_loaded += v != 0;
-    return std::min({T, n_loaded, bdl::kDecodeMaxT});
+    return std::min({T, loaded_adapters(P), bdl::kDecodeMaxT});
 }
 
-// Decode batches, one launch.  Z: where the call's i-th projection keeps its
-// Z lines.  The MLP's first call (mlp_act >= 0) writes the intermediate to h.
 struct DecZ {
     uint16_t* z[bdl::kMaxProjs];
 };
@@ -775,7 +774,10 @@ static int forward_decode(bdlora_pool_t P, int n, const int32_t* projs, const vo
     da.n_proj = n;
     da.T = T;
     da.r8max = L.r8max;
-    da.act_max = decode_act_max(P, T);
+    da.groups = dec_groups(T);
+    da.rows = (T + da.groups - 1) / da.groups;
+    // (a captured forward above the decode size must hold for adapters loaded later)
+    da.act_max = T <= bdl::kDecodeMaxT ? decode_act_max(P, T) : std::min(da.rows, L.max_slots);
     da.pair = mlp_act == BDLORA_ACT_SILU_MUL ? 1 : 0;
     da.h_dst = h;
     // longest K first: the projections with the longest workgroups
@@ -783,7 +785,7 @@ static int forward_decode(bdlora_pool_t P, int n, const int32_t* projs, const vo
     for (int i = 0; i < n; ++i) order[i] = i;
     if (!da.pair)
         std::stable_sort(order, order + n, [&](int x, int y) { return L.proj[projs[x]].K > L.proj[projs[y]].K; });
-    const int waves = bdl::dec_waves((T + 15) / 16);
+    const int waves = bdl::dec_waves((da.rows + 15) / 16);
     int tiles = 0, shrinks = 0;
     for (int q = 0; q < n; ++q) {
         const int i = order[q];
@@ -803,7 +805,7 @@ static int forward_decode(bdlora_pool_t P, int n, const int32_t* projs, const vo
         d.nbA = (pi.S * L.r8max + 15) / 16;
         da.shrink_base[q] = shrinks;
         // (adapter, 16 tokens) items: sum of ceil(tokens / 16) over the adapters in use
-        shrinks += (da.act_max > 0 ? da.act_max + (T - 1) / 16 : 0) * d.nbA;
+        shrinks += (da.act_max > 0 ? da.act_max + (da.rows - 1) / 16 : 0) * d.nbA;
         const int KS = pi.K / 32;
         // about 16 k-steps per part, as far as the workgroup's waves go
         d.kparts = std::min(waves, KS >= 64 ? 8 : KS >= 32 ? 4 : KS >= 16 ? 2 : 1);
@@ -817,13 +819,13 @@ static int forward_decode(bdlora_pool_t P, int n, const int32_t* projs, const vo
         for (int q = 1; q < n; ++q) da.shrink_base[q] = 1;        // its one workgroup only checks the ids
     da.wait_ticks = 20000;                                        // 200 us
     da.flags = P->d_flags;
-    if (da.n_shrink > L.dec_flags) return fail(BDLORA_ERR_SHAPE, "batch exceeds the pool workspace");
+    if ((long long)da.groups * da.n_shrink > L.dec_flags) return fail(BDLORA_ERR_SHAPE, "batch exceeds the pool workspace");
     da.pool = P->d_slabs;
     da.slot_stride = L.slot_stride;
     da.scale = P->d_scale;
     da.ids = B.ids;
     da.n_seg = B.ids ? 0 : B.n_seg;
-    if (da.n_seg > bdl::kDecodeMaxT) return fail(BDLORA_ERR_INVALID_ARG, "more segments than tokens");
+    if (da.n_seg > bdl::kRowsMaxT) return fail(BDLORA_ERR_INVALID_ARG, "more segments than tokens");
     for (int i = 0; i < da.n_seg; ++i) {
         da.seg_start[i] = B.seg_start[i];
         da.seg_slot[i] = B.seg_slot[i];
@@ -839,16 +841,16 @@ static int forward_decode(bdlora_pool_t P, int n, const int32_t* projs, const vo
         ++P->prof_used;
         --P->prof_left;
     }
+    const int before = T <= bdl::kDecodeMaxT ? 3 : 5;              // the launch's timing interval: 1 or 2
     if (ev)
-        for (int i = 0; i < 3; ++i) BDL_HIP(hipEventRecord(ev[i], s));
-    BDL_HIP(bdl::launch_dec_main(da, (T + 15) / 16, s));
+        for (int i = 0; i < before; ++i) BDL_HIP(hipEventRecord(ev[i], s));
+    BDL_HIP(bdl::launch_dec_main(da, (da.rows + 15) / 16, s));
     if (ev)
-        for (int i = 3; i < kProfEvents; ++i) BDL_HIP(hipEventRecord(ev[i], s));
-    P->last_path = BDLORA_PATH_DECODE;
+        for (int i = before; i < kProfEvents; ++i) BDL_HIP(hipEventRecord(ev[i], s));
+    P->last_path = T <= bdl::kDecodeMaxT ? BDLORA_PATH_DECODE : BDLORA_PATH_TILE64;
     return BDLORA_OK;
 }
 
-static bool use_decode(int T) { return T <= bdl::kDecodeMaxT; }
 
 // Batches above the decode size: prep (plan + packing; with pack = false the
 // packed activations are already in place), shrink, base product with the
@@ -858,9 +860,71 @@ static bool use_decode(int T) { return T <= bdl::kDecodeMaxT; }
 struct MlpOut {
     int act;                 // BDLORA_ACT_*
     uint16_t* h;             // H in the fragment layout of down's input
-    int h_KS;                // its k-steps (down's d_in / 32)
+    int h_KS;                // its k-steps (down's d_in / 32); 0 (medium-batch path): H row-major
     float* f32[2];           // 64-row path: the projections' fp32 outputs (formed into H afterwards)
 };
+
+// The medium-batch launches (bf16 weights, kDecodeMaxT < T <= kMidMaxT, all
+// rows of the batch in one tile, each weight fragment read once): whether a
+// call takes them, and how its tiles of 8 waves x nb column blocks are cut
+// into k-ranges so that the items fill the chip once, every item storing one
+// partial tile.
+struct MidPlan {
+    bool use = false;
+    int nb = 2;                    // column blocks per wave
+    int split[bdl::kMaxProjs] = {};   // k-ranges per tile
+    int items = 0;
+};
+
+static MidPlan plan_mid(bdlora_pool_t P, int n, const int32_t* projs, int T, int n_loaded) {
+    const Layout& L = P->L;
+    MidPlan m;
+    if (T <= bdl::kDecodeMaxT || T > bdl::kMidMaxT || !P->d_bigpart) return m;
+    for (int i = 0; i < n; ++i) {
+        // (32-bit byte offsets into X and W)
+        const ProjInfo& pi = L.proj[projs[i]];
+        const long long xb = ((long long)T + 15) / 16 * 16 * pi.K * 2, wb = (long long)pi.N * pi.K * 2;
+        if (pi.wfmt != BDLORA_WEIGHT_BF16 || xb >= (1LL << 31) || wb >= (1LL << 31)) return m;
+    }
+    const long long units = std::min<long long>(P->n_cu, bdl::kBigPartSlots);
+    long long work = 0;
+    auto cut = [&](int nb) {
+        const int tn = 128 * nb;
+        m.nb = nb;
+        work = 0;
+        for (int i = 0; i < n; ++i) work += (long long)((L.proj[projs[i]].N + tn - 1) / tn) * (L.proj[projs[i]].K / 32);
+        for (long long q = std::max(1LL, (work + units - 1) / units); q < 1024; ++q) {
+            m.items = 0;
+            for (int i = 0; i < n; ++i) {
+                const ProjInfo& pi = L.proj[projs[i]];
+                m.split[i] = (int)std::max(1LL, (long long)(pi.K / 32) / q);
+                m.items += (pi.N + tn - 1) / tn * m.split[i];
+            }
+            if (m.items <= bdl::kBigPartSlots) return true;
+        }
+        return false;              // every tile unsplit and still more partials than the workspace holds
+    };
+    if (!cut(2)) return m;
+    // The partials' round trip (written, then read by the epilogue) must stay
+    // well below the weight bytes, of which the row groups of the other path
+    // read most from the caches again (70B layer shard, 256 tokens: 152
+    // against 234 us a step, 100 tokens 107 against 123; 8B, a quarter of the
+    // weights, 100 tokens 52 against 35); or the batch spreads over many
+    // adapters (at most 8 tokens per loaded adapter): its shrink is then long,
+    // and this path runs it beside the base product.
+    long long part_bytes = 0, w_bytes = 0;
+    for (int i = 0; i < n; ++i) {
+        const ProjInfo& pi = L.proj[projs[i]];
+        part_bytes += (long long)((pi.N + 255) / 256) * m.split[i] * ((T + 15) / 16 * 16) * 256 * 4;
+        w_bytes += (long long)pi.N * pi.K * 2;
+    }
+    m.use = 2 * part_bytes * 10 <= 6 * w_bytes || T <= 8 * n_loaded;
+    // short k-ranges: half the columns per tile instead, so half the partials
+    // (8B layer shard, 150 tokens: GEMM and epilogue 41 -> 39 us; with long
+    // ranges it costs: 70B at 256 tokens 151 -> 233 us a step)
+    if (m.use && work < 32 * units && !cut(1)) cut(2);
+    return m;
+}
 
 static int forward_prefill(bdlora_pool_t P, int n, const int32_t* projs, const void* const* X,
                            const void* const* W, void* const* out, const Batch& B, int T, hipStream_t s,
@@ -868,8 +932,12 @@ static int forward_prefill(bdlora_pool_t P, int n, const int32_t* projs, const v
     const Layout& L = P->L;
     long long col_blocks = 0;
     for (int i = 0; i < n; ++i) col_blocks += L.proj[projs[i]].N / 16;
+    // the loaded adapters bound the distinct ones the batch can use; the
+    // path choices below take that bound (the host does not see device ids,
+    // and both forms of the batch must take the same launches)
+    const int n_loaded = loaded_adapters(P);
     const Shapes k = pick_shapes(T, col_blocks, L.r8max);
-    const int mts = 16 * k.smb, nts = 16 * k.snb;
+    const int mts = 16 * k.smb;
     const int MT = 16 * k.gmb, NT = 16 * k.gnb;
 
     bdl::FwdArgs fa;
@@ -882,11 +950,6 @@ static int forward_prefill(bdlora_pool_t P, int n, const int32_t* projs, const v
             return (long long)L.proj[projs[x]].K * L.proj[projs[x]].N >
                    (long long)L.proj[projs[y]].K * L.proj[projs[y]].N;
         });
-    // the loaded adapters bound the distinct ones the batch can use; the
-    // path choices below take that bound (the host does not see device ids,
-    // and both forms of the batch must take the same launches)
-    int n_loaded = 0;
-    for (int v : P->h_loaded) n_loaded += v != 0;
     // bf16 weights above one 256-row tile: the 256 x 256 LDS-staged kernel
     // (its octet lists are those of 64-row blocks, as planned for T > 32),
     // with long-K tiles split into k-ranges when the batch has too few tiles
@@ -900,56 +963,9 @@ static int forward_prefill(bdlora_pool_t P, int n, const int32_t* projs, const v
         const long long xb = ((long long)T + 15) / 16 * 16 * pi.K * 2, wb = (long long)pi.N * pi.K * 2;
         big = big && pi.wfmt == BDLORA_WEIGHT_BF16 && xb < (1LL << 31) && wb < (1LL << 31);
     }
-    // bf16 weights at medium batches: all rows in one tile of the medium-batch
-    // launch (each weight fragment read once), whose partials the 64-row
-    // kernel adds to the expand.  8 waves x mid_nb column blocks per tile;
-    // long-K tiles are cut into k-ranges of about q k-steps so that the
-    // items fill the chip once, every item storing one partial tile.
-    bool mid = !big && T > bdl::kDecodeMaxT && T <= bdl::kMidMaxT && MT == 64 && P->d_bigpart != nullptr;
-    for (int i = 0; i < n; ++i) {
-        const ProjInfo& pi = L.proj[projs[i]];
-        const long long xb = ((long long)T + 15) / 16 * 16 * pi.K * 2, wb = (long long)pi.N * pi.K * 2;
-        mid = mid && pi.wfmt == BDLORA_WEIGHT_BF16 && xb < (1LL << 31) && wb < (1LL << 31);
-    }
-    const int mid_nb = 2, mid_rb = T <= 128 ? 8 : 16, mid_tn = 128 * mid_nb;
-    int mid_split[bdl::kMaxProjs];
-    int mid_items = 0;
-    if (mid) {
-        long long work = 0;
-        for (int i = 0; i < n; ++i) {
-            const ProjInfo& pi = L.proj[projs[i]];
-            work += (long long)((pi.N + mid_tn - 1) / mid_tn) * (pi.K / 32);
-        }
-        const long long units = std::min<long long>(P->n_cu, bdl::kBigPartSlots);
-        for (long long q = std::max(1LL, (work + units - 1) / units);; ++q) {
-            mid_items = 0;
-            for (int i = 0; i < n; ++i) {
-                const ProjInfo& pi = L.proj[projs[i]];
-                mid_split[i] = (int)std::max(1LL, (long long)(pi.K / 32) / q);
-                mid_items += (pi.N + mid_tn - 1) / mid_tn * mid_split[i];
-            }
-            if (mid_items <= bdl::kBigPartSlots) break;
-            // every tile unsplit and still more partials than the workspace holds
-            if (q >= 1024) {
-                mid = false;
-                break;
-            }
-        }
-        // The partials' round trip (written, then read by the epilogue) must
-        // stay well below the weight bytes the launch saves re-reading: short
-        // K ranges (small layers) make the partials as large as the weight,
-        // and then the 64-row kernel is as fast or faster -- unless the batch
-        // spreads over many adapters (at most 8 tokens per loaded adapter):
-        // its shrink is then long, and this path runs it beside the base
-        // product instead of before it.
-        long long part_bytes = 0, w_bytes = 0;
-        for (int i = 0; i < n; ++i) {
-            const ProjInfo& pi = L.proj[projs[i]];
-            part_bytes += (long long)((pi.N + mid_tn - 1) / mid_tn) * mid_split[i] * ((T + 15) / 16 * 16) * mid_tn * 4;
-            w_bytes += (long long)pi.N * pi.K * 2;
-        }
-        mid = mid && (2 * part_bytes * 10 <= 6 * w_bytes || T <= 8 * n_loaded);
-    }
+    const MidPlan mp = plan_mid(P, n, projs, T, n_loaded);
+    const bool mid = !big && mp.use;
+    const int mid_rb = T <= 128 ? 8 : 16, mid_tn = 128 * mp.nb;
     // MLP on the large-tile and medium-batch paths: their epilogues form H
     // and write it once, in bf16 (gate and up in paired tiles); on the
     // 64-row path the projections write fp32 and a pack launch forms H
@@ -985,12 +1001,12 @@ static int forward_prefill(bdlora_pool_t P, int n, const int32_t* projs, const v
     // the medium-batch GEMM's copies (one k-step of a row at a time) and its
     // shrink read the caller's X too, for any K
     if (mid && pack) xrm = true;
-    int tile = 0, cch = 1, fix = 0, pslot = 0, mid_cols = 0;
+    int tile = 0, fix = 0, pslot = 0, mid_cols = 0;
     for (int q = 0; q < n; ++q) {
         const int i = order[q];
         const ProjInfo& pi = L.proj[projs[i]];
         bdl::ProjLaunch& pl = fa.p[q];
-        pl.X = (const uint16_t*)X[i];
+        pl.X = pack ? (const uint16_t*)X[i] : nullptr;
         pl.Xp = P->d_Xp[projs[i]];
         // the large and medium-batch tiles and their shrink gather rows of
         // the caller's X directly (32-bit offsets: T K 2 < 2^31 is part of
@@ -1027,13 +1043,14 @@ static int forward_prefill(bdlora_pool_t P, int n, const int32_t* projs, const v
             pslot += pl.fix_count * pl.ksplit;
         }
         if (mid) {
-            pl.ksplit = mid_split[i];
+            pl.ksplit = mp.split[i];
             pl.part_base = pslot;
-            pslot += (pi.N + mid_tn - 1) / mid_tn * mid_split[i];
+            pslot += (pi.N + mid_tn - 1) / mid_tn * mp.split[i];
             pl.col_base = mid_cols;
             if (!(paired && q == 1)) mid_cols += (pi.N + 63) / 64;
         }
-        cch = std::max(cch, (pi.S * L.r8max + nts - 1) / nts);
+        const int sb = 16 * bdl::shrink_blocks(k.snb, pi.S * L.r8max);
+        fa.schunks[q] = (pi.S * L.r8max + sb - 1) / sb;
     }
     fa.n_proj = n;
     fa.T = T;
@@ -1049,32 +1066,20 @@ static int forward_prefill(bdlora_pool_t P, int n, const int32_t* projs, const v
     // (groups + T / mts) in all, groups bounded by the slots (device ids: a
     // bound that holds whatever is loaded when a captured forward replays)
     fa.items_bound = std::min(T, L.max_slots) + (T + mts - 1) / mts;
-    fa.cchunks = cch;
-    // Small batches over many adapters (groups of a few scattered tokens, at
-    // most 8 per loaded adapter on average) split each shrink item's K over
-    // the XCDs, partials in their own workspace.  Few large groups read X
-    // about once anyway; there the split would only add the partials'
-    // traffic.
-    fa.shrink_kp = 1;
-    fa.shrinkpart = P->d_shrinkpart;
-    // the unsplit shrink's unit order: longest K first (its units' length),
-    // so the short ones fill the end
+    // the shrink's unit order: longest K first (its units' length), so the
+    // short ones fill the end
     fa.queue = P->d_meta + 2;
     for (int q = 0; q < n; ++q) fa.sorder[q] = q;
     std::stable_sort(fa.sorder, fa.sorder + n, [&](int x, int y) { return fa.p[x].K > fa.p[y].K; });
-    if (T <= 512 && T <= 8 * n_loaded && P->d_shrinkpart &&
-        (long long)n * fa.items_bound * cch * bdl::kShrinkKP * mts * nts <= L.shrinkpart_elems)
-        fa.shrink_kp = bdl::kShrinkKP;
     fa.tile_oct = P->d_tile_oct;
     fa.oct_cap = oct_cap(L, MT);
     fa.tiles_m = tm;
     fa.total_tiles = tile;
     fa.bigpart = P->d_bigpart;
-    fa.fixup = 0;
     fa.total_fix = fix;
     fa.mid_rb = mid_rb;
-    fa.mid_nb = mid_nb;
-    fa.mid_items = mid ? mid_items : 0;
+    fa.mid_nb = mp.nb;
+    fa.mid_items = mid ? mp.items : 0;
     fa.mid_col_tiles = mid ? mid_cols : 0;
     fa.max_slots = L.max_slots;
     fa.mlp_act = h_fused ? mlp->act : -1;
@@ -1166,6 +1171,17 @@ static int forward_prefill(bdlora_pool_t P, int n, const int32_t* projs, const v
     return BDLORA_OK;
 }
 
+// The decode launch serves the decode batches, and those up to kRowsMaxT that
+// the medium-batch launches do not take, in row groups of up to 64 tokens
+// (8B layer shard, microseconds a step against the plan, shrink and 64-row
+// GEMM launches before it: 100 tokens 58 -> 35, 150 tokens 72 -> 41, 250
+// tokens 84 -> 54; on an INT4 base, 150 tokens, 63 -> 38; 1B, 100 tokens
+// 35 -> 18).  Above 256 tokens the large tiles win (and, on an INT4 base, the
+// 64-row kernel, whose cost per row falls further).
+static bool use_rows(bdlora_pool_t P, int n, const int32_t* projs, int T) {
+    return T <= bdl::kDecodeMaxT || (T <= bdl::kRowsMaxT && !plan_mid(P, n, projs, T, loaded_adapters(P)).use);
+}
+
 // The batch's adapters: device ids, or host segments checked here (tiling
 // 0..T-1 in order, every slot loaded or -1) and copied into *B.
 static int read_batch(bdlora_pool_t P, const int32_t* ids, const bdlora_segments* sg, int T, Batch* B) {
@@ -1227,7 +1243,7 @@ int bdlora_forward_layer(bdlora_pool_t P, int32_t n, const int32_t* projs, const
     if (!guard.ok) return fail(BDLORA_ERR_HIP, "hipSetDevice failed");
     hipStream_t s = (hipStream_t)stream;
 
-    if (use_decode(T)) return forward_decode(P, n, projs, X, W, out, B, T, s, pool_dec_z(P, n, projs).z);
+    if (use_rows(P, n, projs, T)) return forward_decode(P, n, projs, X, W, out, B, T, s, pool_dec_z(P, n, projs).z);
     return forward_prefill(P, n, projs, X, W, out, B, T, s);
 }
 
@@ -1326,17 +1342,24 @@ int bdlora_forward_mlp(bdlora_pool_t P, int32_t act, const int32_t* first, int32
     const int32_t dn[1] = {down};
     const void* wd[1] = {W_down};
     void* od[1] = {out};
-    if (use_decode(T)) {
-        // first projections: they write H, row-major, where down reads it
-        const void* xd[1] = {h};
+    if (T <= bdl::kRowsMaxT) {
+        // the first projections write H, row-major, where down reads it
         void* none[2] = {nullptr, nullptr};
-        int rc = forward_decode(P, nf, first, xs, W_first, none, B, T, s, pool_dec_z(P, nf, first).z, act, h);
+        const void* xd[1] = {h};
+        MlpOut mo{};
+        mo.act = act;
+        mo.h = h;
+        mo.h_KS = 0;                               // row-major
+        int rc = use_rows(P, nf, first, T)
+                     ? forward_decode(P, nf, first, xs, W_first, none, B, T, s, pool_dec_z(P, nf, first).z, act, h)
+                     : forward_prefill(P, nf, first, xs, W_first, none, B, T, s, true, &mo);
         if (rc) return rc;
-        return forward_decode(P, 1, dn, xd, wd, od, B, T, s, pool_dec_z(P, 1, dn).z);
+        return use_rows(P, 1, dn, T) ? forward_decode(P, 1, dn, xd, wd, od, B, T, s, pool_dec_z(P, 1, dn).z)
+                                     : forward_prefill(P, 1, dn, xd, wd, od, B, T, s);
     }
     // larger batches: the first projections' epilogue writes H (bf16,
-    // packed as down's input) on the large-tile and medium-batch paths; on
-    // the 64-row path they write fp32 to the pool's workspace and a pack
+    // packed as down's input) on the large-tile path; on the 64-row path
+    // they write fp32 to the pool's workspace and a pack
     // launch forms H.  Then down reads H in place.
     MlpOut mo;
     mo.act = act;

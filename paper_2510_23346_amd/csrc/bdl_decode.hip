@@ -17,24 +17,6 @@
 
 namespace bdl {
 
-// The kernel's by-value argument where the launch put it.  (Named as a
-// parameter and indexed with a projection number that depends on the
-// workgroup, it would be copied to scratch memory first.)
-template <class T>
-__device__ __forceinline__ const T& kernel_args() {
-    return *(const T*)(const __attribute__((address_space(4))) T*)__builtin_amdgcn_kernarg_segment_ptr();
-}
-
-constexpr unsigned kOob = 0x7ffffff0u;      // byte offset past every buffer: the load returns zeros
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t dec_rsrc(const void* p, unsigned bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)bytes, kRawBufferWord3);
-}
-
-__device__ __forceinline__ u32x4 buf16(__amdgpu_buffer_rsrc_t r, unsigned off) {
-    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
-}
-
 // A producer workgroup raises its own 64-bit flag in device memory (a.flags)
 // once its stores have reached memory: the flag takes the launch's tag, which
 // no other launch has had (the dispatch packet's running number in its queue,
@@ -87,7 +69,8 @@ __device__ __forceinline__ void split3(float z, uint32_t (&b)[3]) {
     b[2] = __float_as_uint(q) >> 16;
 }
 
-// The batch's plan, computed by one wave (lane t holds token t; T <= 64):
+// The plan of T <= 64 tokens from t0 on, computed by one wave (lane t holds
+// token t0 + t):
 // ids checked against the loaded slots, the adapters in use in ascending slot
 // order ("groups"; at most act_max of them: any past that bound, possible
 // only when a captured forward replays after more adapters were loaded, are
@@ -106,7 +89,7 @@ struct Plan {
     bool bad;       // some id named no adapter (uniform)
 };
 
-__device__ __forceinline__ PlanLoads dec_plan_loads(const DecArgs& a) {
+__device__ __forceinline__ PlanLoads dec_plan_loads(const DecArgs& a, int t0, int T) {
     const int l = threadIdx.x & 63;
     const bool small = a.max_slots <= 64;
     PlanLoads r;
@@ -114,19 +97,19 @@ __device__ __forceinline__ PlanLoads dec_plan_loads(const DecArgs& a) {
     r.rt = small && l < a.max_slots ? a.r8[l] : 0;
     r.id = -1;
     if (a.ids) {
-        if (l < a.T) r.id = a.ids[l];
+        if (l < T) r.id = a.ids[t0 + l];
     } else {
         // segments in token order: the last one starting at or before t
         for (int i = 0; i < a.n_seg; ++i)
-            if (l >= a.seg_start[i]) r.id = a.seg_slot[i];
-        if (l >= a.T) r.id = -1;
+            if (t0 + l >= a.seg_start[i]) r.id = a.seg_slot[i];
+        if (l >= T) r.id = -1;
     }
     return r;
 }
 
-__device__ __forceinline__ Plan dec_plan(const DecArgs& a, const PlanLoads& ld) {
+__device__ __forceinline__ Plan dec_plan(const DecArgs& a, const PlanLoads& ld, int T) {
     const int l = threadIdx.x & 63;
-    const bool in = l < a.T;
+    const bool in = l < T;
     const bool small = a.max_slots <= 64;
     const int lt = ld.lt, rt = ld.rt, id = ld.id;
     const bool in_range = id >= 0 && id < a.max_slots;
@@ -196,57 +179,10 @@ __device__ __forceinline__ int dec_items(const Plan& pl, int* cnt) {
     return (cnt[l] + 15) >> 4;
 }
 
-// Activations.  A wave takes the caller's row-major X in pairs of k-steps: 16
-// rows x 128 bytes with two loads in which eight lanes cover a row's line
-// (lanes 16 rows apart, as the MFMA operand wants them, would touch a line per
-// lane), through its own buffer in LDS, from which the operand fragments
-// are read.  Lane l takes row 8 h + l / 8 and chunk (l mod 8) ^
-// swizzle(row), so that both sides hit distinct banks.
-__device__ __forceinline__ int x_swz(int r) { return ((r >> 1) ^ ((r & 1) << 2)) & 7; }
-
-template <int MB>
-struct XRows {
-    __amdgpu_buffer_rsrc_t rx;
-    unsigned ro[MB][2];     // byte offset of this lane's chunk of pair 0
-    u32x4* buf;             // this wave's MB x 128 pieces
-    int pos[2];             // where this lane's operand of k-step e of a pair lies in a row block
-
-    // row(i): the X row of row i of the MB 16-row blocks
-    template <class Row>
-    __device__ __forceinline__ void init(const uint16_t* X, int K, int T, u32x4* lds, Row row) {
-        const int l = threadIdx.x & 63, lr = l & 15, lg = l >> 4;
-        rx = dec_rsrc(X, (unsigned)T * K * 2u);
-        buf = lds;
-#pragma unroll
-        for (int rb = 0; rb < MB; ++rb)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int r = 8 * h + (l >> 3);
-                ro[rb][h] = (unsigned)row(rb * 16 + r) * K * 2u + (unsigned)((l & 7) ^ x_swz(r)) * 16u;
-            }
-#pragma unroll
-        for (int e = 0; e < 2; ++e) pos[e] = (lr >> 3) * 64 + (lr & 7) * 8 + ((4 * e + lg) ^ x_swz(lr));
-    }
-    // pair g (its k-steps 2 g, 2 g + 1); ok false: zeros, no memory traffic
-    __device__ __forceinline__ void load(u32x4 (&v)[MB][2], int g, bool ok) const {
-#pragma unroll
-        for (int rb = 0; rb < MB; ++rb)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) v[rb][h] = buf16(rx, ok ? ro[rb][h] + (unsigned)g * 128u : kOob);
-    }
-    // (the wave's LDS operations run in order, so one buffer does: a pair is
-    // written after the last one's reads; the fences keep the compiler's order)
-    __device__ __forceinline__ void put(const u32x4 (&v)[MB][2]) const {
-        const int l = threadIdx.x & 63;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-#pragma unroll
-        for (int rb = 0; rb < MB; ++rb)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) buf[rb * 128 + h * 64 + l] = v[rb][h];
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    }
-    __device__ __forceinline__ u32x4 get(int rb, int e) const { return buf[rb * 128 + pos[e]]; }
-};
+// Z of row group g
+__device__ __forceinline__ uint16_t* dec_z(const DecArgs& a, const DecProj& P, int g) {
+    return P.Z + (size_t)g * P.nbA * a.rows * kDecZLine;
+}
 
 // Z of row block c of A^T for 16 tokens (row block rb) of group ai, stored as
 // one 128-byte line per (c, token): three planes of 16 bf16 numbers.  The
@@ -256,7 +192,7 @@ constexpr int kShrinkChunk = 8;
 
 template <int NW>
 __device__ __forceinline__ void dec_shrink(const DecArgs& a, const DecProj& P, const Plan& pl, int ai, int rb, int c,
-                                           u32x4* lds) {
+                                           const uint16_t* X, uint16_t* Z, int T, u32x4* lds) {
     const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lg = l >> 4;
     const int r8s = __builtin_amdgcn_readlane(pl.gr, ai), slot = __builtin_amdgcn_readlane(pl.gs, ai);
     const float sc = a.scale[slot];
@@ -268,9 +204,9 @@ __device__ __forceinline__ void dec_shrink(const DecArgs& a, const DecProj& P, c
 
     const int KS = P.K >> 5, NP = (KS + 1) >> 1, g0 = NP * w / NW, n = NP * (w + 1) / NW - g0;
     const __amdgpu_buffer_rsrc_t ra =
-        dec_rsrc(a.pool + (size_t)slot * a.slot_stride + P.a_off + frag_index(c, 0, KS), KS * 1024u);
+        buf_rsrc(a.pool + (size_t)slot * a.slot_stride + P.a_off + frag_index(c, 0, KS), KS * 1024u);
     XRows<1> x;
-    x.init(P.X, P.K, a.T, lds + w * 128, [=](int r) { return __shfl(toks, min(rb * 16 + r, cnt - 1)); });
+    x.init(X, P.K, T, lds + w * 128, [=](int r) { return __shfl(toks, min(rb * 16 + r, cnt - 1)); });
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int i = 0; i < n; i += kShrinkChunk) {
         u32x4 av[kShrinkChunk][2], xv[kShrinkChunk][1][2];
@@ -304,7 +240,7 @@ __device__ __forceinline__ void dec_shrink(const DecArgs& a, const DecProj& P, c
             uint32_t b[4][3];
 #pragma unroll
             for (int e = 0; e < 4; ++e) split3(sc * v[e], b[e]);
-            uint16_t* z = P.Z + ((size_t)c * a.T + t) * kDecZLine + 4 * lg;
+            uint16_t* z = Z + ((size_t)c * a.rows + t) * kDecZLine + 4 * lg;
 #pragma unroll
             for (int q = 0; q < 3; ++q)
                 __hip_atomic_store(reinterpret_cast<unsigned long long*>(z + 16 * q),
@@ -328,7 +264,7 @@ __device__ __forceinline__ void dec_k_bf16(f32x4 (&acc)[MB][NB], const DecProj* 
     const int l = threadIdx.x & 63, NP = (KS + 1) >> 1, g0 = NP * kq / kparts, n = NP * (kq + 1) / kparts - g0;
     __amdgpu_buffer_rsrc_t rw[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) rw[c] = dec_rsrc(Pc[C0 + c]->W + frag_index(blk[C0 + c], 0, KS), KS * 1024u);
+    for (int c = 0; c < NC; ++c) rw[c] = buf_rsrc(Pc[C0 + c]->W + frag_index(blk[C0 + c], 0, KS), KS * 1024u);
     u32x4 wv[D][2][NC], xv[D][MB][2];
     auto load = [&](int d, int i) __attribute__((always_inline)) {
         const bool ok = i < n;
@@ -382,9 +318,9 @@ __device__ __forceinline__ void dec_k_int4(f32x4 (&acc)[MB][NB], const DecProj* 
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
         const DecProj& P = *Pc[C0 + c];
-        rw[c] = dec_rsrc(reinterpret_cast<const char*>(P.W) + (size_t)blk[C0 + c] * KS * kInt4FragBytes,
+        rw[c] = buf_rsrc(reinterpret_cast<const char*>(P.W) + (size_t)blk[C0 + c] * KS * kInt4FragBytes,
                          KS * (unsigned)kInt4FragBytes);
-        rs[c] = dec_rsrc(P.Ws + (size_t)blk[C0 + c] * G * 16, G * 32u);
+        rs[c] = buf_rsrc(P.Ws + (size_t)blk[C0 + c] * G * 16, G * 32u);
     }
     uint32_t q[DW][NC][4];
     u32x4 xv[D][2][MB][2];
@@ -503,15 +439,16 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lg = l >> 4;
     const int bid = blockIdx.x;
 
-    if (bid < a.n_shrink) {
-        const Plan pl = dec_plan(a, dec_plan_loads(a));
-        if (bid == 0 && pl.bad && threadIdx.x == 0) atomicOr(a.err, 1);
+    if (bid < a.groups * a.n_shrink) {
+        const int g = bid / a.n_shrink, sb = bid - g * a.n_shrink, t0 = g * a.rows, T = min(a.rows, a.T - t0);
+        const Plan pl = dec_plan(a, dec_plan_loads(a, t0, T), T);
+        if (sb == 0 && pl.bad && threadIdx.x == 0) atomicOr(a.err, 1);
         int p = 0;
 #pragma unroll
         for (int q = 1; q < kMaxProjs; ++q)
-            if (q < a.n_proj && bid >= a.shrink_base[q]) p = q;
+            if (q < a.n_proj && sb >= a.shrink_base[q]) p = q;
         const DecProj& P = a.p[p];
-        const int idx = bid - a.shrink_base[p], item = idx / P.nbA, c = idx - item * P.nbA;
+        const int idx = sb - a.shrink_base[p], item = idx / P.nbA, c = idx - item * P.nbA;
         // items are numbered group after group
         const int nit = dec_items(pl, s_cnt[w]), incl = wave_incl_scan(nit);
         const unsigned long long after = __ballot(incl > item);
@@ -519,14 +456,19 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
             const int ai = __ffsll((long long)after) - 1;
             const int rb = item - (__builtin_amdgcn_readlane(incl, ai) - __builtin_amdgcn_readlane(nit, ai));
             if (c * 16 < P.n_slices * __builtin_amdgcn_readlane(pl.gr, ai)) {
-                dec_shrink<NW>(a, P, pl, ai, rb, c, lds);
+                dec_shrink<NW>(a, P, pl, ai, rb, c, P.X + (size_t)t0 * P.K, dec_z(a, P, g), T, lds);
             }
         }
         if (threadIdx.x == 0) raise_flag(a, bid);
         return;
     }
 
-    const int mbid = bid - a.n_shrink;
+    // the row groups of a tile run on one XCD (workgroup b runs on XCD b mod 8)
+    // close together, so that its L2 serves the weights to all but the first
+    const int mb0 = bid - a.groups * a.n_shrink, per = 8 * a.groups, m8 = mb0 / per, in8 = mb0 - m8 * per;
+    const int mbid = a.groups == 1 ? mb0 : m8 * 8 + (in8 & 7), g = a.groups == 1 ? 0 : in8 >> 3;
+    if (mbid >= a.n_main) return;
+    const int t0 = g * a.rows, T = min(a.rows, a.T - t0);
     int p = 0;
     if constexpr (!PAIR) {
 #pragma unroll
@@ -558,12 +500,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
         for (int cb = 0; cb < NB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
     XRows<MB> x;
-    const int last = a.T - 1;
-    x.init(P.X, P.K, a.T, lds + w * MB * 128, [last](int r) { return min(r, last); });
+    const int last = T - 1;
+    x.init(P.X + (size_t)t0 * P.K, P.K, T, lds + w * MB * 128, [last](int r) { return min(r, last); });
 
     // wave 0 plans the batch (its loads go ahead of the weights')
     PlanLoads ld = PlanLoads{0, 0, -1};
-    if (w == 0 && a.act_max > 0) ld = dec_plan_loads(a);
+    if (w == 0 && a.act_max > 0) ld = dec_plan_loads(a, t0, T);
     // Expand turn: 4 octets of the adapters in use (lane group lg takes
     // octet lg; tokens of other adapters see zeros, which cost no traffic:
     // their loads are past the end of Z).  Turns past the list multiply
@@ -587,10 +529,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     };
     auto load_z = [&](TurnZ& t, int cd, int q) __attribute__((always_inline)) {
         const int slot = cd >> 12, vr = sig[q] * ((cd >> 4) & 0xff) + (cd & 15) * 8;   // row of A^T
-        const __amdgpu_buffer_rsrc_t rz = dec_rsrc(Pc[q]->Z, (unsigned)(Pc[q]->nbA * a.T * kDecZLine * 2));
+        const __amdgpu_buffer_rsrc_t rz = buf_rsrc(dec_z(a, *Pc[q], g), (unsigned)(Pc[q]->nbA * a.rows * kDecZLine * 2));
 #pragma unroll
         for (int rb = 0; rb < MB; ++rb) {
-            const unsigned zo = (unsigned)(((vr >> 4) * a.T + rb * 16 + lr) * kDecZLine + (vr & 15)) * 2u;
+            const unsigned zo = (unsigned)(((vr >> 4) * a.rows + rb * 16 + lr) * kDecZLine + (vr & 15)) * 2u;
             const bool own = cd >= 0 && s_vid[rb * 16 + lr] == slot;
 #pragma unroll
             for (int i = 0; i < 3; ++i) t.z[rb][i] = buf16(rz, own ? zo + i * 32u : kOob);
@@ -604,7 +546,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     };
     auto pre = [&]() __attribute__((always_inline)) {
         if (w == 0 && a.act_max > 0) {
-            const Plan pl = dec_plan(a, ld);
+            const Plan pl = dec_plan(a, ld, T);
             s_vid[l] = pl.vid;
             const int c = pl.gr >> 3, incl = wave_incl_scan(c), total = wave_total(incl);
             for (int j = 0; j < c; ++j) s_oct[incl - c + j] = (pl.gs << 12) | (pl.gr << 4) | j;
@@ -647,13 +589,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         if (w == 0) {
             // (the two projections of a pair have their shrink workgroups side by side)
             const int i0 = a.shrink_base[p], i1 = p + (PAIR ? 2 : 1) < a.n_proj ? a.shrink_base[p + (PAIR ? 2 : 1)] : a.n_shrink;
-            const bool ok = wait_flags(a, i0, i1 - i0);
+            const bool ok = wait_flags(a, g * a.n_shrink + i0, i1 - i0);
             if (l == 0) s_info[1] = ok;
         }
         __syncthreads();
         if (!s_info[1]) {
             // this tile's projections, every item
-            const Plan mine = dec_plan(a, dec_plan_loads(a));
+            const Plan mine = dec_plan(a, dec_plan_loads(a, t0, T), T);
             const int nit = dec_items(mine, s_cnt[w]);
             for (int q = 0; q < (PAIR ? 2 : 1); ++q) {
                 const DecProj& Q = a.p[p + q];
@@ -661,7 +603,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
                     const int nb = (Q.n_slices * __builtin_amdgcn_readlane(mine.gr, ai) + 15) >> 4;
                     const int items = __builtin_amdgcn_readlane(nit, ai);
                     for (int rb = 0; rb < items; ++rb)
-                        for (int c = 0; c < nb; ++c) dec_shrink<NW>(a, Q, mine, ai, rb, c, lds);
+                        for (int c = 0; c < nb; ++c) 
+                            dec_shrink<NW>(a, Q, mine, ai, rb, c, Q.X + (size_t)t0 * Q.K, dec_z(a, Q, g), T, lds);
                 }
             }
         }
@@ -712,7 +655,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         // lane ln of fragment (rb, cb): token 16 rb + ln mod 16, columns 4 (ln / 16) + i
         const int ln = e & 63, f = e >> 6, cb = f % NS, rb = (f / NS) % MB, g = f / (NS * MB);
         const int t = rb * 16 + (ln & 15), b = (tile * ncg + g) * NS + cb, col = b * 16 + 4 * (ln >> 4);
-        if (t >= a.T || b >= nWb) continue;
+        if (t >= T || b >= nWb) continue;
         const f32x4* src = red + ((g * kparts * MB + rb) * NB + cb) * 64 + ln;
         f32x4 v = src[0];
         for (int q = 1; q < kparts; ++q) v += src[q * MB * NB * 64];
@@ -725,7 +668,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         const uint2 o = make_uint2((uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
                                    (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
         // out, or the MLP intermediate H (the second projection's input)
-        *reinterpret_cast<uint2*>((a.h_dst ? a.h_dst : P.out) + (size_t)t * P.N + col) = o;
+        *reinterpret_cast<uint2*>((a.h_dst ? a.h_dst : P.out) + (size_t)(t0 + t) * P.N + col) = o;
     }
 }
 
@@ -735,7 +678,7 @@ static hipError_t launch_mb(const DecArgs& a, bool q4, hipStream_t s) {
     bool zs = false;
     for (int i = 0; i < a.n_proj; ++i)
         for (int q = 1; q < a.p[i].n_slices; ++q) zs = zs || a.p[i].slice_col[q] % (16 * kDecNB) != 0;
-    const dim3 grid(a.n_shrink + a.n_main);
+    const dim3 grid(a.groups * (a.n_shrink + (a.groups == 1 ? a.n_main : (a.n_main + 7) / 8 * 8)));
 #define BDL_DEC_CASE(Q, R, Z) hipLaunchKernelGGL((dec_main_kernel<NW, MB, kDecNB, Q, R, Z>), grid, dim3(64 * NW), 0, s, a)
     if (a.pair) {
         if (q4) BDL_DEC_CASE(true, true, true); else BDL_DEC_CASE(false, true, true);
@@ -749,7 +692,8 @@ static hipError_t launch_mb(const DecArgs& a, bool q4, hipStream_t s) {
 }
 
 hipError_t launch_dec_main(const DecArgs& a, int mb, hipStream_t s) {
-    if (a.n_main <= 0 || a.n_shrink < 1 || a.T < 1 || a.T > mb * 16 || !a.flags) return hipErrorInvalidValue;
+    if (a.n_main <= 0 || a.n_shrink < 1 || a.T < 1 || a.rows > mb * 16 || a.rows > kDecodeMaxT ||
+        a.groups != (a.T + a.rows - 1) / a.rows || !a.flags) return hipErrorInvalidValue;
     bool q4 = false;
     for (int i = 0; i < a.n_proj; ++i) {
         q4 = q4 || a.p[i].Ws != nullptr;

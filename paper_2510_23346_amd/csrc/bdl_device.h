@@ -186,6 +186,115 @@ __device__ __forceinline__ void mma_range_int4(f32x4 (&acc)[MB][NB], const uint1
         if (d < rem) mma_int4_kstep<MB, NB>(acc, a[d], q[d], sc[d]);
 }
 
+// The kernel's by-value argument where the launch put it.  (Named as a
+// parameter and indexed with a projection number that depends on the
+// workgroup, it would be copied to scratch memory first.)
+template <class T>
+__device__ __forceinline__ const T& kernel_args() {
+    return *(const T*)(const __attribute__((address_space(4))) T*)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
+constexpr unsigned kOob = 0x7ffffff0u;      // byte offset past every buffer: the load returns zeros
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* p, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)bytes, kRawBufferWord3);
+}
+
+__device__ __forceinline__ u32x4 buf16(__amdgpu_buffer_rsrc_t r, unsigned off) {
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+}
+
+// Activations.  A wave takes the caller's row-major X in pairs of k-steps: 16
+// rows x 128 bytes with two loads in which eight lanes cover a row's line
+// (lanes 16 rows apart, as the MFMA operand wants them, would touch a line per
+// lane), through its own buffer in LDS, from which the operand fragments
+// are read.  Lane l takes row 8 h + l / 8 and chunk (l mod 8) ^
+// swizzle(row), so that both sides hit distinct banks.
+__device__ __forceinline__ int x_swz(int r) { return ((r >> 1) ^ ((r & 1) << 2)) & 7; }
+
+// BIG: X of 2 GB or more, beyond a buffer's 32-bit offsets (64-bit addresses;
+// a load that is not wanted repeats the row's first pair, unused).
+template <int MB, bool BIG = false>
+struct XRows {
+    __amdgpu_buffer_rsrc_t rx;
+    unsigned ro[MB][2];     // byte offset of this lane's chunk of pair 0
+    unsigned st;            // bytes from one pair to the next
+    const char* rp[BIG ? MB : 1][2];   // BIG: the chunk's address instead
+    u32x4* buf;             // this wave's MB x 128 pieces
+    int pos[2];             // where this lane's operand of k-step e of a pair lies in a row block
+
+    // row(i): the X row of row i of the MB 16-row blocks
+    template <class Row>
+    __device__ __forceinline__ void init(const uint16_t* X, int K, int T, u32x4* lds, Row row) {
+        const int l = threadIdx.x & 63;
+        rx = buf_rsrc(X, (unsigned)T * K * 2u);
+        buf = lds;
+        st = 128u;
+#pragma unroll
+        for (int rb = 0; rb < MB; ++rb)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int r = 8 * h + (l >> 3);
+                const unsigned c = (unsigned)((l & 7) ^ x_swz(r)) * 16u;
+                if constexpr (BIG)
+                    rp[rb][h] = reinterpret_cast<const char*>(X + (size_t)row(rb * 16 + r) * K) + c;
+                else
+                    ro[rb][h] = (unsigned)row(rb * 16 + r) * K * 2u + c;
+            }
+        init_pos();
+    }
+    // the same from X in the fragment layout (rows padded to 16)
+    template <class Row>
+    __device__ __forceinline__ void init_packed(const uint16_t* Xp, int K, int T, u32x4* lds, Row row) {
+        const int l = threadIdx.x & 63;
+        const unsigned KS = (unsigned)K >> 5;
+        rx = buf_rsrc(Xp, (unsigned)((T + 15) >> 4) * KS * 1024u);
+        buf = lds;
+        st = 2048u;
+#pragma unroll
+        for (int rb = 0; rb < MB; ++rb)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int r = 8 * h + (l >> 3), c = (l & 7) ^ x_swz(r), t = row(rb * 16 + r);
+                const unsigned o = (unsigned)((t & 15) + 16 * (c & 3)) * 16u + (unsigned)(c >> 2) * 1024u;
+                if constexpr (BIG)
+                    rp[rb][h] = reinterpret_cast<const char*>(Xp + frag_index(t >> 4, 0, (int)KS)) + o;
+                else
+                    ro[rb][h] = (unsigned)(t >> 4) * KS * 1024u + o;
+            }
+        init_pos();
+    }
+    __device__ __forceinline__ void init_pos() {
+        const int l = threadIdx.x & 63, lr = l & 15, lg = l >> 4;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) pos[e] = (lr >> 3) * 64 + (lr & 7) * 8 + ((4 * e + lg) ^ x_swz(lr));
+    }
+    // pair g (its k-steps 2 g, 2 g + 1); ok false: zeros, no memory traffic
+    __device__ __forceinline__ void load(u32x4 (&v)[MB][2], int g, bool ok) const {
+#pragma unroll
+        for (int rb = 0; rb < MB; ++rb)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if constexpr (BIG)
+                    v[rb][h] = *reinterpret_cast<const u32x4*>(rp[rb][h] + (ok ? (size_t)g * st : 0));
+                else
+                    v[rb][h] = buf16(rx, ok ? ro[rb][h] + (unsigned)g * st : kOob);
+            }
+    }
+    // (the wave's LDS operations run in order, so one buffer does: a pair is
+    // written after the last one's reads; the fences keep the compiler's order)
+    __device__ __forceinline__ void put(const u32x4 (&v)[MB][2]) const {
+        const int l = threadIdx.x & 63;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int rb = 0; rb < MB; ++rb)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) buf[rb * 128 + h * 64 + l] = v[rb][h];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    __device__ __forceinline__ u32x4 get(int rb, int e) const { return buf[rb * 128 + pos[e]]; }
+};
+
 // minimum / bitwise or over the 64 lanes of a wave, as a uniform value
 __device__ __forceinline__ int wave_min(int v) {
     constexpr int kMax = 0x7fffffff;

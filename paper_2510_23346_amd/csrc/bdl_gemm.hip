@@ -36,8 +36,8 @@
 //
 // Split tiles: when a batch has too few tiles for the chip, the host cuts a
 // projection's tiles into ksplit k-ranges.  Each range stores its fp32 sum as
-// a partial; a second launch of this kernel (fixup) adds a tile's partials
-// in range order, then runs the expand and the store.
+// a partial; a second launch (big_fix_kernel) adds a tile's partials in range
+// order, then runs the expand and the store.
 //
 // Tile order: projections heaviest first (set by the host), inside a
 // projection bands of kBigBand row tiles walked column by column.
@@ -164,20 +164,18 @@ __global__ __launch_bounds__(128 * (16 / RB)) void gemm_big_kernel(FwdArgs a) {
     const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lg = l >> 4;
     const int wr = w % NWR, wc = w / NWR;        // rows 16 RB wr .., columns 128 wc .. of the tile
 
-    // Main launch: workgroup = one work item, a tile's k-range (split tiles
-    // have ksplit items, item = tile * ksplit + range).  Fix-up launch:
-    // workgroup = one split tile, whose partials it adds before the expand.
+    // workgroup = one work item, a tile's k-range (split tiles have ksplit
+    // items, item = tile * ksplit + range)
     const int bid = blockIdx.x;
-    const bool fix = a.fixup != 0;
-    if (bid >= (fix ? a.total_fix : a.total_tiles)) return;
+    if (bid >= a.total_tiles) return;
     int p = 0;
 #pragma unroll
     for (int q = 1; q < kMaxProjs; ++q)
-        if (q < a.n_proj && (fix ? bid >= a.p[q].fix_base && a.p[q].fix_count > 0 : bid >= a.p[q].tile_base)) p = q;
+        if (q < a.n_proj && bid >= a.p[q].tile_base) p = q;
     const ProjLaunch& P = a.p[p];
     const int S = P.ksplit;
-    const int item = fix ? bid - P.fix_base : bid - P.tile_base;
-    const int local = fix ? item : item / S, split = fix ? 0 : item - local * S;
+    const int item = bid - P.tile_base;
+    const int local = item / S, split = item - local * S;
     const int band = local / (kBigBand * P.tiles_n), off = local - band * kBigBand * P.tiles_n;
     const int bh = min(kBigBand, a.tiles_m - band * kBigBand);
     const int nt = off / bh, mt = band * kBigBand + (off - nt * bh);
@@ -221,16 +219,6 @@ __global__ __launch_bounds__(128 * (16 / RB)) void gemm_big_kernel(FwdArgs a) {
     const size_t part_lane = ((size_t)w * RB * 8) * 64 + l;
     f32x4* const part = reinterpret_cast<f32x4*>(a.bigpart) + (size_t)(P.part_base + local * S) * (kBigPartElems / 4);
 
-    if (fix) {
-        // partials in range order (fixed order: reproducible sums)
-        for (int j = 0; j < S; ++j) {
-            const f32x4* src = part + (size_t)j * (kBigPartElems / 4) + part_lane;
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-                for (int cb = 0; cb < 8; ++cb) acc[rb][cb] += src[(rb * 8 + cb) * 64];
-        }
-    } else {
     // this item's k-steps [k0, k0 + NK); row-major X: even bounds, so every
     // pair of k-steps starts a 128-byte line (the host keeps KS even and
     // each range at least 2 k-steps long)
@@ -240,6 +228,9 @@ __global__ __launch_bounds__(128 * (16 / RB)) void gemm_big_kernel(FwdArgs a) {
         k1 = split + 1 == S ? KS : k1 & ~1;
     }
     const int NK = k1 - k0;
+    // (always true; as straight-line code the compiler spills the accumulators,
+    // and a spill's loads would break the waits, which count copies into LDS only)
+    if (NK > 0) {
 
     // staging: fragments 0..15 of a k-step are the tile's activation row
     // blocks, 16..31 its weight column blocks (blocks past the edge are
@@ -543,6 +534,133 @@ __global__ __launch_bounds__(128 * (16 / RB)) void gemm_big_kernel(FwdArgs a) {
 // wave tile height of the launch: 4 row blocks (eight waves of 64 x 128)
 constexpr int kBigRB = 4;
 
+// Fix-up of split tiles: out = the sum of a tile's partials (range order) + the
+// expand.  Workgroup = one row quarter x column half of the tile (PAIR: both
+// halves, gate and up), wave = 16 of its rows, so that a tile's partials are
+// read by 32 waves at once with 8 (16) accumulators each.  Bound by the
+// partials' bytes.  The form before (one workgroup per tile, 32 accumulators
+// per wave: the large-tile kernel itself) took 48 us for the 8B layer at 333
+// tokens, as long as the products; this one 20 us (52 MB of partials: 2.6 TB/s).
+// (At least two waves per SIMD keep the accumulators out of the accumulation
+// registers, whose reads after an MFMA across a branch this compiler places
+// too early.)
+template <bool PAIR>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void big_fix_kernel(FwdArgs a) {
+    constexpr int H = PAIR ? 2 : 1, RB = kBigRB;
+    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lg = l >> 4;
+    const int item = blockIdx.x / (PAIR ? 4 : 8), sub = blockIdx.x - item * (PAIR ? 4 : 8);
+    if (item >= a.total_fix) return;
+    const int wr = sub & 3, wc = PAIR ? 0 : sub >> 2;
+    int p = 0;
+#pragma unroll
+    for (int q = 1; q < kMaxProjs; ++q)
+        if (q < a.n_proj && item >= a.p[q].fix_base && a.p[q].fix_count > 0) p = q;
+    const ProjLaunch& P = a.p[p];
+    const int S = P.ksplit, local = item - P.fix_base;
+    const int band = local / (kBigBand * P.tiles_n), off = local - band * kBigBand * P.tiles_n;
+    const int bh = min(kBigBand, a.tiles_m - band * kBigBand);
+    const int nt = off / bh, mt = band * kBigBand + (off - nt * bh);
+    const int T = a.T, N = P.N;
+    const int blk64 = mt * kBigM + wr * 64;            // the 64-row block of the octet list
+    if (blk64 >= T) return;
+    const int c0 = PAIR ? nt * 128 : nt * kBigN + wc * 128;
+    const int row = blk64 + w * 16 + lr;
+    // (clamped: a bad entry can cost a wrong row, never an access past Z or out)
+    const int tok = row < T ? (a.rowtok ? (int)min((unsigned)a.rowtok[row], (unsigned)(T - 1)) : row) : -1;
+    const int vid = tok >= 0 ? a.vid[tok] : -1;
+    const int* codes = a.tile_oct + (size_t)(mt * 4 + wr) * a.oct_cap;
+    int cd = codes[lg];
+
+    f32x4 acc[H][8];
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int cb = 0; cb < 8; ++cb) acc[h][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const f32x4* part = reinterpret_cast<const f32x4*>(a.bigpart) + (size_t)(P.part_base + local * S) * (kBigPartElems / 4) + l;
+    // wave (wr, wc) of the tile, its row block w: partial element ((wave RB + w) 8 + cb) 64 + lane
+#pragma unroll 2
+    for (int j = 0; j < S; ++j) {
+        f32x4 v[H][8];
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+            for (int cb = 0; cb < 8; ++cb)
+                v[h][cb] = part[(size_t)j * (kBigPartElems / 4) + ((((wc + h) * 4 + wr) * RB + w) * 8 + cb) * 64];
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+            for (int cb = 0; cb < 8; ++cb) acc[h][cb] += v[h][cb];
+    }
+
+    // expand, as in the large-tile kernel
+    int sig[8];
+#pragma unroll
+    for (int cb = 0; cb < 8; ++cb) {
+        sig[cb] = 0;
+#pragma unroll
+        for (int q = 1; q < kMaxSlices; ++q)
+            if (q < P.n_slices && c0 + cb * 16 >= P.slice_col[q]) sig[cb] = q;
+    }
+    const u32x4 zero4 = u32x4{0u, 0u, 0u, 0u};
+    for (int e = 0;;) {
+        if (!__any(cd >= 0)) break;
+        const int cdn = e + 8 <= a.oct_cap ? codes[e + 4 + lg] : -1;
+        const int slot = cd >> 12, r8s = (cd >> 4) & 0xff, j0 = (cd & 15) * 8;
+        const bool match = cd >= 0 && vid == slot;
+        if (__any(match)) {
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+                const ProjLaunch& Pe = a.p[p + h];
+                // (Z is loaded again for every column block, from the caches where
+                // the slice is the same: no branch between the MFMAs)
+                u32x4 bv[8], zh[8], zl[8];
+#pragma unroll
+                for (int cb = 0; cb < 8; ++cb) {
+                    const uint16_t* zp = Pe.Z + (size_t)max(tok, 0) * Pe.zs + sig[cb] * a.r8max + j0;
+                    bv[cb] = zh[cb] = zl[cb] = zero4;
+                    if (cd >= 0)
+                        bv[cb] = ld16(a.pool + (size_t)slot * a.slot_stride + Pe.b_off +
+                                      (size_t)min(c0 + cb * 16 + lr, N - 1) * r8s + j0);
+                    if (match) {
+                        zh[cb] = ld16(zp);
+                        zl[cb] = ld16(zp + Pe.zplane);
+                    }
+                }
+#pragma unroll
+                for (int cb = 0; cb < 8; ++cb) {
+                    acc[h][cb] = mfma(bv[cb], zh[cb], acc[h][cb]);
+                    acc[h][cb] = mfma(bv[cb], zl[cb], acc[h][cb]);
+                }
+            }
+        }
+        e += 4;
+        if (e + 4 > a.oct_cap) break;
+        cd = cdn;
+    }
+    if (tok < 0) return;
+#pragma unroll
+    for (int cb = 0; cb < 8; ++cb) {
+        const int col = c0 + cb * 16 + 4 * lg;
+        if (col >= N) continue;
+        f32x4 v = acc[0][cb];
+        if constexpr (PAIR) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = v[i] / (1.f + __expf(-v[i])) * acc[H - 1][cb][i];
+        }
+        if (a.mlp_act < 0 && P.out_f32) {
+            *reinterpret_cast<f32x4*>(P.out_f32 + (size_t)tok * N + col) = v;
+            continue;
+        }
+        const uint2 o = make_uint2((uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
+                                   (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
+        // out, or the MLP intermediate H in the fragment layout of the second projection's input
+        uint16_t* dst = a.mlp_act >= 0 ? a.h_dst + ((size_t)(tok >> 4) * a.h_KS + (col >> 5)) * kFrag +
+                                             ((tok & 15) + 16 * ((col & 31) >> 3)) * 8 + (col & 7)
+                                       : P.out + (size_t)tok * N + col;
+        *reinterpret_cast<uint2*>(dst) = o;
+    }
+}
+
 hipError_t launch_gemm_big(const FwdArgs& a, hipStream_t s) {
     if (a.total_tiles <= 0) return hipSuccess;
     // every projection of a launch reads X the same way; row-major X needs
@@ -555,9 +673,10 @@ hipError_t launch_gemm_big(const FwdArgs& a, hipStream_t s) {
     else
         hipLaunchKernelGGL((gemm_big_kernel<kBigRB, false>), dim3(a.total_tiles), dim3(128 * (16 / kBigRB)), 0, s, a);
     if (a.total_fix > 0) {
-        FwdArgs f = a;
-        f.fixup = 1;
-        hipLaunchKernelGGL((gemm_big_kernel<kBigRB, false>), dim3(a.total_fix), dim3(128 * (16 / kBigRB)), 0, s, f);
+        if (a.mlp_act == BDLORA_ACT_SILU_MUL)
+            hipLaunchKernelGGL((big_fix_kernel<true>), dim3(a.total_fix * 4), dim3(256), 0, s, a);
+        else
+            hipLaunchKernelGGL((big_fix_kernel<false>), dim3(a.total_fix * 8), dim3(256), 0, s, a);
     }
     return hipGetLastError();
 }
@@ -617,23 +736,17 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(FwdArgs a) {
     // the epilogue's consecutive rows share adapters); each lane gathers its
     // row's token through its buffer-load offset, and the copy puts lane l's
     // 16 bytes at byte 16 l of the LDS fragment, so lane l = r + 16 c loads
-    // inputs 32 ks + 8 c .. + 7 of row r's token: in the caller's row-major
-    // X (k-steps 64 bytes apart; buffer bounds = X's size) or in the packed X
-    // (the token's fragment, lane slot (token mod 16) + 16 c; k-steps a
-    // fragment apart).  Rows past T repeat a valid token (their sums are
-    // never read).
-    const bool xrm = P.x_rowmajor != 0;
-    const __amdgpu_buffer_rsrc_t rx =
-        xrm ? __builtin_amdgcn_make_buffer_rsrc((void*)P.X, 0, T * P.K * 2, kRawBufferWord3)
-            : __builtin_amdgcn_make_buffer_rsrc((void*)P.Xp, 0, nrb * KS * 1024, kRawBufferWord3);
-    const int xst = xrm ? 64 : 1024;       // bytes from one k-step to the next
+    // inputs 32 ks + 8 c .. + 7 of row r's token in the row-major X (k-steps 64
+    // bytes apart; buffer bounds = X's size).  Rows past T repeat a valid token
+    // (their sums are never read).
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)P.X, 0, T * P.K * 2, kRawBufferWord3);
+    constexpr int xst = 64;                // bytes from one k-step to the next
     int vo[CPX];
 #pragma unroll
     for (int i = 0; i < CPX; ++i) {
         const int pos = min((w + NW * i) * 16 + (l & 15), T - 1);
         const int t = (int)min((unsigned)a.rowtok[pos], (unsigned)(T - 1));
-        vo[i] = xrm ? (t * P.K + k0 * 32 + 8 * (l >> 4)) * 2
-                    : ((t >> 4) * KS + k0) * 1024 + ((t & 15) + 16 * (l >> 4)) * 16;
+        vo[i] = (t * P.K + k0 * 32 + 8 * (l >> 4)) * 2;
     }
     // this wave's weight column blocks (clamped at the projection's edge):
     // copied the same way into the wave's own fragments RB + w NB + c of the
@@ -893,17 +1006,13 @@ __global__ __launch_bounds__(256) void mid_epi_kernel(FwdArgs a) {
     }
     if (!live) return;
     if (a.mlp_act >= 0) {
-        // the MLP intermediate H in bf16 in the second projection's input
-        // layout (token tt, columns col ..): CPT / 4 pieces of 4 contiguous
-        // elements
+        // the MLP intermediate H in bf16, row-major (the second projection's
+        // input)
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            const int c = col + 4 * q;
-            const size_t idx = ((size_t)(tt >> 4) * a.h_KS + (c >> 5)) * kFrag + ((tt & 15) + 16 * ((c & 31) >> 3)) * 8 +
-                               (c & 7);
             const uint32_t lo = (uint32_t)f2bf(acc[4 * q]) | ((uint32_t)f2bf(acc[4 * q + 1]) << 16);
             const uint32_t hi = (uint32_t)f2bf(acc[4 * q + 2]) | ((uint32_t)f2bf(acc[4 * q + 3]) << 16);
-            *reinterpret_cast<uint2*>(a.h_dst + idx) = make_uint2(lo, hi);
+            *reinterpret_cast<uint2*>(a.h_dst + (size_t)tt * N + col + 4 * q) = make_uint2(lo, hi);
         }
         return;
     }
@@ -928,6 +1037,8 @@ hipError_t launch_gemm_mid(const FwdArgs& a, hipStream_t s) {
     if (a.mid_items <= 0) return hipSuccess;
     if (a.T <= 0 || a.T > a.mid_rb * 16 || a.mid_rb * a.mid_nb * 2048 > kBigPartElems || !a.rowtok)
         return hipErrorInvalidValue;
+    for (int i = 0; i < a.n_proj; ++i)
+        if (!a.p[i].X) return hipErrorInvalidValue;
     bool ok = false;
 #define BDL_MID_CASE(R, NN)                                                                     \
     if (a.mid_rb == R && a.mid_nb == NN) {                                                      \

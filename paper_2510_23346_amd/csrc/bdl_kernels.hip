@@ -39,172 +39,170 @@ constexpr int kStages = 3;                    // k-steps of loads kept in flight
 
 // --------------------------------------------------------------------------
 // 2. shrink: Z[t, sigma * r8max + j] = scale_a * sum_k X[t, k] A_a,sigma[k, j]
-//    work item = (projection, shrink item, 16*NB-column chunk of A^T_cat)
+//    work unit = (projection, shrink item of 16 MB tokens of one adapter,
+//    chunk of 16 NB columns of A^T_cat)
 //
-//    Unsplit (shrink_kp = 1): a resident set of workgroups takes the work
-//    units (projection in the order sorder, longest K first; item; chunk)
-//    one at a time from a counter that the plan zeroes, so the long units
-//    start first and no workgroup is spent on the host's padding of the
-//    item count.
+//    A resident set of workgroups takes the units (projection in the order
+//    sorder, longest K first; item; chunk) one at a time from a counter that
+//    the plan zeroes, so the long units start first and no workgroup is spent
+//    on the host's padding of the item count; the next unit's number is
+//    fetched while the current one runs.  Eight waves split K; a wave's A^T
+//    and X (pairs of k-steps, see XRows) run through a ring of D pairs.  A
+//    projection whose columns all fit the smaller chunk (NBS blocks: one
+//    slice) takes that, the others the larger (NBL: q, k and v from one pass
+//    over X).
 //
-//    Small batches (shrink_kp = kShrinkKP): an item's adapter group holds a
-//    few scattered tokens, and every item reads its rows out of the whole
-//    X, so each XCD would fetch most of X from HBM.  There each item's K is
-//    cut into kShrinkKP = 4 ranges, range k running on XCDs k and k + 4
-//    (workgroup b runs on XCD b mod 8, and the flat index keeps the range
-//    in its two low bits): each XCD fetches only its quarter of X.  (Eight
-//    ranges, one per XCD, leave each wave too few k-steps to stream.)  The
-//    ranges store fp32 partial tiles (their own workspace);
-//    shrink_reduce_kernel adds them in range order and writes Z.
+//    Bound by X and A^T from the caches and HBM, by round trips on small
+//    batches.  Against the form before (rows gathered as MFMA operands, a
+//    cache line per lane; 16 x 16 units up to 512 tokens, with K split over
+//    the XCDs and a second launch for scattered adapters), kernel trace: 8B
+//    layer, 150 tokens 18 -> 14 us, 333 tokens 30 -> 21 us, 4096 tokens 54
+//    -> 47 us (119 MB of X: 2.5 TB/s); 70B, 256 tokens over 128 adapters,
+//    beside the base product, 99 (both launches) -> 102 us, the step 155 ->
+//    148 us; 70B, 4288 tokens, 117 us as before.
 // --------------------------------------------------------------------------
 
-// XRM: the launch's projections read the caller's row-major X (the
-// large-tile path); else the packed X
-template <int MB, int NB, bool XRM>
-__global__ __launch_bounds__(kThreads) void shrink_kernel(FwdArgs a) {
-    constexpr int MT = MB * 16, NT = NB * 16, FR = MB * NB * 64;
-    // the waves' sums in lane order (fragment (rb, cb) of wave w at
-    // ((w MB + rb) NB + cb) 64 + lane), added in wave order after one barrier
-    __shared__ f32x4 red[kWaves * FR];
-    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15;
-    // (clamped: the plan writes at most items_bound items)
-    const int n_items = min(a.meta[1], a.items_bound);
-    const int KP = a.shrink_kp;
-    const bool queue = KP == 1;
-    const int per_proj = (queue ? n_items : a.items_bound) * a.cchunks;
-    const int total = a.n_proj * per_proj * KP;
-    __shared__ int s_unit;
+// LDS (u32x4): the waves' X buffers, then (overlaid) their sums
+constexpr int shrink_lds(int mb, int nb) { return kWaves * 64 * mb * (nb > 2 ? nb : 2); }
 
-    for (int iter = 0;; ++iter) {
-        int flat = blockIdx.x + iter * gridDim.x;
-        if (queue) {
-            if (threadIdx.x == 0) s_unit = atomicAdd(a.queue, 1);
-            __syncthreads();
-            flat = s_unit;
-            __syncthreads();
-        }
-        if (flat >= total) break;
-        const int f = flat / KP, kp = flat - f * KP;
-        const int ps = f / per_proj, rem = f - ps * per_proj;
-        const int p = queue ? a.sorder[ps] : ps;
-        const int item = rem / a.cchunks, cc = rem - item * a.cchunks;
-        const int4 it = a.items[item];       // in bounds for every item < items_bound
-        if (item >= n_items) continue;
-        const int slot = it.x, nrows = it.z, r8s = it.w;
-        const ProjLaunch& P = a.p[p];
-        const int ncols = P.n_slices * r8s;
-        const int c0 = cc * NT;
-        if (c0 >= ncols) continue;
-        const float sc = a.scale[slot];
-        const int* prow = a.perm + it.y;
-        const int KS = P.K >> 5;
-        const int nblk = (ncols + 15) >> 4;
-        const uint16_t* abase = a.pool + (size_t)slot * a.slot_stride + P.a_off;
-
-        // the lane's row (token t) at k-step 0: in X row-major (k-steps 32
-        // elements apart) or in the packed X (k-steps a fragment apart)
-        const uint16_t* ap[MB];
-        const uint16_t* bp[NB];
+template <int MB, int NB, bool BIG>
+__device__ __forceinline__ void shrink_unit(const FwdArgs& a, const ProjLaunch& P, const int4& it, int chunk, u32x4* lds) {
+    constexpr int D0 = 144 / (8 * (MB + NB)), D = D0 > 8 ? 8 : D0 < 2 ? 2 : D0;      // pairs in flight
+    const int w = wave_id(), l = threadIdx.x & 63;
+    const int slot = it.x, nrows = it.z, r8s = it.w, ncols = P.n_slices * r8s, cb0 = chunk * NB;
+    const float sc = a.scale[slot];
+    const int* prow = a.perm + it.y;
+    const int KS = P.K >> 5, NP = (KS + 1) >> 1, nblk = (ncols + 15) >> 4;
+    const uint16_t* abase = a.pool + (size_t)slot * a.slot_stride + P.a_off;
+    __amdgpu_buffer_rsrc_t ra[NB];
 #pragma unroll
-        for (int rb = 0; rb < MB; ++rb) {
-            const int t = prow[min(rb * 16 + lr, nrows - 1)];
-            ap[rb] = XRM ? P.X + (size_t)t * P.K + 8 * (l >> 4)
-                         : P.Xp + frag_index(t >> 4, 0, KS) + ((t & 15) + 16 * (l >> 4)) * 8;
-        }
+    for (int cb = 0; cb < NB; ++cb) ra[cb] = buf_rsrc(abase + frag_index(min(cb0 + cb, nblk - 1), 0, KS), KS * 1024u);
+    int g0, n;                                         // this wave's pairs
+    wave_krange(NP, w, &g0, &n);
+    XRows<MB, BIG> x;
+    auto row = [=](int r) { return prow[min(r, nrows - 1)]; };
+    if (P.X)
+        x.init(P.X, P.K, a.T, lds + w * MB * 128, row);
+    else
+        x.init_packed(P.Xp, P.K, a.T, lds + w * MB * 128, row);
+    f32x4 acc[MB][NB];
 #pragma unroll
-        for (int cb = 0; cb < NB; ++cb) bp[cb] = abase + frag_index(min((c0 >> 4) + cb, nblk - 1), 0, KS) + l * 8;
-        f32x4 acc[MB][NB];
+    for (int rb = 0; rb < MB; ++rb)
 #pragma unroll
-        for (int rb = 0; rb < MB; ++rb)
+        for (int cb = 0; cb < NB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    u32x4 av[D][2][NB], xv[D][MB][2];
+    auto load = [&](int d, int i) __attribute__((always_inline)) {
+        const bool ok = i < n;
 #pragma unroll
-            for (int cb = 0; cb < NB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        // this range's k-steps, split over the 8 waves
-        const int ks0 = kp * KS / KP;
-        int k0, nk;
-        wave_krange((kp + 1) * KS / KP - ks0, w, &k0, &nk);
-        if (nk > 0) mma_range<MB, NB, kStages>(acc, ap, bp, ks0 + k0, nk, XRM ? 32 : kFrag, kFrag);
+        for (int e = 0; e < 2; ++e)
 #pragma unroll
-        for (int rb = 0; rb < MB; ++rb)
+            for (int cb = 0; cb < NB; ++cb)
+                av[d][e][cb] = buf16(ra[cb], ok ? (unsigned)(2 * (g0 + i) + e) * 1024u + l * 16u : kOob);
+        x.load(xv[d], g0 + i, ok);
+    };
+    auto comp = [&](int d, int i) __attribute__((always_inline)) {
+        x.put(xv[d]);
 #pragma unroll
-            for (int cb = 0; cb < NB; ++cb) red[((w * MB + rb) * NB + cb) * 64 + l] = acc[rb][cb];
-        __syncthreads();
-        // thread = one fragment slot at a time: rows rb 16 + 4 (ln / 16) + i
-        // (i < 4), column cb 16 + ln mod 16
-        float* const part = a.shrinkpart + (size_t)flat * (MT * NT);
-        for (int e = threadIdx.x; e < FR; e += kThreads) {
-            f32x4 v = red[e];
+        for (int e = 0; e < 2; ++e) {
+            if (2 * (g0 + i) + e >= KS) continue;      // an odd K's last pair holds one k-step
 #pragma unroll
-            for (int ww = 1; ww < kWaves; ++ww) v += red[ww * FR + e];
-            const int fr = e >> 6, ln = e & 63, rb = fr / NB, cb = fr - rb * NB;
-            const int c = cb * 16 + (ln & 15), cg = c0 + c;
+            for (int rb = 0; rb < MB; ++rb) {
+                const u32x4 xf = x.get(rb, e);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int r = rb * 16 + 4 * (ln >> 4) + i;
-                if (KP > 1) {
-                    // partial tile of range kp (row-major MT x NT), summed by shrink_reduce_kernel
-                    part[r * NT + c] = v[i];
-                } else if (r < nrows && cg < ncols) {
-                    const int t = prow[r];
-                    const int sig = cg / r8s, j = cg - sig * r8s;
-                    const float z = sc * v[i];
-                    const uint16_t hi = f2bf(z);
-                    const size_t zi = (size_t)t * P.zs + sig * a.r8max + j;
-                    P.Z[zi] = hi;
-                    P.Z[zi + P.zplane] = f2bf(z - bf2f(hi));
-                }
+                for (int cb = 0; cb < NB; ++cb) acc[rb][cb] = mfma(av[d][e][cb], xf, acc[rb][cb]);
             }
         }
-        __syncthreads();
+    };
+#pragma unroll
+    for (int d = 0; d < D; ++d) load(d, d);
+    int i = 0;
+    for (; i + D < n; i += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            comp(d, i + d);
+            load(d, i + d + D);
+        }
     }
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        if (i + d < n) comp(d, i + d);
+    // the waves' sums in lane order (fragment (rb, cb) of wave w at
+    // ((w MB + rb) NB + cb) 64 + lane), added in wave order
+    f32x4* const red = reinterpret_cast<f32x4*>(lds);
+    __syncthreads();
+#pragma unroll
+    for (int rb = 0; rb < MB; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < NB; ++cb) red[((w * MB + rb) * NB + cb) * 64 + l] = acc[rb][cb];
+    __syncthreads();
+    constexpr int FR = MB * NB * 64;
+    for (int e = threadIdx.x; e < FR; e += kThreads) {
+        f32x4 v = red[e];
+#pragma unroll
+        for (int ww = 1; ww < kWaves; ++ww) v += red[ww * FR + e];
+        // 4 consecutive rows of A^T (ranks of one octet) of one token
+        const int fr = e >> 6, ln = e & 63, rb = fr / NB, cb = fr - rb * NB;
+        const int r = rb * 16 + (ln & 15), vr = (cb0 + cb) * 16 + 4 * (ln >> 4);
+        if (r < nrows && vr < ncols) {
+            const int t = prow[r], sig = vr / r8s, j = vr - sig * r8s;
+            uint32_t hi[4], lo[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float z = sc * v[q];
+                hi[q] = f2bf(z);
+                lo[q] = f2bf(z - bf2f((uint16_t)hi[q]));
+            }
+            uint16_t* zp = P.Z + (size_t)t * P.zs + sig * a.r8max + j;
+            *reinterpret_cast<uint2*>(zp) = make_uint2(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16));
+            *reinterpret_cast<uint2*>(zp + P.zplane) = make_uint2(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16));
+        }
+    }
+    __syncthreads();
 }
 
-// Z of the split shrink: the kShrinkKP range partials of each (projection,
-// item, chunk) tile added in range order, scaled, stored as the bf16 pair.
-template <int MB, int NB>
-__global__ __launch_bounds__(256) void shrink_reduce_kernel(FwdArgs a) {
-    constexpr int MT = MB * 16, NT = NB * 16, KP = kShrinkKP;
-    const int n_items = a.meta[1];
-    const int per_proj = a.items_bound * a.cchunks;
-    const int total = a.n_proj * per_proj;
-    for (int f = blockIdx.x; f < total; f += gridDim.x) {
-        const int p = f / per_proj, rem = f - p * per_proj;
-        const int item = rem / a.cchunks, cc = rem - item * a.cchunks;
-        const int4 it = a.items[item];
-        if (item >= n_items) continue;
-        const int slot = it.x, nrows = it.z, r8s = it.w;
-        const ProjLaunch& P = a.p[p];
-        const int ncols = P.n_slices * r8s, c0 = cc * NT;
-        if (c0 >= ncols) continue;
-        const float sc = a.scale[slot];
-        const int* prow = a.perm + it.y;
-        const float* src = a.shrinkpart + (size_t)f * KP * (MT * NT);
-        for (int idx = threadIdx.x; idx < MT * NT; idx += 256) {
-            const int r = idx / NT, c = idx - (idx / NT) * NT, cg = c0 + c;
-            if (r < nrows && cg < ncols) {
-                float z = 0.f;
-#pragma unroll
-                for (int k = 0; k < KP; ++k) z += src[(size_t)k * (MT * NT) + idx];
-                z *= sc;
-                const int t = prow[r];
-                const int sig = cg / r8s, j = cg - sig * r8s;
-                const uint16_t hi = f2bf(z);
-                const size_t zi = (size_t)t * P.zs + sig * a.r8max + j;
-                P.Z[zi] = hi;
-                P.Z[zi + P.zplane] = f2bf(z - bf2f(hi));
-            }
+template <int MB, int NBS, int NBL, bool BIG>
+__global__ __launch_bounds__(kThreads) void shrink_kernel(FwdArgs) {
+    const FwdArgs& a = kernel_args<FwdArgs>();
+    __shared__ u32x4 lds[shrink_lds(MB, NBL)];
+    __shared__ int s_unit[2];
+    // (clamped: the plan writes at most items_bound items)
+    const int n_items = min(a.meta[1], a.items_bound);
+    int total = 0;
+    for (int q = 0; q < a.n_proj; ++q) total += n_items * a.schunks[q];
+    int u = blockIdx.x;                                // the first unit needs no counter
+    for (int turn = 0; u < total; ++turn) {
+        int next = 0;
+        if (threadIdx.x == 0) next = (int)gridDim.x + atomicAdd(a.queue, 1);
+        int p = a.sorder[0];
+        for (int ps = 0; ps + 1 < a.n_proj && u >= n_items * a.schunks[p]; ++ps) {
+            u -= n_items * a.schunks[p];
+            p = a.sorder[ps + 1];
         }
+        const ProjLaunch& P = a.p[p];
+        const int item = u / a.schunks[p], chunk = u - item * a.schunks[p];
+        const int4 it = a.items[item];
+        const bool small = P.n_slices * a.r8max <= 16 * NBS;
+        if (chunk * 16 * (small ? NBS : NBL) < P.n_slices * it.w) {
+            if (NBS == NBL || !small)
+                shrink_unit<MB, NBL, BIG>(a, P, it, chunk, lds);
+            else
+                shrink_unit<MB, NBS, BIG>(a, P, it, chunk, lds);
+        }
+        if (threadIdx.x == 0) s_unit[turn & 1] = next;
+        __syncthreads();
+        u = s_unit[turn & 1];
     }
 }
 
 // workgroups of the shrink kernel that the device holds at once (cached)
-template <int MB, int NB, bool XRM>
+template <int MB, int NBS, int NBL, bool BIG>
 int shrink_resident() {
     static int n = 0;
     if (n == 0) {
         int dev = 0, cu = 0, per = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, shrink_kernel<MB, NB, XRM>, kThreads, 0) != hipSuccess)
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, shrink_kernel<MB, NBS, NBL, BIG>, kThreads, 0) != hipSuccess)
             return 0;
         n = cu * (per > 1 ? per : 1);
     }
@@ -212,47 +210,29 @@ int shrink_resident() {
 }
 
 hipError_t launch_shrink(const FwdArgs& a, int mb, int nb, hipStream_t s) {
-    const int KP = a.shrink_kp;
-    if (KP != 1 && (KP != kShrinkKP || !a.shrinkpart)) return hipErrorInvalidValue;
-    if (KP == 1 && !a.queue) return hipErrorInvalidValue;
-    for (int i = 0; i < a.n_proj; ++i)
-        if (a.sorder[i] < 0 || a.sorder[i] >= a.n_proj) return hipErrorInvalidValue;
-    const int tiles = a.n_proj * a.items_bound * a.cchunks;
-    const int total = tiles * KP;
-    // split: every unit at once, or a multiple of 8 workgroups (either way
-    // each workgroup keeps one k-range, so XCD b mod 8 gets range b mod 4);
-    // unsplit: the resident workgroups take units from the queue
-    const int cap = 4096;
+    if (!a.queue) return hipErrorInvalidValue;
+    long long total = 0;
+    bool big = false;                    // X beyond 32-bit offsets (only with more than 512 tokens)
+    for (int i = 0; i < a.n_proj; ++i) {
+        if (a.sorder[i] < 0 || a.sorder[i] >= a.n_proj || a.schunks[i] < 1) return hipErrorInvalidValue;
+        big = big || (long long)((a.T + 15) / 16 * 16) * a.p[i].K * 2 >= 0x7fffff00LL;
+        total += (long long)a.items_bound * a.schunks[i];
+    }
     if (total <= 0) return hipSuccess;
-    const int rgrid = tiles < 2048 ? tiles : 2048;
-    // every projection of a launch reads X the same way (the large-tile path
-    // reads the caller's row-major X)
-    const bool xrm = a.p[0].x_rowmajor != 0;
-    for (int i = 1; i < a.n_proj; ++i)
-        if ((a.p[i].x_rowmajor != 0) != xrm) return hipErrorInvalidValue;
-#define BDL_SHRINK_LAUNCH(M, NN, X)                                                                 \
-    {                                                                                               \
-        int grid = total < cap ? total : cap;                                                       \
-        if (KP == 1) {                                                                              \
-            const int r = shrink_resident<M, NN, X>();                          \
-            if (r <= 0) return hipErrorInvalidValue;                                                \
-            grid = total < r ? total : r;                                                           \
-        }                                                                                           \
-        hipLaunchKernelGGL((shrink_kernel<M, NN, X>), dim3(grid), dim3(kThreads), 0, s, a);         \
+#define BDL_SHRINK_CASE(M, NS, NL, BG)                                                                    \
+    if (mb == M && nb == NL && big == BG) {                                                               \
+        const int r = shrink_resident<M, NS, NL, BG>();                                                   \
+        if (r <= 0) return hipErrorInvalidValue;                                                          \
+        const dim3 grid((unsigned)(total < r ? total : r));                                               \
+        hipLaunchKernelGGL((shrink_kernel<M, NS, NL, BG>), grid, dim3(kThreads), 0, s, a);                \
+        return hipGetLastError();                                                                         \
     }
-#define BDL_SHRINK_CASE(M, NN)                                                                          \
-    if (mb == M && nb == NN) {                                                                          \
-        if (xrm)                                                                                        \
-            BDL_SHRINK_LAUNCH(M, NN, true)                                                              \
-        else                                                                                            \
-            BDL_SHRINK_LAUNCH(M, NN, false)                                                             \
-        if (KP > 1) hipLaunchKernelGGL((shrink_reduce_kernel<M, NN>), dim3(rgrid), dim3(256), 0, s, a); \
-        return hipGetLastError();                                                                       \
-    }
-    BDL_SHRINK_CASE(1, 1) BDL_SHRINK_CASE(1, 2) BDL_SHRINK_CASE(1, 4)
-    BDL_SHRINK_CASE(4, 1) BDL_SHRINK_CASE(4, 2) BDL_SHRINK_CASE(4, 4) BDL_SHRINK_CASE(2, 6)
+    BDL_SHRINK_CASE(1, 1, 3, false) BDL_SHRINK_CASE(1, 2, 6, false) BDL_SHRINK_CASE(1, 4, 4, false)
+    BDL_SHRINK_CASE(2, 1, 3, false) BDL_SHRINK_CASE(2, 2, 6, false) BDL_SHRINK_CASE(2, 4, 4, false)
+    BDL_SHRINK_CASE(4, 4, 4, false)
+    BDL_SHRINK_CASE(1, 1, 3, true) BDL_SHRINK_CASE(1, 2, 6, true) BDL_SHRINK_CASE(1, 4, 4, true)
+    BDL_SHRINK_CASE(2, 1, 3, true) BDL_SHRINK_CASE(2, 2, 6, true) BDL_SHRINK_CASE(4, 4, 4, true)
 #undef BDL_SHRINK_CASE
-#undef BDL_SHRINK_LAUNCH
     return hipErrorInvalidValue;
 }
 

@@ -20,15 +20,14 @@ constexpr int kBigM = 256, kBigN = 256;   // output tile of the large-tile base 
 constexpr int kBigPartSlots = 256;        // fp32 partial tiles of the large-tile GEMM's split tiles
 constexpr int kBigPartElems = kBigM * kBigN;
 constexpr int kMidMaxT = 256;             // medium-batch base GEMM: largest batch (all rows in one tile)
-constexpr int kShrinkKP = 4;              // shrink k-ranges per item when split (range k on XCDs k, k + 4)
-constexpr long long kShrinkPartElems = 8LL << 20;   // fp32 partials of the split shrink (32 MiB)
 
 // One projection of a forward launch.
 struct ProjLaunch {
-    const uint16_t* X;        // [T x K] bf16 activations (row-major)
+    const uint16_t* X;        // [T x K] bf16 activations (row-major); null: an intermediate, in Xp only
     const uint16_t* Xp;       // packed activations, fragment layout, rows padded to 16
-    int x_rowmajor;           // large-tile and medium-batch paths: the shrink and the GEMM read X
-                              // (row-major, rows gathered by token) and Xp is not written; else Xp
+    int x_rowmajor;           // large-tile and medium-batch paths: the GEMM reads X (row-major, rows
+                              // gathered by token) and Xp is not written; else Xp.  (The shrink reads
+                              // X wherever there is one.)
     const uint16_t* W;        // packed base weight, fragment layout ([N x K] nn.Linear rows)
     const uint16_t* Ws;       // INT4 base: its scales (null for a bf16 base)
     uint16_t* out;            // [T x N] bf16
@@ -65,18 +64,14 @@ struct FwdArgs {
     const int4* items;        // shrink items {slot, first perm index, rows, r8}
     const int* meta;          // [1] number of shrink items
     int items_bound;          // shrink: upper bound on items
-    int cchunks;              // shrink: column chunks per item (upper bound)
-    int shrink_kp;            // shrink: k-ranges per item (1, or kShrinkKP: fp32 partials in
-                              // shrinkpart that a second launch sums into Z)
-    int* queue;               // unsplit shrink: unit counter, zeroed by the plan (meta[2])
-    int sorder[kMaxProjs];    // unsplit shrink: projections in unit order (longest K first)
-    float* shrinkpart;        // split shrink: fp32 partials (kShrinkPartElems)
+    int* queue;               // shrink: unit counter, zeroed by the plan (meta[2])
+    int sorder[kMaxProjs];    // shrink: projections in unit order (longest K first)
+    int schunks[kMaxProjs];   // shrink: column chunks of an item, by projection (not by unit order)
     const int* tile_oct;      // expand octet codes per row tile (-1 padded)
     int oct_cap;              // entries per row tile in tile_oct
     int tiles_m;              // base GEMM: row tiles
     int total_tiles;          // base GEMM: flattened tiles (large tiles: work items) over all projections
     float* bigpart;           // large-tile GEMM: fp32 partials of split tiles (kBigPartSlots tiles)
-    int fixup;                // large-tile GEMM: 0 main launch, 1 fix-up launch of the split tiles
     int total_fix;            // large-tile GEMM: split tiles over all projections
     int mid_rb, mid_nb;       // medium-batch GEMM: 16-row blocks per tile, 16-column blocks per wave
     int mid_items;            // medium-batch GEMM: work items (tile x k-range) over all projections
@@ -134,6 +129,7 @@ struct PrepArgs {
 // ---- decode path (T <= kDecodeMaxT) ----------------------------------------
 // One launch: shrink and main workgroups (bdl_decode.hip).
 constexpr int kDecodeMaxT = BDLORA_DECODE_MAX_T;
+constexpr int kRowsMaxT = 256;       // largest batch that takes it, in row groups of up to kDecodeMaxT
 constexpr int kDecNB = 2;            // 16-column blocks per wave of a main workgroup
 // Waves per workgroup for mb blocks of 16 tokens.  The registers allow two
 // waves per SIMD, so four-wave workgroups leave room for shrink and main ones
@@ -148,8 +144,9 @@ struct DecProj {
     const uint16_t* W;        // packed base weight
     const uint16_t* Ws;       // INT4 base: its scales (null for a bf16 base)
     uint16_t* out;            // [T x N] bf16
-    uint16_t* Z;              // [nbA][T][kDecZLine] scale * X A: per 16-row block of A^T and token three
-                              // planes of 16 bf16 numbers that sum to the fp32 value (the rest unused)
+    uint16_t* Z;              // [groups][nbA][rows][kDecZLine] scale * X A: per 16-row block of A^T and
+                              // token three planes of 16 bf16 numbers that sum to the fp32 value (the
+                              // rest unused)
     int K, N, n_slices;
     int slice_col[kMaxSlices + 1];
     long long a_off, b_off;
@@ -159,8 +156,10 @@ struct DecProj {
 
 struct DecArgs {
     // what a workgroup reads first
-    int n_shrink, n_main;           // workgroups of each kind, in launch order (n_shrink >= 1: the first
-                                    // also reports invalid ids)
+    int groups, rows;               // row groups, each planned by itself: group g holds the tokens
+                                    // [g rows, (g + 1) rows) of the batch (rows <= kDecodeMaxT)
+    int n_shrink, n_main;           // workgroups of each kind and group, in launch order (n_shrink >= 1:
+                                    // the first also reports invalid ids)
     int n_proj;
     int shrink_base[kMaxProjs];     // first shrink workgroup of each projection
     int tile_base[kMaxProjs];       // first main workgroup of each projection
@@ -171,7 +170,7 @@ struct DecArgs {
     int r8max;
     int pair;                 // gated MLP: projections 0 and 1 share the tiles of 0, H = silu(0) * 1
     unsigned wait_ticks;      // longest wait for a producer (100 MHz ticks), then its work is done here
-    unsigned long long* flags;   // [n_shrink] launch tags (bdl_decode.hip, launch_tag)
+    unsigned long long* flags;   // [groups][n_shrink] launch tags (bdl_decode.hip, launch_tag)
     const int* ids;           // [T] per-token slot ids, or null: the segments below
     const int* loaded;        // [max_slots] nonzero: the slot holds an adapter
     const int* r8;            // [max_slots] padded rank of each slot
@@ -182,14 +181,17 @@ struct DecArgs {
     int* err;                 // sticky error flag
     DecProj p[kMaxProjs];
     int n_seg;                // segments (ids null): token t takes seg_slot[i] of the last i with
-    int seg_start[kDecodeMaxT];   // seg_start[i] <= t (the host checked that they tile 0..T-1)
-    int seg_slot[kDecodeMaxT];
+    int seg_start[kRowsMaxT];     // seg_start[i] <= t (the host checked that they tile 0..T-1)
+    int seg_slot[kRowsMaxT];
 };
+static_assert(sizeof(DecArgs) <= 4096, "kernel arguments");
 
 // Host-side launchers (bdl_kernels.hip, bdl_prep.hip, bdl_decode.hip).
 hipError_t launch_dec_main(const DecArgs& a, int mb, hipStream_t s);
 hipError_t launch_prep(const PrepArgs& a, hipStream_t s);
 hipError_t launch_shrink(const FwdArgs& a, int mb, int nb, hipStream_t s);
+// column blocks of the shrink's chunks for a projection of cols = n_slices * r8max columns (shape mb x nb)
+constexpr int shrink_blocks(int nb, int cols) { return nb == 6 ? (cols <= 32 ? 2 : 6) : nb == 3 ? (cols <= 16 ? 1 : 3) : nb; }
 hipError_t launch_gemm(const FwdArgs& a, int mb, int nb, hipStream_t s);
 hipError_t launch_gemm_big(const FwdArgs& a, hipStream_t s);
 hipError_t launch_gemm_mid(const FwdArgs& a, hipStream_t s);

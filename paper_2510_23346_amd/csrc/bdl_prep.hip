@@ -57,9 +57,10 @@ __device__ void pack_activations(const PrepArgs& a, int blk, int nblk) {
     }
 }
 
-// Stable placement by all 16 waves (batches of more than 1024 tokens, at
-// most kPlanWaveGroups adapters, pools of at most kPlanParMaxSlots slots,
-// ids in LDS; smaller batches count each token's rank directly): wave w
+// Stable placement by all 16 waves (batches of more than 64 tokens, at most
+// kPlanWaveGroups adapters, pools of at most kPlanParMaxSlots slots, ids in
+// LDS; up to 1024 tokens that do not fit this, each token counts its rank
+// directly, a serial walk over the batch): wave w
 // takes the tokens [w C, (w + 1) C) and counts them per group into its LDS
 // row wh[w][g]; a prefix over the waves turns the counts into each wave's
 // first position per group (and for the tokens without an adapter); then
@@ -311,7 +312,7 @@ __global__ __launch_bounds__(1024) void prep_kernel(PrepArgs a) {
     // (rowtok[n_ad + #{t' < t : no adapter}] = t), a permutation of all rows
     const int n_ad = wpre[15][0] + wsum[15][0];   // tokens with an adapter
     const int n_groups_all = wpre[15][1] + wsum[15][1];
-    if (a.T > 1024 && in_lds && n_groups_all <= kPlanWaveGroups && a.max_slots <= kPlanParMaxSlots) {
+    if (a.T > 64 && in_lds && n_groups_all <= kPlanWaveGroups && a.max_slots <= kPlanParMaxSlots) {
         place_waves(a, vid_l, ldl, r8l, tabs + 3 * a.max_slots + 15 * nwords, cg_l, gstart_l, wnone, n_groups_all,
                     n_ad);
     } else if (a.T <= 1024) {
@@ -431,7 +432,7 @@ hipError_t launch_prep(const PrepArgs& a, hipStream_t s) {
     const int nwords = (a.max_slots + 31) >> 5;
     size_t lds = 3 * (size_t)a.max_slots * sizeof(int) + 15 * (size_t)nwords * sizeof(unsigned);
     // place_waves' per-wave counts, for the batches that take it
-    if (a.T > 1024 && a.max_slots <= kPlanParMaxSlots) lds += 16 * kPlanWaveGroups * sizeof(int);
+    if (a.T > 64 && a.max_slots <= kPlanParMaxSlots) lds += 16 * kPlanWaveGroups * sizeof(int);
     hipLaunchKernelGGL(prep_kernel, dim3(1 + pack_blocks), dim3(1024), lds, s, a);
     return hipGetLastError();
 }

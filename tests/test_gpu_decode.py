@@ -1,4 +1,6 @@
-"""The one-launch decode path at the edges of its tiles, against the oracle.
+"""The one-launch decode path at the edges of its tiles, against the oracle,
+also over the row groups of batches above the decode size; the shrink of
+larger batches on activations beyond 32-bit offsets.
 
 Token counts around the 16-row blocks; inputs of one k-step, an odd number of
 them and more than the waves' shares; output widths that end inside a
@@ -63,7 +65,7 @@ def test_decode_tile_edges(torch_cuda, T, ids_kind):
     pool.close()
 
 
-@pytest.mark.parametrize("T", [5, 30, 64])
+@pytest.mark.parametrize("T", [5, 30, 64, 130])
 def test_decode_int4_and_bf16_projections_in_one_call(torch_cuda, T):
     # one launch over an INT4 and a bf16 projection, and the gated MLP with
     # gate and up on different bases (either way round)
@@ -115,3 +117,101 @@ def test_decode_int4_and_bf16_projections_in_one_call(torch_cuda, T):
         assert e["pointwise"] <= 2 * TOL, f"{fmts} mlp: {e}"
         assert pool.device_error() == 0
         pool.close()
+
+
+@pytest.mark.parametrize("T,ids_kind", [(65, "many"), (127, "one"), (128, "many"), (129, "many"), (193, "none"),
+                                        (256, "many")])
+def test_row_groups(torch_cuda, T, ids_kind):
+    # batches of 65 to 256 tokens run the decode launch in groups of nearly
+    # equal size, the last one shorter; ids and segments give the same bits
+    torch = torch_cuda
+    import paper_2510_23346_amd as bd
+    ranks = [8, 64, 3, 0, 24, 16]
+    rng = np.random.default_rng(T)
+    ids = {"one": np.full(T, 1), "none": np.full(T, -1), "many": rng.integers(-1, len(ranks), size=T)}[ids_kind]
+    spec = wl.custom_workload(f"rows-{T}-{ids_kind}", PROJS, T, ranks, ids=ids, seed=160 + T)
+    layer = wl.draw_layer(spec, slots=range(len(ranks)))
+    pool = make_pool(spec)
+    load_adapters(pool, spec, range(len(ranks)), cache=layer.adapters)
+    dl = DeviceLayer(layer)
+    refs = bdlora.layer_forward(layer)
+    pool.forward_layer([0, 1, 2], dl.X, dl.W, dl.out, dl.ids)
+    torch.cuda.synchronize()
+    assert pool.last_path() == "tile64"
+    first = dl.outputs()
+    for p, y in enumerate(first):
+        e = bdlora.rel_errors(y, refs[p])
+        assert e["pointwise"] <= TOL, f"T={T} {ids_kind} {spec.projs[p].name}: {e}"
+    for o in dl.out:
+        o.fill_(float("nan"))
+    pool.forward_layer([0, 1, 2], dl.X, dl.W, dl.out, None, segs=bd.Segments.from_ids(ids))
+    torch.cuda.synchronize()
+    for p, y in enumerate(dl.outputs()):
+        assert np.array_equal(y.view(np.uint32), first[p].view(np.uint32)), f"segments, {spec.projs[p].name}"
+    assert pool.device_error() == 0
+    pool.close()
+
+
+def test_row_groups_captured_before_an_adapter_was_loaded(torch_cuda):
+    # above the decode size a captured forward holds for adapters loaded later
+    torch = torch_cuda
+    T, ranks = 100, [8, 16, 24]
+    ids = np.random.default_rng(5).integers(0, 3, size=T)
+    spec = wl.custom_workload("rows-capture", PROJS, T, ranks, ids=ids, seed=9)
+    layer = wl.draw_layer(spec, slots=range(3))
+    pool = make_pool(spec)
+    load_adapters(pool, spec, [0], cache=layer.adapters)
+    dl = DeviceLayer(layer)
+    with torch.cuda.stream(torch.cuda.Stream()):
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            pool.forward_layer([0, 1, 2], dl.X, dl.W, dl.out, dl.ids)
+    load_adapters(pool, spec, [1, 2], cache=layer.adapters)
+    refs = bdlora.layer_forward(layer)
+    for rep in range(3):
+        for o in dl.out:
+            o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        for p, y in enumerate(dl.outputs()):
+            e = bdlora.rel_errors(y, refs[p])
+            assert e["pointwise"] <= TOL, f"replay {rep} {spec.projs[p].name}: {e}"
+    assert pool.device_error() == 0
+    pool.close()
+
+
+def test_shrink_of_activations_beyond_two_gigabytes(torch_cuda):
+    # X of 4100 x 262144 bf16 (2.15 GB): the prefill launches address it with
+    # 64-bit offsets; a few rows (the last ones past 2 GB) against float64
+    torch = torch_cuda
+    import paper_2510_23346_amd as bd
+    T, K, N, ranks = 4100, 262144, 64, [8, 5]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+
+    def normal(*shape, std=1.0):
+        return (torch.randn(*shape, generator=gen, device="cuda") * std).to(torch.bfloat16)
+    pool = bd.Pool([("row", K, (N,))], 2, 8, T)
+    A = [normal(K, r, std=K ** -0.5) for r in ranks]
+    B = [normal(r, N, std=r ** -0.5) for r in ranks]
+    bits = lambda t: t.view(torch.int16).cpu().numpy().view(np.uint16)  # noqa: E731
+    for s in range(2):
+        pool.load_adapter(s, ranks[s], 2.0, [[bits(A[s])]], [[bits(B[s])]])
+    X = torch.empty(T, K, dtype=torch.bfloat16, device="cuda")
+    for t in range(0, T, 410):
+        X[t:t + 410] = normal(410, K)
+    W = normal(N, K, std=K ** -0.5)
+    out = torch.full((T, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ids = (torch.arange(T, device="cuda") % 3 - 1).to(torch.int32)
+    pool.forward_shard(0, X, bd.pack_weight(W), ids, out)
+    torch.cuda.synchronize()
+    for t in (0, 1, 2, 2047, 4095, 4096, 4097, 4098, 4099):
+        x, a = X[t].double(), int(ids[t])
+        y = x @ W.double().t()
+        if a >= 0:
+            y += 2.0 * (x @ A[a].double()) @ B[a].double()
+        err = (out[t].double() - y).abs() / torch.maximum(y.abs(), y.square().mean().sqrt())
+        assert float(err.max()) <= 1e-2, f"row {t}: {float(err.max())}"
+    assert pool.device_error() == 0
+    pool.close()
