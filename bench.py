@@ -473,7 +473,8 @@ def measure(index, K, warmup, rotate=0, eager=False):
         names = ("prep", "shrink", "gemm")
         # the library's base GEMM: the 256 x 256 LDS-staged kernel for bf16
         # weights above 256 tokens, the 64-row kernel otherwise
-        dom, dom_name = 2, "bdl::gemm_big_kernel" if path == "large" else "bdl::gemm_kernel"
+        dom, dom_name = 2, ("bdl::gemm_kernel" if path != "large" else
+                              "bdl::gemm_big_kernel" if spec.weight_format == "bf16" else "bdl::gemm_big_int4_kernel")
         algo = g_flops
         achieved = algo / (k_ms[dom] * 1e-3) / 1e12
         roof = {"bound": "mfma", "achieved": round(achieved, 2), "peak": MFMA_BF16_PEAK_TFS,

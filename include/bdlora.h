@@ -420,8 +420,8 @@ int bdlora_profile_end(bdlora_pool_t pool, float* ms, int32_t* n);
  *   BDLORA_PATH_DECODE  the decode launch (T <= BDLORA_DECODE_MAX_T)
  *   BDLORA_PATH_TILE64  64-row tiles, base product with the fused expand: up
  *                       to 256 tokens the decode launch over row groups of up
- *                       to 64 tokens, above (INT4 weights, or operands too
- *                       large for the large tiles) a 64-row GEMM
+ *                       to 64 tokens, above (what the large tiles do not
+ *                       take) a 64-row GEMM
  *   BDLORA_PATH_MEDIUM  all rows of the batch in one tile (bf16 weights,
  *                       T <= 256, layers whose weight is large against the
  *                       fp32 partials or batches of at most 8 tokens per
@@ -430,7 +430,9 @@ int bdlora_profile_end(bdlora_pool_t pool, float* ms, int32_t* n);
  *                       base product on a stream the pool owns, forked from
  *                       the caller's stream after the plan and joined back
  *                       before the epilogue (graph capture follows the fork)
- *   BDLORA_PATH_LARGE   256 x 256 tiles (bf16 weights, T > 256)
+ *   BDLORA_PATH_LARGE   256 x 256 tiles: bf16 weights, T > 256; INT4 weights,
+ *                       T > 384 and T sum(d_out d_in) >= 2^25 per compute unit,
+ *                       outside bdlora_forward_mlp
  * INVALID_ARG for a null pool or path. */
 #define BDLORA_PATH_DECODE 1
 #define BDLORA_PATH_TILE64 2

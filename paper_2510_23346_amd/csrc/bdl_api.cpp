@@ -961,7 +961,18 @@ static int forward_prefill(bdlora_pool_t P, int n, const int32_t* projs, const v
         // its buffer loads take 32-bit byte offsets into the packed X and W
         const ProjInfo& pi = L.proj[projs[i]];
         const long long xb = ((long long)T + 15) / 16 * 16 * pi.K * 2, wb = (long long)pi.N * pi.K * 2;
-        big = big && pi.wfmt == BDLORA_WEIGHT_BF16 && xb < (1LL << 31) && wb < (1LL << 31);
+        big = big && pi.wfmt == L.proj[projs[0]].wfmt && xb < (1LL << 31) && wb < (1LL << 31);
+    }
+    // INT4: plain projections of the caller's X only, from one and a half row
+    // tiles on and where the call holds at least 16 k-steps of a tile per
+    // compute unit (8B layer shard, us a call on the 64-row kernel and here: 300
+    // tokens 84 / 92, 400 tokens 104 / 93, 1001 tokens 189 / 129; its up
+    // projection alone: 400 tokens, 5 k-steps, 39 / 54; 1001 tokens, 14, 72 / 66)
+    const bool int4 = big && L.proj[projs[0]].wfmt == BDLORA_WEIGHT_INT4_G128;
+    if (int4) {
+        long long macs = 0;
+        for (int i = 0; i < n; ++i) macs += (long long)T * L.proj[projs[i]].N * L.proj[projs[i]].K;
+        if (mlp || !pack || 2 * T <= 3 * bdl::kBigM || macs < 16LL * P->n_cu * bdl::kBigM * bdl::kBigN * 32) big = false;
     }
     const MidPlan mp = plan_mid(P, n, projs, T, n_loaded);
     const bool mid = !big && mp.use;
@@ -988,8 +999,17 @@ static int forward_prefill(bdlora_pool_t P, int n, const int32_t* projs, const v
             work += (long long)tm * ((pi.N + tn - 1) / tn) * (pi.K / 32);
         }
         const long long units = std::min<long long>(P->n_cu, bdl::kBigPartSlots);
-        const long long q = std::max(1LL, (work + units - 1) / units);
-        for (int i = 0; i < n; ++i) ksplit[i] = (int)std::max(1LL, (long long)(L.proj[projs[i]].K / 32) / q);
+        if (int4) {
+            // an item is two workgroups (column halves): half the items, rounded
+            // up per projection (K > q gives at most 2 K / q, so the partials
+            // fit all the same; 8B layer shard, 1001 tokens: 129 us
+            // a call; split twice as fine 135, unsplit 145)
+            const long long q = std::max(1LL, (2 * work + units - 1) / units);
+            for (int i = 0; i < n; ++i) ksplit[i] = (int)((L.proj[projs[i]].K / 32 + q - 1) / q);
+        } else {
+            const long long q = std::max(1LL, (work + units - 1) / units);
+            for (int i = 0; i < n; ++i) ksplit[i] = (int)std::max(1LL, (long long)(L.proj[projs[i]].K / 32) / q);
+        }
     }
     // row-major X (the caller's, on the large-tile path): its copies take the
     // two k-steps of a pair at once, so K must hold whole pairs and every
@@ -997,7 +1017,7 @@ static int forward_prefill(bdlora_pool_t P, int n, const int32_t* projs, const v
     bool xrm = big && pack;
     for (int i = 0; i < n; ++i) xrm = xrm && L.proj[projs[i]].K % 64 == 0;
     if (xrm)
-        for (int i = 0; i < n; ++i) ksplit[i] = std::min(ksplit[i], std::max(1, L.proj[projs[i]].K / 64));
+        for (int i = 0; i < n; ++i) ksplit[i] = std::min(ksplit[i], std::max(1, L.proj[projs[i]].K / (int4 ? 128 : 64)));
     // the medium-batch GEMM's copies (one k-step of a row at a time) and its
     // shrink read the caller's X too, for any K
     if (mid && pack) xrm = true;

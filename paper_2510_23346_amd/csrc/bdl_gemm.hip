@@ -1,6 +1,6 @@
-// Base GEMMs of batches above the decode size, bf16 weights: the large-tile
-// GEMM with the fused BD-LoRA expand (prefill batches, below), and the
-// medium-batch GEMM with its epilogue (further down).
+// Base GEMMs of batches above the decode size: the large-tile GEMM with the
+// fused BD-LoRA expand (prefill batches; bf16 weights below, INT4 after them),
+// and the medium-batch GEMM (bf16) with its epilogue (further down).
 //
 // Large-tile GEMM.
 // One workgroup computes a 256 x 256 output tile (tokens x columns) of one
@@ -144,6 +144,94 @@ __device__ __forceinline__ void big_wait_n(int n) {
         big_wait_barrier<2>();
     else
         big_wait_barrier<0>();
+}
+
+// The expand of a wave's 16 RB rows x 16 CB columns (from column c0): acc += Zhat
+// B over the octets of each of its 64-row blocks (octet list at blk64 + h;
+// code: the first four codes of each block; rvid, tok: adapter and token of
+// this lane's row of each row block, -1 for none).
+template <int RB, int CB>
+__device__ __forceinline__ void big_expand(const FwdArgs& a, const ProjLaunch& Pe, f32x4 (&acc)[RB][CB],
+                                           const int (&code)[RB / 4], const int (&rvid)[RB], const int (&tok)[RB],
+                                           int blk64, int c0, int N) {
+    constexpr int NH = RB / 4;
+    const int l = threadIdx.x & 63, lr = l & 15, lg = l >> 4;
+    int sig[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+        const int c = c0 + cb * 16;
+        int sgm = 0;
+#pragma unroll
+        for (int q = 1; q < kMaxSlices; ++q)
+            if (q < Pe.n_slices && c >= Pe.slice_col[q]) sgm = q;
+        sig[cb] = sgm;
+    }
+    const u32x4 zero4 = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+        const int* codes = a.tile_oct + (size_t)(blk64 + h) * a.oct_cap;
+        int cd = code[h];
+        for (int e = 0;;) {
+            if (!__any(cd >= 0)) break;
+            // the next four codes, in flight with this turn's operands
+            const int cdn = e + 8 <= a.oct_cap ? codes[e + 4 + lg] : -1;
+            const int slot = cd >> 12, r8s = (cd >> 4) & 0xff, j0 = (cd & 15) * 8;
+            u32x4 bv[CB];
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) {
+                const int col = min(c0 + cb * 16 + lr, N - 1);
+                bv[cb] = cd >= 0 ? ld16(a.pool + (size_t)slot * a.slot_stride + Pe.b_off + (size_t)col * r8s + j0)
+                                 : zero4;
+            }
+            u32x4 zh[4], zl[4];
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) {
+                if (cb == 0 || sig[cb] != sig[cb - 1]) {
+#pragma unroll
+                    for (int rb = 0; rb < 4; ++rb) {
+                        const bool match = cd >= 0 && rvid[4 * h + rb] == slot;
+                        const uint16_t* zp =
+                            Pe.Z + (size_t)max(tok[4 * h + rb], 0) * Pe.zs + sig[cb] * a.r8max + j0;
+                        zh[rb] = match ? ld16(zp) : zero4;
+                        zl[rb] = match ? ld16(zp + Pe.zplane) : zero4;
+                    }
+                }
+#pragma unroll
+                for (int rb = 0; rb < 4; ++rb) {
+                    acc[4 * h + rb][cb] = mfma(bv[cb], zh[rb], acc[4 * h + rb][cb]);
+                    acc[4 * h + rb][cb] = mfma(bv[cb], zl[rb], acc[4 * h + rb][cb]);
+                }
+            }
+            e += 4;
+            if (e + 4 > a.oct_cap) break;
+            cd = cdn;
+        }
+    }
+}
+
+// Its plain store: bf16, or fp32 where the projection asks for it.
+template <int RB, int CB>
+__device__ __forceinline__ void big_store(const ProjLaunch& P, const f32x4 (&acc)[RB][CB], const int (&tok)[RB], int c0,
+                                          int N) {
+    const int lg = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        const int row = tok[rb];
+        if (row < 0) continue;
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            const int col = c0 + cb * 16 + 4 * lg;
+            if (col >= N) continue;
+            const f32x4 v = acc[rb][cb];
+            if (P.out_f32) {
+                *reinterpret_cast<f32x4*>(P.out_f32 + (size_t)row * N + col) = v;
+            } else {
+                const uint32_t lo = (uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16);
+                const uint32_t hi = (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16);
+                *reinterpret_cast<uint2*>(P.out + (size_t)row * N + col) = make_uint2(lo, hi);
+            }
+        }
+    }
 }
 
 // RB = 16-row blocks per wave: 4 (eight waves, 4 x 2) or 8 (four waves, 2 x 2).
@@ -414,58 +502,7 @@ __global__ __launch_bounds__(128 * (16 / RB)) void gemm_big_kernel(FwdArgs a) {
     }
     }
 
-    // expand: acc += Zhat B over the octets of each 64-row block of the wave
-    int sig[8];
-#pragma unroll
-    for (int cb = 0; cb < 8; ++cb) {
-        const int c = c0 + cb * 16;
-        int sgm = 0;
-#pragma unroll
-        for (int q = 1; q < kMaxSlices; ++q)
-            if (q < Pe.n_slices && c >= Pe.slice_col[q]) sgm = q;
-        sig[cb] = sgm;
-    }
-    const u32x4 zero4 = u32x4{0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int h = 0; h < NH; ++h) {
-        const int* codes = a.tile_oct + (size_t)(mt * 4 + wr * NH + h) * a.oct_cap;
-        int cd = code[h];
-        for (int e = 0;;) {
-            if (!__any(cd >= 0)) break;
-            // the next four codes, in flight with this turn's operands
-            const int cdn = e + 8 <= a.oct_cap ? codes[e + 4 + lg] : -1;
-            const int slot = cd >> 12, r8s = (cd >> 4) & 0xff, j0 = (cd & 15) * 8;
-            u32x4 bv[8];
-#pragma unroll
-            for (int cb = 0; cb < 8; ++cb) {
-                const int col = min(c0 + cb * 16 + lr, N - 1);
-                bv[cb] = cd >= 0 ? ld16(a.pool + (size_t)slot * a.slot_stride + Pe.b_off + (size_t)col * r8s + j0)
-                                 : zero4;
-            }
-            u32x4 zh[4], zl[4];
-#pragma unroll
-            for (int cb = 0; cb < 8; ++cb) {
-                if (cb == 0 || sig[cb] != sig[cb - 1]) {
-#pragma unroll
-                    for (int rb = 0; rb < 4; ++rb) {
-                        const bool match = cd >= 0 && rvid[4 * h + rb] == slot;
-                        const uint16_t* zp =
-                            Pe.Z + (size_t)max(tok[4 * h + rb], 0) * Pe.zs + sig[cb] * a.r8max + j0;
-                        zh[rb] = match ? ld16(zp) : zero4;
-                        zl[rb] = match ? ld16(zp + Pe.zplane) : zero4;
-                    }
-                }
-#pragma unroll
-                for (int rb = 0; rb < 4; ++rb) {
-                    acc[4 * h + rb][cb] = mfma(bv[cb], zh[rb], acc[4 * h + rb][cb]);
-                    acc[4 * h + rb][cb] = mfma(bv[cb], zl[rb], acc[4 * h + rb][cb]);
-                }
-            }
-            e += 4;
-            if (e + 4 > a.oct_cap) break;
-            cd = cdn;
-        }
-    }
+    big_expand<RB, 8>(a, Pe, acc, code, rvid, tok, mt * 4 + wr * NH, c0, N);
 
     // store: lane (lr, lg) of block (rb, cb) holds row rbase + 16 rb + lr
     // (token tok[rb]), columns c0 + 16 cb + 4 lg + i
@@ -511,24 +548,188 @@ __global__ __launch_bounds__(128 * (16 / RB)) void gemm_big_kernel(FwdArgs a) {
         }
         return;
     }
+    big_store<RB, 8>(P, acc, tok, c0, N);
+}
+
+// ---------------------------------------------------------------------------
+// Large tiles on an INT4 base: rows, X copies, split tiles and expand of the
+// bf16 form, the k-loop in scale groups of 4 k-steps.
+//
+// A workgroup computes one 256 x 128 half of a work item's tile, eight waves
+// of 64 x 64.  (64 x 128 as in the bf16 form does not fit the registers: the
+// group's X fragments, 64 of them, and the group's sums stand beside the
+// tile's.)  A group's weights of a column block are 1 KB of the packed
+// layout, one copy into LDS; its scales (32 bytes per block) come with 4-byte
+// copies.  Both rings and X's hold two groups, with one barrier per group,
+// behind which the next but one is copied.  A wave holds the group's 16 X
+// fragments, and per column block unpacks the four weight fragments, sums the
+// group's products from -24 sum x (see unpack_int4_16) and adds them to the
+// tile's sums with the scale in fp32.  Bound by the issue of both units: 16
+// MFMAs for the offset join the 64 of the products, and unpacking and scaling
+// take 210 vector instructions, in the gaps of those 80.
+// Waits: every load in flight in the loop is a copy into LDS, and all of them
+// belong to the group that the barrier waits for.
+// 8B layer shard, 1001 tokens: 85 us and 13 of the fix-up launch; the 64-row
+// kernel 154.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(512) void gemm_big_int4_kernel(FwdArgs) {
+    const FwdArgs& a = kernel_args<FwdArgs>();
+    constexpr int RB = 4, CB = 4, NW = 8;
+    // two groups of X (2 pairs of 32 half fragments each), of weights (8 KB), of scales (256 B)
+    __shared__ u32x4 lds[(2 * 64 + 2 * 8) * 64 + 2 * 16];
+    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lg = l >> 4;
+    const int wr = w & 3, wc = w >> 2;
+    const int bid = blockIdx.x >> 1, half = blockIdx.x & 1;
+    if (bid >= a.total_tiles) return;
+    int p = 0;
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-        const int row = tok[rb];
-        if (row < 0) continue;
+    for (int q = 1; q < kMaxProjs; ++q)
+        if (q < a.n_proj && bid >= a.p[q].tile_base) p = q;
+    const ProjLaunch& P = a.p[p];
+    const int S = P.ksplit, item = bid - P.tile_base, local = item / S, split = item - local * S;
+    const int band = local / (kBigBand * P.tiles_n), rest = local - band * kBigBand * P.tiles_n;
+    const int bh = min(kBigBand, a.tiles_m - band * kBigBand);
+    const int nt = rest / bh, mt = band * kBigBand + (rest - nt * bh);
+    const int T = a.T, N = P.N, KS = P.K >> 5, G = KS / kInt4Group, ncb = N >> 4;
+    if (nt * kBigN + half * 128 >= N) return;
+    const int g0 = split * G / S, NG = (split + 1) * G / S - g0;   // this item's groups (at least one)
+    const int rbase = mt * kBigM + wr * 64, c0 = nt * kBigN + half * 128 + wc * 64;
+
+    // copies: half fragments w + 8 j of a pair (as in the bf16 form), weight
+    // block w of the half, the scales of its 8 blocks (4 bytes per lane)
+    const __amdgpu_buffer_rsrc_t rx = buf_rsrc(P.X, (unsigned)T * P.K * 2u);
+    const __amdgpu_buffer_rsrc_t rw = buf_rsrc(P.W, (unsigned)ncb * KS * (unsigned)kInt4FragBytes);
+    const __amdgpu_buffer_rsrc_t rs = buf_rsrc(P.Ws, (unsigned)ncb * G * 32u);
+    int xo[4];
 #pragma unroll
-        for (int cb = 0; cb < 8; ++cb) {
-            const int col = c0 + cb * 16 + 4 * lg;
-            if (col >= N) continue;
-            const f32x4 v = acc[rb][cb];
-            if (P.out_f32) {
-                *reinterpret_cast<f32x4*>(P.out_f32 + (size_t)row * N + col) = v;
-            } else {
-                const uint32_t lo = (uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16);
-                const uint32_t hi = (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16);
-                *reinterpret_cast<uint2*>(P.out + (size_t)row * N + col) = make_uint2(lo, hi);
+    for (int j = 0; j < 4; ++j) {
+        const int h = w + NW * j, rr = 8 * (h & 1) + (l >> 3), row = min((mt * 16 + (h >> 1)) * 16 + rr, T - 1);
+        const int t = (int)min((unsigned)a.rowtok[row], (unsigned)(T - 1));
+        xo[j] = t * (P.K * 2) + g0 * 256 + ((l & 7) ^ big_swz(rr)) * 16;
+    }
+    const int blk0 = nt * 16 + half * 8;
+    const int wo = (min(blk0 + w, ncb - 1) * KS + kInt4Group * g0) * kInt4FragBytes + l * 16;
+    const int so = (min(blk0 + (l >> 3), ncb - 1) * G + g0) * 32 + (l & 7) * 4;
+    u32x4* const wring = lds + 2 * 64 * 64;
+    u32x4* const sring = wring + 2 * 8 * 64;
+    auto issue = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(lds + ((g & 1) * 64 + q * 32 + w + NW * j) * 64),
+                                                         16, xo[j], g * 256 + q * 128, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void*)(wring + ((g & 1) * 8 + w) * 64), 16, wo,
+                                                 g * kInt4Group * kInt4FragBytes, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(sring + (g & 1) * 16), 4, so, g * 32, 0, 0);
+    };
+
+    f32x4 acc[RB][CB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // lane (lr, lg) of k-step j of the group finds its 8 inputs in pair j / 2's
+    // slot (row lr, chunk 4 (j mod 2) + lg; see read_x of the bf16 form)
+    const int xbase = wr * RB * 128 + (lr >> 3) * 64 + (lr & 7) * 8, xsw = big_swz(lr);
+    u32x4 x[4][RB];
+    auto read_x = [&](int g, int j) __attribute__((always_inline)) {
+        const u32x4* S0 = lds + ((g & 1) * 64 + (j >> 1) * 32) * 64 + xbase + ((4 * (j & 1) + lg) ^ xsw);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) x[j][rb] = S0[rb * 128];
+    };
+    // words of a column block's four k-steps; the group's scales of this lane's
+    // 4 columns per block, all read while no copy is in flight (the compiler
+    // waits for every copy before such a read)
+    uint32_t q[2][4];
+    uint2 sc[CB];
+    auto read_w = [&](int g, int cb) __attribute__((always_inline)) {
+        const uint32_t* B = reinterpret_cast<const uint32_t*>(wring + ((g & 1) * 8 + wc * CB + cb) * 64) + l;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) q[cb & 1][j] = B[j * 64];
+    };
+    auto read_s = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) sc[cb] = reinterpret_cast<const uint2*>(sring + (g & 1) * 16)[(wc * CB + cb) * 4 + lg];
+    };
+    const u32x4 woff = int4_offset16_operand();
+    uint32_t um = 0x00780078u, uc = 0x41804180u;
+    asm("" : "+v"(um), "+v"(uc));
+    const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    issue(0);
+    if (NG > 1) {
+        issue(1);
+        big_wait_barrier<10>();
+    } else {
+        big_wait_barrier<0>();
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) read_x(0, j);
+    read_w(0, 0);
+    read_s(0);
+    for (int g = 0; g < NG; ++g) {
+        f32x4 corr[RB];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) corr[rb] = mfma(woff, x[j][rb], j ? corr[rb] : zero);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            const uint2 c = sc[cb];
+            if (cb == CB - 1) {
+                // group g + 1 is in LDS (everything in flight belongs to it), and
+                // every wave has read all of this group
+                big_wait_barrier<0>();
+                read_s(g + 1);
+                if (g + 2 < NG) issue(g + 2);
             }
+            // the next block's words (past the last group: what the slot holds, never used)
+            read_w(cb < CB - 1 ? g : g + 1, (cb + 1) % CB);
+            f32x4 t[RB];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const u32x4 wv = unpack_int4_16(q[cb & 1][j], um, uc);
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) t[rb] = mfma(wv, x[j][rb], j ? t[rb] : corr[rb]);
+                if (cb == CB - 1) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    read_x(g + 1, j);
+                }
+            }
+            const float s[4] = {__uint_as_float(c.x << 16), __uint_as_float(c.x & 0xffff0000u),
+                                __uint_as_float(c.y << 16), __uint_as_float(c.y & 0xffff0000u)};
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[rb][cb][i] = fmaf(s[i], t[rb][i], acc[rb][cb][i]);
         }
     }
+
+    if (S > 1) {
+        // a range of a split tile: store the partial (in the bf16 form's order:
+        // waves of 64 x 128), the fix-up launch adds it
+        f32x4* dst = reinterpret_cast<f32x4*>(a.bigpart) +
+                     (size_t)(P.part_base + local * S + split) * (kBigPartElems / 4) +
+                     (size_t)((wr + 4 * half) * 32 + wc * CB) * 64 + l;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) dst[(rb * 8 + cb) * 64] = acc[rb][cb];
+        return;
+    }
+    int code[1], rvid[RB], tok[RB];
+    code[0] = rbase < T ? (a.tile_oct + (size_t)(mt * 4 + wr) * a.oct_cap)[lg] : -1;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        const int row = rbase + rb * 16 + lr;
+        // (clamped: a bad entry can cost a wrong row, never an access past X or out)
+        tok[rb] = row < T ? (int)min((unsigned)a.rowtok[row], (unsigned)(T - 1)) : -1;
+        rvid[rb] = tok[rb] >= 0 ? a.vid[tok[rb]] : -1;
+    }
+    big_expand<RB, CB>(a, P, acc, code, rvid, tok, mt * 4 + wr, c0, N);
+    big_store<RB, CB>(P, acc, tok, c0, N);
 }
 
 // wave tile height of the launch: 4 row blocks (eight waves of 64 x 128)
@@ -667,8 +868,14 @@ hipError_t launch_gemm_big(const FwdArgs& a, hipStream_t s) {
     // an even number of k-steps (pairs share a 128-byte line)
     const bool xrm = a.p[0].x_rowmajor != 0;
     for (int i = 0; i < a.n_proj; ++i)
-        if ((a.p[i].x_rowmajor != 0) != xrm || (xrm && (a.p[i].K & 63) != 0)) return hipErrorInvalidValue;
-    if (xrm)
+        if ((a.p[i].x_rowmajor != 0) != xrm || (xrm && (a.p[i].K & 63) != 0) ||
+            (a.p[i].Ws != nullptr) != (a.p[0].Ws != nullptr) ||
+            // the INT4 form: row-major X, whole scale groups, plain outputs
+            (a.p[i].Ws && (!xrm || a.mlp_act >= 0 || (a.p[i].K & 127) != 0)))
+            return hipErrorInvalidValue;
+    if (a.p[0].Ws)
+        hipLaunchKernelGGL(gemm_big_int4_kernel, dim3(2 * a.total_tiles), dim3(512), 0, s, a);
+    else if (xrm)
         hipLaunchKernelGGL((gemm_big_kernel<kBigRB, true>), dim3(a.total_tiles), dim3(128 * (16 / kBigRB)), 0, s, a);
     else
         hipLaunchKernelGGL((gemm_big_kernel<kBigRB, false>), dim3(a.total_tiles), dim3(128 * (16 / kBigRB)), 0, s, a);
