@@ -1,9 +1,10 @@
 // HIP kernels of the BD-LoRA shard forward for gfx950 (MI355X).
 //
 // A forward launch of one token batch over P projections (all sharing the
-// tokens' adapter ids) above the decode size runs these kernels on the
-// caller's stream (medium batches swap step 3 for the medium-batch GEMM and
-// its epilogue in bdl_gemm.hip, large ones for the large-tile GEMM there):
+// tokens' adapter ids) that the decode launch does not take runs these kernels
+// on the caller's stream (medium batches swap step 3 for the medium-batch GEMM
+// and its epilogue in bdl_gemm.hip, large ones for the large-tile GEMMs there;
+// step 3 is left with what those do not take above 256 tokens):
 //
 //  1. prep_kernel   -- workgroup 0 plans the batch: validates ids and groups
 //                      tokens by adapter (counting sort over slots), and
@@ -228,9 +229,7 @@ hipError_t launch_shrink(const FwdArgs& a, int mb, int nb, hipStream_t s) {
         return hipGetLastError();                                                                         \
     }
     BDL_SHRINK_CASE(1, 1, 3, false) BDL_SHRINK_CASE(1, 2, 6, false) BDL_SHRINK_CASE(1, 4, 4, false)
-    BDL_SHRINK_CASE(2, 1, 3, false) BDL_SHRINK_CASE(2, 2, 6, false) BDL_SHRINK_CASE(2, 4, 4, false)
-    BDL_SHRINK_CASE(4, 4, 4, false)
-    BDL_SHRINK_CASE(1, 1, 3, true) BDL_SHRINK_CASE(1, 2, 6, true) BDL_SHRINK_CASE(1, 4, 4, true)
+    BDL_SHRINK_CASE(2, 1, 3, false) BDL_SHRINK_CASE(2, 2, 6, false) BDL_SHRINK_CASE(4, 4, 4, false)
     BDL_SHRINK_CASE(2, 1, 3, true) BDL_SHRINK_CASE(2, 2, 6, true) BDL_SHRINK_CASE(4, 4, 4, true)
 #undef BDL_SHRINK_CASE
     return hipErrorInvalidValue;
@@ -365,8 +364,7 @@ hipError_t launch_gemm(const FwdArgs& a, int mb, int nb, hipStream_t s) {
         hipLaunchKernelGGL((gemm_kernel<M, NN>), grid, block, 0, s, a);        \
         return hipGetLastError();                                              \
     }
-    BDL_GEMM_CASE(1, 1) BDL_GEMM_CASE(1, 2) BDL_GEMM_CASE(1, 4)
-    BDL_GEMM_CASE(2, 1) BDL_GEMM_CASE(2, 2) BDL_GEMM_CASE(2, 4)
+    // (batches above 256 tokens only: always 64 rows)
     BDL_GEMM_CASE(4, 1) BDL_GEMM_CASE(4, 2) BDL_GEMM_CASE(4, 4)
 #undef BDL_GEMM_CASE
     return hipErrorInvalidValue;
