@@ -31,6 +31,9 @@
  *  - Adapter ids: int32, one per token; -1 = no adapter (base only).  An id
  *    that is out of range or names an empty slot is treated as -1 and raises
  *    the pool's sticky device error flag (see bdlora_get_device_error).
+ *  - An out of a forward call may share memory with an X of the same call
+ *    (in whole or in part): the call reads all of X as it was before.  Nothing
+ *    else that a call writes may overlap anything it reads or writes.
  *  - Device pointers are caller-owned and must stay valid until the work
  *    enqueued on `stream` has finished.  `stream` is a hipStream_t (NULL =
  *    the default stream).  Forward calls only enqueue; they never block.

@@ -755,6 +755,18 @@ static int decode_act_max(bdlora_pool_t P, int T) {
     return std::min({T, loaded_adapters(P), bdl::kDecodeMaxT});
 }
 
+// An out of the call may share memory with an X of the call: whether X[j]
+// (T x its d_in) meets any of the outs (T x their d_out; null: none).
+static bool out_meets_x(const Layout& L, int n, const int32_t* projs, const void* const* X, void* const* out, int T, int j) {
+    const char* x0 = static_cast<const char*>(X[j]);
+    const char* x1 = x0 + (size_t)T * L.proj[projs[j]].K * 2;
+    for (int i = 0; i < n; ++i) {
+        const char* o = static_cast<const char*>(out[i]);
+        if (o && o < x1 && x0 < o + (size_t)T * L.proj[projs[i]].N * 2) return true;
+    }
+    return false;
+}
+
 struct DecZ {
     uint16_t* z[bdl::kMaxProjs];
 };
@@ -765,10 +777,29 @@ static DecZ pool_dec_z(bdlora_pool_t P, int n, const int32_t* projs) {
     return r;
 }
 
+static DecZ pool_xp(bdlora_pool_t P, int n, const int32_t* projs) {
+    DecZ r;
+    for (int i = 0; i < n; ++i) r.z[i] = P->d_Xp[projs[i]];
+    return r;
+}
+
 static int forward_decode(bdlora_pool_t P, int n, const int32_t* projs, const void* const* X,
                           const void* const* W, void* const* out, const Batch& B, int T, hipStream_t s,
-                          uint16_t* const* Z, int mlp_act = -1, uint16_t* h = nullptr) {
+                          uint16_t* const* Z, uint16_t* const* Xcopy, int mlp_act = -1, uint16_t* h = nullptr) {
     const Layout& L = P->L;
+    // the launch stores outputs while other workgroups still read X: an X that
+    // an out shares memory with is read from a copy (Xcopy[i], for projection i)
+    const void* Xr[bdl::kMaxProjs];
+    int copies = 0, copied[bdl::kMaxProjs];
+    for (int i = 0; i < n; ++i) {
+        Xr[i] = X[i];
+        if (!out_meets_x(L, n, projs, X, out, T, i)) continue;
+        int same = -1;
+        for (int c = 0; c < copies && same < 0; ++c)
+            if (X[copied[c]] == X[i] && L.proj[projs[copied[c]]].K == L.proj[projs[i]].K) same = copied[c];
+        if (same < 0) copied[copies++] = i;
+        Xr[i] = Xcopy[same < 0 ? i : same];
+    }
     bdl::DecArgs da;
     std::memset(&da, 0, sizeof(da));
     da.n_proj = n;
@@ -791,7 +822,7 @@ static int forward_decode(bdlora_pool_t P, int n, const int32_t* projs, const vo
         const int i = order[q];
         const ProjInfo& pi = L.proj[projs[i]];
         bdl::DecProj& d = da.p[q];
-        d.X = (const uint16_t*)X[i];
+        d.X = (const uint16_t*)Xr[i];
         d.W = (const uint16_t*)W[i];
         d.Ws = int4_scales(pi, W[i]);
         d.out = (uint16_t*)out[i];
@@ -841,6 +872,9 @@ static int forward_decode(bdlora_pool_t P, int n, const int32_t* projs, const vo
         ++P->prof_used;
         --P->prof_left;
     }
+    for (int c = 0; c < copies; ++c)
+        BDL_HIP(bdl::launch_copy((const uint16_t*)X[copied[c]], Xcopy[copied[c]],
+                                 (long long)T * L.proj[projs[copied[c]]].K, s));
     const int before = T <= bdl::kDecodeMaxT ? 3 : 5;              // the launch's timing interval: 1 or 2
     if (ev)
         for (int i = 0; i < before; ++i) BDL_HIP(hipEventRecord(ev[i], s));
@@ -963,6 +997,12 @@ static int forward_prefill(bdlora_pool_t P, int n, const int32_t* projs, const v
         const long long xb = ((long long)T + 15) / 16 * 16 * pi.K * 2, wb = (long long)pi.N * pi.K * 2;
         big = big && pi.wfmt == L.proj[projs[0]].wfmt && xb < (1LL << 31) && wb < (1LL << 31);
     }
+    // an out that shares memory with an X: the bf16 large tiles read a packed
+    // copy of X, and an INT4 call stays on the 64-row kernel, which does (the
+    // shrink is past its reads of X when either stores; the medium-batch
+    // epilogue stores after every read of X)
+    bool inplace = false;
+    for (int i = 0; i < n && pack; ++i) inplace = inplace || out_meets_x(L, n, projs, X, out, T, i);
     // INT4: plain projections of the caller's X only, from one and a half row
     // tiles on and where the call holds at least 16 k-steps of a tile per
     // compute unit (8B layer shard, us a call on the 64-row kernel and here: 300
@@ -972,7 +1012,7 @@ static int forward_prefill(bdlora_pool_t P, int n, const int32_t* projs, const v
     if (int4) {
         long long macs = 0;
         for (int i = 0; i < n; ++i) macs += (long long)T * L.proj[projs[i]].N * L.proj[projs[i]].K;
-        if (mlp || !pack || 2 * T <= 3 * bdl::kBigM || macs < 16LL * P->n_cu * bdl::kBigM * bdl::kBigN * 32) big = false;
+        if (mlp || !pack || inplace || 2 * T <= 3 * bdl::kBigM || macs < 16LL * P->n_cu * bdl::kBigM * bdl::kBigN * 32) big = false;
     }
     const MidPlan mp = plan_mid(P, n, projs, T, n_loaded);
     const bool mid = !big && mp.use;
@@ -1014,7 +1054,7 @@ static int forward_prefill(bdlora_pool_t P, int n, const int32_t* projs, const v
     // row-major X (the caller's, on the large-tile path): its copies take the
     // two k-steps of a pair at once, so K must hold whole pairs and every
     // k-range at least one pair
-    bool xrm = big && pack;
+    bool xrm = big && pack && !inplace;
     for (int i = 0; i < n; ++i) xrm = xrm && L.proj[projs[i]].K % 64 == 0;
     if (xrm)
         for (int i = 0; i < n; ++i) ksplit[i] = std::min(ksplit[i], std::max(1, L.proj[projs[i]].K / (int4 ? 128 : 64)));
@@ -1263,7 +1303,7 @@ int bdlora_forward_layer(bdlora_pool_t P, int32_t n, const int32_t* projs, const
     if (!guard.ok) return fail(BDLORA_ERR_HIP, "hipSetDevice failed");
     hipStream_t s = (hipStream_t)stream;
 
-    if (use_rows(P, n, projs, T)) return forward_decode(P, n, projs, X, W, out, B, T, s, pool_dec_z(P, n, projs).z);
+    if (use_rows(P, n, projs, T)) return forward_decode(P, n, projs, X, W, out, B, T, s, pool_dec_z(P, n, projs).z, pool_xp(P, n, projs).z);
     return forward_prefill(P, n, projs, X, W, out, B, T, s);
 }
 
@@ -1287,6 +1327,14 @@ int bdlora_forward_layer_static(bdlora_pool_t P, int32_t n, const int32_t* projs
     for (int i = 0; i < n; ++i) {
         Z[i] = reinterpret_cast<uint16_t*>(base + off);
         off = round_up(off + (L.proj[projs[i]].zs + 15) / 16 * (long long)T * bdl::kDecZLine * 2, 256);
+    }
+    // ... and copies of the activations that an out shares memory with (the
+    // capacity below counts as much)
+    uint16_t* Xcopy[bdl::kMaxProjs] = {};
+    for (int i = 0; i < n; ++i) {
+        if (!out_meets_x(L, n, projs, X, out, T, i)) continue;
+        Xcopy[i] = reinterpret_cast<uint16_t*>(base + off);
+        off = round_up(off + (long long)T * L.proj[projs[i]].K * 2, 256);
     }
     if (off > bdl::kStaticScratchBytes) return fail(BDLORA_ERR_SHAPE, "the call exceeds the static scratch");
     // The capacity of the entry point counts plan tables, packed activations
@@ -1313,7 +1361,7 @@ int bdlora_forward_layer_static(bdlora_pool_t P, int32_t n, const int32_t* projs
                                           std::to_string((long long)bdl::kStaticScratchBytes));
     DeviceGuard guard(P->device);
     if (!guard.ok) return fail(BDLORA_ERR_HIP, "hipSetDevice failed");
-    return forward_decode(P, n, projs, X, W, out, B, T, (hipStream_t)stream, Z);
+    return forward_decode(P, n, projs, X, W, out, B, T, (hipStream_t)stream, Z, Xcopy);
 }
 
 int bdlora_forward_shard(bdlora_pool_t P, int32_t proj, const void* X, const void* W, const int32_t* ids,
@@ -1371,10 +1419,12 @@ int bdlora_forward_mlp(bdlora_pool_t P, int32_t act, const int32_t* first, int32
         mo.h = h;
         mo.h_KS = 0;                               // row-major
         int rc = use_rows(P, nf, first, T)
-                     ? forward_decode(P, nf, first, xs, W_first, none, B, T, s, pool_dec_z(P, nf, first).z, act, h)
+                     ? forward_decode(P, nf, first, xs, W_first, none, B, T, s, pool_dec_z(P, nf, first).z,
+                                      pool_xp(P, nf, first).z, act, h)
                      : forward_prefill(P, nf, first, xs, W_first, none, B, T, s, true, &mo);
         if (rc) return rc;
-        return use_rows(P, 1, dn, T) ? forward_decode(P, 1, dn, xd, wd, od, B, T, s, pool_dec_z(P, 1, dn).z)
+        return use_rows(P, 1, dn, T) ? forward_decode(P, 1, dn, xd, wd, od, B, T, s, pool_dec_z(P, 1, dn).z,
+                                                    pool_xp(P, 1, dn).z)
                                      : forward_prefill(P, 1, dn, xd, wd, od, B, T, s);
     }
     // larger batches: the first projections' epilogue writes H (bf16,

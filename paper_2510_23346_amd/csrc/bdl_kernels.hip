@@ -397,6 +397,18 @@ hipError_t launch_pack_rows(const uint16_t* src, uint16_t* dst, int rows, int K,
     return hipGetLastError();
 }
 
+__global__ void copy_kernel(const uint16_t* src, uint16_t* dst, long long pieces) {
+    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < pieces; i += (long long)gridDim.x * blockDim.x)
+        *reinterpret_cast<u32x4*>(dst + i * 8) = ld16(src + i * 8);
+}
+
+hipError_t launch_copy(const uint16_t* src, uint16_t* dst, long long elems, hipStream_t s) {
+    if (elems < 8 || elems % 8) return hipErrorInvalidValue;
+    const long long blocks = (elems / 8 + 255) / 256;
+    hipLaunchKernelGGL(copy_kernel, dim3((unsigned)(blocks < 8192 ? blocks : 8192)), dim3(256), 0, s, src, dst, elems / 8);
+    return hipGetLastError();
+}
+
 // INT4 base weight: nn.Linear rows of nibbles (low nibble = even input) and
 // bf16 scales [N x K/128] -> the forward layout (one 32-bit word per lane and
 // k-step, then the scales grouped per 16-column block).  Thread = one word or

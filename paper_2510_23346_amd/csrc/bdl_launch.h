@@ -198,6 +198,7 @@ hipError_t launch_gemm_mid(const FwdArgs& a, hipStream_t s);
 hipError_t launch_mid_epi(const FwdArgs& a, hipStream_t s);
 hipError_t launch_pack_adapter(uint16_t* dst_a, uint16_t* dst_b, const uint16_t* stage, int K,
                                int n_slices, const int* slice_out, int rank, int r8, hipStream_t s);
+hipError_t launch_copy(const uint16_t* src, uint16_t* dst, long long elems, hipStream_t s);   // elems: a multiple of 8
 hipError_t launch_pack_rows(const uint16_t* src, uint16_t* dst, int rows, int K, hipStream_t s);
 // rank and scale tables of up to kMaxSlotBatch consecutive slots (kernel argument)
 constexpr int kMaxSlotBatch = 64;

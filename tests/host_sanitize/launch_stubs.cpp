@@ -18,6 +18,7 @@ hipError_t launch_mid_epi(const FwdArgs&, hipStream_t) { return hipErrorNotSuppo
 hipError_t launch_pack_adapter(uint16_t*, uint16_t*, const uint16_t*, int, int, const int*, int, int, hipStream_t) {
     return hipErrorNotSupported;
 }
+hipError_t launch_copy(const uint16_t*, uint16_t*, long long, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_pack_rows(const uint16_t*, uint16_t*, int, int, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_set_slots(int*, float*, int*, const SlotBatch&, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_pack_int4(const uint8_t*, const uint16_t*, uint32_t*, uint16_t*, int, int, hipStream_t) {

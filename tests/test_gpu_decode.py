@@ -215,3 +215,69 @@ def test_shrink_of_activations_beyond_two_gigabytes(torch_cuda):
         assert float(err.max()) <= 1e-2, f"row {t}: {float(err.max())}"
     assert pool.device_error() == 0
     pool.close()
+
+
+@pytest.mark.parametrize("T,fmt,entry,path", [
+    (1, "bf16", "layer", "decode"), (16, "bf16", "static", "decode"), (64, "bf16", "layer", "decode"),
+    (64, "int4", "static", "decode"), (100, "bf16", "layer", "medium"), (100, "int4", "layer", "tile64"),
+    (200, "bf16", "layer", "tile64"), (300, "bf16", "layer", "large"), (300, "int4", "layer", "tile64"),
+    (400, "int4", "wide", "tile64")])
+def test_out_may_share_memory_with_x(torch_cuda, T, fmt, entry, path):
+    # an out on top of its own X and of the X that another projection shares,
+    # another one beginning inside an X: every X is read as it was before the
+    # call.  (Each launch sequence; "wide" would take the INT4 large tiles.)
+    # Against the same call with memory of its own, to the tolerance above
+    # (twice: both sides round): the large tiles add k-steps in another order.
+    torch = torch_cuda
+    import paper_2510_23346_amd as bd
+    projs = [("column", 1408, (16000,))] if entry == "wide" else [
+        ("column", 256, (256,)), ("column", 256, (192,)), ("row", 128, (320,))]
+    f = bd.WEIGHT_INT4_G128 if fmt == "int4" else bd.WEIGHT_BF16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(T)
+
+    def normal(*shape, std=1.0):
+        return (torch.randn(*shape, generator=gen, device="cuda") * std).to(torch.bfloat16)
+    pool = bd.Pool(projs, 16, 24, T, weight_formats=f)
+    bits = lambda t: t.view(torch.int16).cpu().numpy().view(np.uint16)  # noqa: E731
+    for s in range(16):
+        r = (8, 24, 16)[s % 3]
+        pool.load_adapter(s, r, 2.0, [[bits(normal(k, r, std=k ** -0.5))] for _, k, _ in projs],
+                          [[bits(normal(r, n[0], std=r ** -0.5))] for _, _, n in projs])
+    W = []
+    for _, k, (n,) in projs:
+        if fmt == "bf16":
+            W.append(bd.pack_weight(normal(n, k, std=k ** -0.5)))
+        else:
+            q = torch.randint(0, 256, (n, k // 2), generator=gen, device="cuda", dtype=torch.uint8)
+            W.append(bd.pack_weight_int4(q, (torch.rand(n, k // 128, generator=gen, device="cuda") * 0.01).bfloat16()))
+    x0 = [normal(T, k) for _, k, _ in projs]
+    if entry != "wide":
+        x0[1] = x0[0]
+    ids = torch.randint(-1, 16, (T,), generator=gen, device="cuda", dtype=torch.int32)
+    call = pool.forward_layer_static if entry == "static" else pool.forward_layer
+    idx = list(range(len(projs)))
+    want = [torch.empty(T, n, dtype=torch.bfloat16, device="cuda") for _, _, (n,) in projs]
+    call(idx, x0, W, want, ids)
+    torch.cuda.synchronize()
+    for rep in range(3):
+        if entry == "wide":
+            mem = [normal(T * 16000)]
+            X, out = [mem[0][:T * 1408].view(T, 1408)], [mem[0].view(T, 16000)]
+        else:
+            mem = [normal(T * 256), normal(T * 192), normal(T * (128 + 320))]
+            X = [mem[0].view(T, 256), mem[0].view(T, 256), mem[2][:T * 128].view(T, 128)]
+            at = T * 64                                       # half way into the third X
+            out = [mem[0].view(T, 256), mem[1].view(T, 192), mem[2][at:at + T * 320].view(T, 320)]
+        for x, v in zip(X, x0):
+            x.copy_(v)
+        torch.cuda.synchronize()
+        call(idx, X, W, out, ids)
+        torch.cuda.synchronize()
+        assert pool.last_path() == path
+        for i in idx:
+            y, r = out[i].double(), want[i].double()
+            err = float(((y - r).abs() / torch.maximum(r.abs(), r.square().mean().sqrt())).max())
+            assert err <= (0.0 if path != "large" and entry != "wide" else 2 * TOL), f"call {rep} projection {i}: {err}"
+    assert pool.device_error() == 0
+    pool.close()
