@@ -96,8 +96,8 @@ extern "C" {
  *   with one bf16 scale per output column and group of 128 inputs,
  *   W[n][k] = scale[n][k / 128] * q[n][k], q in -8..7, packed by
  *   bdlora_pack_weight_int4.  The kernels multiply the raw q by the bf16
- *   activations on the matrix cores and apply the scale in fp32 per k-step,
- *   so no dequantized weight is ever formed. */
+ *   activations on the matrix cores and apply the scale in fp32 to sums over
+ *   32 to 128 inputs of a group, so no dequantized weight is ever formed. */
 #define BDLORA_WEIGHT_BF16      0
 #define BDLORA_WEIGHT_INT4_G128 1
 

@@ -306,8 +306,11 @@ __device__ __forceinline__ void dec_k_bf16(f32x4 (&acc)[MB][NB], const DecProj* 
 }
 
 // The same on an INT4 base, in scale groups of 4 k-steps.  With q + 8 held as
-// 128 + (q + 8), sum x (136 + q) - 136 sum x = sum x q; the scale of the group
-// is applied to that sum in fp32.
+// 16 + (q + 8), the sum of x (24 + q) over a pair of k-steps, begun at
+// -24 sum x, is sum x q; the group's scale is applied to it in fp32.  (Begun
+// there, so that no large sum is rounded: the two added up over a whole group
+// apart, with 128 + (q + 8), were 4 times less exact, and 10 times with
+// activations of mean 1.)
 template <int MB, int NB, int C0, int NC, class Pre, class Mid>
 __device__ __forceinline__ void dec_k_int4(f32x4 (&acc)[MB][NB], const DecProj* const (&Pc)[NB], const int (&blk)[NB],
                                            const XRows<MB>& x, int KS, int kq, int kparts, Pre pre, Mid mid) {
@@ -337,11 +340,11 @@ __device__ __forceinline__ void dec_k_int4(f32x4 (&acc)[MB][NB], const DecProj* 
             sc[d][c] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rs[c], (int)so, 0, 0));
         }
     };
-    auto load_x = [&](int d, int i) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) x.load(xv[d][j], 2 * (g0 + i) + j, i < n);
-    };
-    const u32x4 off = int4_offset_operand();
+    auto load_x = [&](int d, int h, int i) __attribute__((always_inline)) { x.load(xv[d][h], 2 * (g0 + i) + h, i < n); };
+    const u32x4 off = int4_offset16_operand();
+    uint32_t um = 0x00780078u, uc = 0x41804180u;
+    asm("" : "+v"(um), "+v"(uc));
+    const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
     auto comp = [&](int dw, int dx, int next) __attribute__((always_inline)) {
         float s[NC][4];
         u32x4 wf[NC][4];
@@ -352,40 +355,32 @@ __device__ __forceinline__ void dec_k_int4(f32x4 (&acc)[MB][NB], const DecProj* 
             s[c][2] = __uint_as_float(sc[dw][c].y << 16);
             s[c][3] = __uint_as_float(sc[dw][c].y & 0xffff0000u);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) wf[c][j] = unpack_int4(q[dw][c][j]);
-        }
-        // t[rb][c] = sum over the group of x (136 + q), corr[rb] = -136 sum x
-        f32x4 t[MB][NC], corr[MB];
-#pragma unroll
-        for (int rb = 0; rb < MB; ++rb) {
-            corr[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int c = 0; c < NC; ++c) t[rb][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < 4; ++j) wf[c][j] = unpack_int4_16(q[dw][c][j], um, uc);
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if ((j & 1) == 0) x.put(xv[dx][j >> 1]);
+        for (int h = 0; h < 2; ++h) {
+            x.put(xv[dx][h]);
+            if (next >= 0) load_x(dx, h, next);
 #pragma unroll
             for (int rb = 0; rb < MB; ++rb) {
-                const u32x4 xf = x.get(rb, j & 1);
-                corr[rb] = mfma(off, xf, corr[rb]);
+                const u32x4 x0 = x.get(rb, 0), x1 = x.get(rb, 1);
+                const f32x4 corr = mfma(off, x1, mfma(off, x0, zero));
 #pragma unroll
-                for (int c = 0; c < NC; ++c) t[rb][c] = mfma(wf[c][j], xf, t[rb][c]);
+                for (int c = 0; c < NC; ++c) {
+                    const f32x4 t = mfma(wf[c][2 * h + 1], x1, mfma(wf[c][2 * h], x0, corr));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[rb][C0 + c][i] = fmaf(s[c][i], t[i], acc[rb][C0 + c][i]);
+                }
             }
         }
-        if (next >= 0) load_x(dx, next);
-#pragma unroll
-        for (int rb = 0; rb < MB; ++rb)
-#pragma unroll
-            for (int c = 0; c < NC; ++c)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    acc[rb][C0 + c][i] = fmaf(s[c][i], t[rb][c][i] + corr[rb][i], acc[rb][C0 + c][i]);
     };
 #pragma unroll
     for (int d = 0; d < DW; ++d) load_w(d, d);
 #pragma unroll
-    for (int d = 0; d < D; ++d) load_x(d, d);
+    for (int d = 0; d < D; ++d) {
+        load_x(d, 0, d);
+        load_x(d, 1, d);
+    }
     pre();
     int i = 0;
     for (; i + DW < n; i += DW) {

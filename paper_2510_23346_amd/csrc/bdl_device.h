@@ -112,7 +112,8 @@ __device__ __forceinline__ void mma_range(f32x4 (&acc)[MB][NB], const uint16_t* 
 // Each nibble u becomes the bf16 number 128 + u (exponent of 128, u in the low
 // mantissa bits), which is exact; an extra MFMA against -136 removes the
 // offset, so the matrix cores see exactly sum_k x_k q_k for the k-step.  The
-// group scale is applied in fp32 to that k-step's product.
+// group scale is applied in fp32 to that k-step's product.  (The 64-row kernel;
+// the decode launch and the large tiles take the form after it.)
 constexpr int kInt4Group = 4;                 // k-steps per scale group (128 inputs)
 constexpr int kInt4FragBytes = 256;           // one k-step of one 16-column block
 
@@ -127,7 +128,7 @@ __device__ __forceinline__ u32x4 int4_offset_operand() {
 
 // The same with 16 + u (u in the mantissa bits 6..3) and an offset of -24: one
 // more shift per fragment, and the offset's rounding is 5.7 times smaller,
-// for sums over a whole scale group.
+// for sums over a pair of k-steps or a whole scale group.
 // (m = 0x00780078 and c = 0x41804180 in registers: one and-or per word then)
 __device__ __forceinline__ u32x4 unpack_int4_16(uint32_t w, uint32_t m, uint32_t c) {
     return u32x4{((w << 3) & m) | c, ((w >> 1) & m) | c, ((w >> 5) & m) | c, ((w >> 9) & m) | c};

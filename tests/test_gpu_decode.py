@@ -281,3 +281,40 @@ def test_out_may_share_memory_with_x(torch_cuda, T, fmt, entry, path):
             assert err <= (0.0 if path != "large" and entry != "wide" else 2 * TOL), f"call {rep} projection {i}: {err}"
     assert pool.device_error() == 0
     pool.close()
+
+
+@pytest.mark.parametrize("mean", [0.0, 1.0])
+@pytest.mark.parametrize("T,N,path", [(5, 256, "decode"), (32, 256, "decode"), (48, 256, "decode"), (64, 256, "decode"),
+                                      (200, 256, "tile64"), (800, 2688, "large")])
+def test_int4_sums_are_as_exact_as_the_64_row_kernel(torch_cuda, T, N, path, mean):
+    # The fp32 sums of an INT4 base, seen through outputs that are exactly zero:
+    # the second half of the inputs repeats the first, permuted inside each
+    # scale group, with the opposite weights.  What comes out is the sums'
+    # rounding.  The 64-row kernel (above 256 tokens) takes the offset of the
+    # stored nibbles out of every single k-step; the rounding of the decode
+    # launch and of the large tiles, over the same rows, is no larger.
+    torch = torch_cuda
+    import paper_2510_23346_amd as bd
+    K, G, TB = 4096, 16, 300
+    R = max(T, TB)
+    rng = np.random.default_rng(17)
+    q = rng.integers(-7, 8, size=(N, G, 128))
+    s = np.tile(rng.uniform(0.005, 0.02, size=(N, G)).astype(np.float32), 2)
+    x = torch.from_numpy(rng.standard_normal((R, G, 128)).astype(np.float32) + np.float32(mean)).bfloat16()
+    perm = np.stack([rng.permutation(128) for _ in range(G)])
+    take = torch.from_numpy(perm)[None].expand(R, G, 128)
+    X = torch.cat([x, torch.gather(x, 2, take)], dim=1).reshape(R, K).cuda()
+    qq = np.concatenate([q, -np.take_along_axis(q, np.broadcast_to(perm, q.shape), axis=2)], axis=1).reshape(N, K) + 8
+    nib = torch.from_numpy((qq[:, 0::2] | (qq[:, 1::2] << 4)).astype(np.uint8)).cuda()
+    W = bd.pack_weight_int4(nib, torch.from_numpy(s).bfloat16().cuda())
+    pool = bd.Pool([("row", K, (N,))], 1, 8, R, weight_formats=bd.WEIGHT_INT4_G128)
+    rms = {}
+    for t, want in ((T, path), (TB, "tile64")):
+        out = torch.full((t, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        pool.forward_shard(0, X[:t], W, torch.full((t,), -1, dtype=torch.int32, device="cuda"), out)
+        torch.cuda.synchronize()
+        rms[t] = float(out[:min(T, TB)].double().square().mean().sqrt())
+        assert pool.last_path() == want
+    assert rms[TB] > 0
+    assert rms[T] <= rms[TB], f"rounding {rms[T]:.3e}, 64-row kernel {rms[TB]:.3e}"
+    pool.close()
