@@ -13,6 +13,7 @@
 #include <stdint.h>
 
 #include "bdl_launch.h"
+#include "bdl_xaddr.h"
 
 namespace bdl {
 
@@ -225,14 +226,17 @@ __device__ __forceinline__ u32x4 buf16(__amdgpu_buffer_rsrc_t r, unsigned off) {
 // swizzle(row), so that both sides hit distinct banks.
 __device__ __forceinline__ int x_swz(int r) { return ((r >> 1) ^ ((r & 1) << 2)) & 7; }
 
-// BIG: X of 2 GB or more, beyond a buffer's 32-bit offsets (64-bit addresses;
-// a load that is not wanted repeats the row's first pair, unused).
+// BIG: X of 2 GB or more, beyond a buffer's 32-bit offsets (64-bit addresses,
+// which no bounds check guards: every load lies inside X by x_pair_offset, and
+// one that is not wanted repeats the row's first pair, unused).
 template <int MB, bool BIG = false>
 struct XRows {
     __amdgpu_buffer_rsrc_t rx;
     unsigned ro[MB][2];     // byte offset of this lane's chunk of pair 0
     unsigned st;            // bytes from one pair to the next
-    const char* rp[BIG ? MB : 1][2];   // BIG: the chunk's address instead
+    const char* rp[BIG ? MB : 1][2];   // BIG: the chunk's address instead,
+    int kx, ch[2];          // the inputs of a row and the chunk
+    bool pk;                // and whether X is packed
     u32x4* buf;             // this wave's MB x 128 pieces
     int pos[2];             // where this lane's operand of k-step e of a pair lies in a row block
 
@@ -250,11 +254,11 @@ struct XRows {
                 const int r = 8 * h + (l >> 3);
                 const unsigned c = (unsigned)((l & 7) ^ x_swz(r)) * 16u;
                 if constexpr (BIG)
-                    rp[rb][h] = reinterpret_cast<const char*>(X + (size_t)row(rb * 16 + r) * K) + c;
+                    rp[rb][h] = reinterpret_cast<const char*>(X) + x_chunk_offset(false, row(rb * 16 + r), K, (int)c >> 4);
                 else
                     ro[rb][h] = (unsigned)row(rb * 16 + r) * K * 2u + c;
             }
-        init_pos();
+        init_pos(K, false);
     }
     // the same from X in the fragment layout (rows padded to 16)
     template <class Row>
@@ -271,14 +275,20 @@ struct XRows {
                 const int r = 8 * h + (l >> 3), c = (l & 7) ^ x_swz(r), t = row(rb * 16 + r);
                 const unsigned o = (unsigned)((t & 15) + 16 * (c & 3)) * 16u + (unsigned)(c >> 2) * 1024u;
                 if constexpr (BIG)
-                    rp[rb][h] = reinterpret_cast<const char*>(Xp + frag_index(t >> 4, 0, (int)KS)) + o;
+                    rp[rb][h] = reinterpret_cast<const char*>(Xp) + x_chunk_offset(true, t, K, c);
                 else
                     ro[rb][h] = (unsigned)(t >> 4) * KS * 1024u + o;
             }
-        init_pos();
+        init_pos(K, true);
     }
-    __device__ __forceinline__ void init_pos() {
+    __device__ __forceinline__ void init_pos(int K, bool packed) {
         const int l = threadIdx.x & 63, lr = l & 15, lg = l >> 4;
+        if constexpr (BIG) {
+            kx = K;
+            pk = packed;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) ch[h] = (l & 7) ^ x_swz(8 * h + (l >> 3));
+        }
 #pragma unroll
         for (int e = 0; e < 2; ++e) pos[e] = (lr >> 3) * 64 + (lr & 7) * 8 + ((4 * e + lg) ^ x_swz(lr));
     }
@@ -289,7 +299,7 @@ struct XRows {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 if constexpr (BIG)
-                    v[rb][h] = *reinterpret_cast<const u32x4*>(rp[rb][h] + (ok ? (size_t)g * st : 0));
+                    v[rb][h] = *reinterpret_cast<const u32x4*>(rp[rb][h] + x_pair_offset(pk, kx, ch[h], ok ? g : 0));
                 else
                     v[rb][h] = buf16(rx, ok ? ro[rb][h] + (unsigned)g * st : kOob);
             }

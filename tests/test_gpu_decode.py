@@ -181,12 +181,14 @@ def test_row_groups_captured_before_an_adapter_was_loaded(torch_cuda):
     pool.close()
 
 
-def test_shrink_of_activations_beyond_two_gigabytes(torch_cuda):
-    # X of 4100 x 262144 bf16 (2.15 GB): the prefill launches address it with
-    # 64-bit offsets; a few rows (the last ones past 2 GB) against float64
+@pytest.mark.parametrize("T,K", [(4100, 262144), (32768, 32800)])
+def test_shrink_of_activations_beyond_two_gigabytes(torch_cuda, T, K):
+    # X of 4100 x 262144 bf16 (2.15 GB), and one of an odd number of k-steps
+    # that ends where its memory does (2050 MiB): the prefill launches address
+    # it with 64-bit offsets; a few rows (the last ones past 2 GB) against float64
     torch = torch_cuda
     import paper_2510_23346_amd as bd
-    T, K, N, ranks = 4100, 262144, 64, [8, 5]
+    N, ranks = 64, [8, 5]
     gen = torch.Generator(device="cuda")
     gen.manual_seed(3)
 
@@ -200,17 +202,50 @@ def test_shrink_of_activations_beyond_two_gigabytes(torch_cuda):
         pool.load_adapter(s, ranks[s], 2.0, [[bits(A[s])]], [[bits(B[s])]])
     X = torch.empty(T, K, dtype=torch.bfloat16, device="cuda")
     for t in range(0, T, 410):
-        X[t:t + 410] = normal(410, K)
+        X[t:t + 410] = normal(min(410, T - t), K)
     W = normal(N, K, std=K ** -0.5)
     out = torch.full((T, N), float("nan"), dtype=torch.bfloat16, device="cuda")
     ids = (torch.arange(T, device="cuda") % 3 - 1).to(torch.int32)
     pool.forward_shard(0, X, bd.pack_weight(W), ids, out)
     torch.cuda.synchronize()
-    for t in (0, 1, 2, 2047, 4095, 4096, 4097, 4098, 4099):
+    for t in (0, 1, 2, 2047, 4095, T - 5, T - 4, T - 3, T - 2, T - 1):
         x, a = X[t].double(), int(ids[t])
         y = x @ W.double().t()
         if a >= 0:
             y += 2.0 * (x @ A[a].double()) @ B[a].double()
+        err = (out[t].double() - y).abs() / torch.maximum(y.abs(), y.square().mean().sqrt())
+        assert float(err.max()) <= 1e-2, f"row {t}: {float(err.max())}"
+    assert pool.device_error() == 0
+    pool.close()
+
+
+def test_mlp_intermediate_beyond_two_gigabytes(torch_cuda):
+    # the same for an intermediate of 32768 x 32800, which down's shrink reads
+    # in its packed form (an odd number of k-steps, no row of padding)
+    torch = torch_cuda
+    import paper_2510_23346_amd as bd
+    T, K, H, N = 32768, 64, 32800, 64
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(4)
+
+    def normal(*shape, std=1.0):
+        return (torch.randn(*shape, generator=gen, device="cuda") * std).to(torch.bfloat16)
+    pool = bd.Pool([("column", K, (H,)), ("row", H, (N,))], 1, 8, T)
+    A, B = [normal(K, 8, std=K ** -0.5), normal(H, 8, std=H ** -0.5)], [normal(8, H, std=8 ** -0.5), normal(8, N, std=8 ** -0.5)]
+    bits = lambda t: t.view(torch.int16).cpu().numpy().view(np.uint16)  # noqa: E731
+    pool.load_adapter(0, 8, 2.0, [[bits(a)] for a in A], [[bits(b)] for b in B])
+    X, W0, W1 = normal(T, K), normal(H, K, std=K ** -0.5), normal(N, H, std=H ** -0.5)
+    out = torch.full((T, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ids = (torch.arange(T, device="cuda") % 2 - 1).to(torch.int32)
+    pool.forward_mlp(bd.ACT_NONE, [0], 1, X, [bd.pack_weight(W0)], bd.pack_weight(W1), out, ids)
+    torch.cuda.synchronize()
+    for t in (0, 1, 15, 16, 4095, T - 17, T - 16, T - 2, T - 1):
+        y, a = X[t].double(), int(ids[t])
+        for i, w in enumerate((W0, W1)):
+            z = y @ w.double().t()
+            if a >= 0:
+                z = z + 2.0 * (y @ A[i].double()) @ B[i].double()
+            y = z.bfloat16().double() if i == 0 else z
         err = (out[t].double() - y).abs() / torch.maximum(y.abs(), y.square().mean().sqrt())
         assert float(err.max()) <= 1e-2, f"row {t}: {float(err.max())}"
     assert pool.device_error() == 0

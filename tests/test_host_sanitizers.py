@@ -37,3 +37,13 @@ def test_host_code_is_clean_under_asan_and_ubsan(tmp_path):
     r = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=300)
     assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-4000:])
     assert "0 failed checks" in r.stdout
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_activation_loads_stay_inside_x(tmp_path):
+    exe = str(tmp_path / "xaddr")
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "paper_2510_23346_amd", "csrc"),
+                        os.path.join(ROOT, "tests", "host_sanitize", "xaddr.cpp"), "-o", exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and " 0 bad" in r.stdout, r.stdout
