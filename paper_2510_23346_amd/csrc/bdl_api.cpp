@@ -51,6 +51,7 @@ struct Layout {
     long long xp_elems[bdl::kMaxProjs];
     long long dec_z_elems[bdl::kMaxProjs];   // decode path: Z lines
     long long dec_flags = 0;           // decode path: producer flags
+    long long dec_counts = 0;          // decode path: bound on the workgroups of a launch
     long long mlp_elems = 0;           // prefill MLP: gate and up outputs, fp32
     long long bigpart_elems = 0;       // large-tile GEMM: fp32 partials of split tiles
 };
@@ -129,7 +130,12 @@ int make_layout(const bdlora_proj_desc* projs, int n_projs, int max_slots, int m
         ws += L->dec_z_elems[p] * 2;
         L->dec_flags += (dec_t + dec_t / 16) * nbA;
     }
-    ws += L->dec_flags * 8;
+    // shrink workgroups (one at least per row group) and, rounded up to the
+    // XCDs, at most a main workgroup per 16 columns and row group
+    const long long groups = (std::min(max_tokens, bdl::kRowsMaxT) + bdl::kDecodeMaxT - 1) / bdl::kDecodeMaxT;
+    L->dec_counts = L->dec_flags + groups * 8;
+    for (int p = 0; p < n_projs; ++p) L->dec_counts += groups * (L->proj[p].N / 16);
+    ws += L->dec_flags * 8 + L->dec_counts * 4;
     int max_n = 0;                                  // widest single-slice column projection
     for (int p = 0; p < n_projs; ++p)
         if (L->proj[p].kind == BDLORA_COLUMN && L->proj[p].S == 1) max_n = std::max(max_n, L->proj[p].N);
@@ -190,6 +196,7 @@ struct bdlora_pool {
     uint16_t* d_Z[bdl::kMaxProjs] = {};
     uint16_t* d_decZ[bdl::kMaxProjs] = {};
     unsigned long long* d_flags = nullptr;
+    unsigned* d_count = nullptr;
     float* d_mlp = nullptr;
     float* d_bigpart = nullptr;
     // medium batches: the shrink runs on side_stream, forked from the
@@ -236,6 +243,7 @@ void free_pool(bdlora_pool* P) {
     for (auto z : P->d_Z) f(z);
     for (auto z : P->d_decZ) f(z);
     f(P->d_flags);
+    f(P->d_count);
     f(P->d_mlp);
     f(P->d_bigpart);
     for (auto x : P->d_Xp) f(x);
@@ -458,6 +466,7 @@ int bdlora_create_pool(const bdlora_proj_desc* projs, int32_t n_projs, int32_t m
     BDL_TRY(dev_alloc(&P->d_loaded, S, &tot));
     BDL_TRY(dev_alloc(&P->d_vid, MT, &tot));
     BDL_TRY(dev_alloc(&P->d_flags, L.dec_flags, &tot));
+    BDL_TRY(dev_alloc(&P->d_count, L.dec_counts, &tot));
     BDL_TRY(dev_alloc(&P->d_mlp, L.mlp_elems, &tot));
     if (L.bigpart_elems > 0) BDL_TRY(dev_alloc(&P->d_bigpart, L.bigpart_elems, &tot));
     BDL_TRY(dev_alloc(&P->d_perm, MT, &tot));
@@ -500,6 +509,7 @@ int bdlora_create_pool(const bdlora_proj_desc* projs, int32_t n_projs, int32_t m
     if (int r = hipz(P->d_err, 4)) return r;
     if (int r = hipz(P->d_meta, 16)) return r;
     if (int r = hipz(P->d_flags, (size_t)L.dec_flags * 8)) return r;
+    if (int r = hipz(P->d_count, (size_t)L.dec_counts * 4)) return r;
     // plan tables: entries past a batch's counts are never written by the
     // plan; zero (slot 0) rather than whatever the allocation held
     if (int r = hipz(P->d_gslot, (size_t)(S + 1) * 4)) return r;
@@ -850,6 +860,8 @@ static int forward_decode(bdlora_pool_t P, int n, const int32_t* projs, const vo
         for (int q = 1; q < n; ++q) da.shrink_base[q] = 1;        // its one workgroup only checks the ids
     da.wait_ticks = 20000;                                        // 200 us
     da.flags = P->d_flags;
+    da.count = P->d_count;
+    da.counts = (int)L.dec_counts;
     if ((long long)da.groups * da.n_shrink > L.dec_flags) return fail(BDLORA_ERR_SHAPE, "batch exceeds the pool workspace");
     da.pool = P->d_slabs;
     da.slot_stride = L.slot_stride;
@@ -1566,6 +1578,22 @@ int bdlora_profile_end(bdlora_pool_t P, float* ms, int32_t* n) {
 int bdlora_last_path(bdlora_pool_t P, int32_t* path) {
     if (!P || !path) return fail(BDLORA_ERR_INVALID_ARG, "null argument");
     *path = P->last_path;
+    return BDLORA_OK;
+}
+
+// For tests, outside the header: this pool's launch counts and flags (DecArgs).
+int bdlora_internal_launches(bdlora_pool_t P, uint32_t* count, int64_t max_count, int64_t* n_count, uint64_t* flags,
+                             int64_t max_flags, int64_t* n_flags) {
+    if (!P || !n_count || !n_flags) return fail(BDLORA_ERR_INVALID_ARG, "null argument");
+    *n_count = P->L.dec_counts;
+    *n_flags = P->L.dec_flags;
+    if (!count && !flags) return BDLORA_OK;
+    if (!count || !flags || max_count < *n_count || max_flags < *n_flags) return fail(BDLORA_ERR_INVALID_ARG, "short buffer");
+    DeviceGuard guard(P->device);
+    if (!guard.ok) return fail(BDLORA_ERR_HIP, "hipSetDevice failed");
+    BDL_HIP(hipDeviceSynchronize());
+    BDL_HIP(hipMemcpy(count, P->d_count, (size_t)*n_count * 4, hipMemcpyDeviceToHost));
+    BDL_HIP(hipMemcpy(flags, P->d_flags, (size_t)*n_flags * 8, hipMemcpyDeviceToHost));
     return BDLORA_OK;
 }
 

@@ -9,7 +9,7 @@
 //           bf16 once.  No partial sum leaves the CU.
 // A main workgroup streams its weights at once; only before the expand it
 // waits for its projection's shrink workgroups (flags in device memory, see
-// launch_tag).  Those are launched first and are usually done by then; a wait
+// raise_flag).  Those are launched first and are usually done by then; a wait
 // that runs past a time limit (other work can hold the CUs that they need)
 // ends with the workgroup computing that Z itself, so that no workgroup ever
 // depends on another one being scheduled.
@@ -17,34 +17,55 @@
 
 namespace bdl {
 
-// A producer workgroup raises its own 64-bit flag in device memory (a.flags)
-// once its stores have reached memory: the flag takes the launch's tag, which
-// no other launch has had (the dispatch packet's running number in its queue,
-// and the queue's address), so flags need no reset between launches.  (One
-// counter that all producers add to costs about 40 ns per addition.)  What a
+// A producer workgroup raises its own 64-bit flag in device memory once its
+// stores have reached memory: the flag takes the launch's tag.  (One counter
+// that all producers add to costs about 40 ns per addition.)  What a
 // producer writes for others is whole cache lines, written through; no cache
 // of a consumer can hold an older copy, since nothing reads that memory
 // earlier in the launch and a launch starts with its caches invalidated.
+//
+// The tag is the number of the launch among those on this pool's flags, so that
+// no flag needs a reset, also where a captured launch is replayed.  Every
+// workgroup keeps its own count of them (a.count): it reads its word, which
+// no other one touches in the launch, and at its end writes it back one higher,
+// with its share of the words that no workgroup of this launch has; so after
+// every launch all words agree.  (8B layer, one token: 15.9 us; 15.6 with the
+// packet's number in its queue and the queue's address for a tag, which repeat
+// where a new queue gets an old one's address; 24.6 with the id that HSA gives
+// each queue, which lies in host memory; 16.6 with one count for all, raised by
+// the last workgroup that has read it: a wave's later loads wait behind the
+// atomic operation's answer.)  The packet's number still stands beside the
+// count: it costs nothing, and tells launches apart where calls on one pool
+// overlapped against the rules.
 extern "C" __device__ unsigned long long bdl_dispatch_id() __asm("llvm.amdgcn.dispatch.id");
 
-__device__ __forceinline__ unsigned long long launch_tag() {
-    return ((unsigned long long)__builtin_amdgcn_queue_ptr() >> 12) << 40 | (bdl_dispatch_id() + 1);
+__device__ __forceinline__ unsigned launch_no(const DecArgs& a) { return a.count[blockIdx.x] + 1; }
+
+// one wave, once it has the number
+__device__ __forceinline__ void count_launch(const DecArgs& a, unsigned no) {
+    const int l = threadIdx.x & 63, s0 = gridDim.x + blockIdx.x * a.count_share;
+    if (l == 0) a.count[blockIdx.x] = no;
+    for (int i = s0 + l; i < min(s0 + a.count_share, a.counts); i += 64) a.count[i] = no;
+}
+
+__device__ __forceinline__ unsigned long long launch_tag(unsigned no) {
+    return (unsigned long long)no << 32 | (unsigned)bdl_dispatch_id();
 }
 
 // every wave of a producer: its stores have reached memory
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-__device__ __forceinline__ void raise_flag(const DecArgs& a, int i) {
-    __hip_atomic_store(a.flags + i, launch_tag(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void raise_flag(const DecArgs& a, int i, unsigned no) {
+    __hip_atomic_store(a.flags + i, launch_tag(no), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // one wave: wait for flags i0 .. i0 + n - 1; false when the time limit passed
-__device__ __forceinline__ bool wait_flags(const DecArgs& a, int i0, int n) {
+__device__ __forceinline__ bool wait_flags(const DecArgs& a, int i0, int n, unsigned no) {
     const int l = threadIdx.x & 63;
-    const unsigned long long tag = launch_tag(), t0 = __builtin_amdgcn_s_memrealtime();
+    const unsigned long long tag = launch_tag(no), t0 = __builtin_amdgcn_s_memrealtime();
     for (int i = 0; i < n;) {
-        const unsigned long long f =
-            __hip_atomic_load(a.flags + i0 + min(i + l, n - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long f = __hip_atomic_load(a.flags + i0 + min(i + l, n - 1), __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT);
         if (__all(f == tag)) {
             i += 64;
         } else {
@@ -436,6 +457,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
 
     if (bid < a.groups * a.n_shrink) {
         const int g = bid / a.n_shrink, sb = bid - g * a.n_shrink, t0 = g * a.rows, T = min(a.rows, a.T - t0);
+        const unsigned no = launch_no(a);
         const Plan pl = dec_plan(a, dec_plan_loads(a, t0, T), T);
         if (sb == 0 && pl.bad && threadIdx.x == 0) atomicOr(a.err, 1);
         int p = 0;
@@ -454,7 +476,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
                 dec_shrink<NW>(a, P, pl, ai, rb, c, P.X + (size_t)t0 * P.K, dec_z(a, P, g), T, lds);
             }
         }
-        if (threadIdx.x == 0) raise_flag(a, bid);
+        if (threadIdx.x == 0) raise_flag(a, bid, no);
+        if (w == 0) count_launch(a, no);
         return;
     }
 
@@ -462,7 +485,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     // close together, so that its L2 serves the weights to all but the first
     const int mb0 = bid - a.groups * a.n_shrink, per = 8 * a.groups, m8 = mb0 / per, in8 = mb0 - m8 * per;
     const int mbid = a.groups == 1 ? mb0 : m8 * 8 + (in8 & 7), g = a.groups == 1 ? 0 : in8 >> 3;
-    if (mbid >= a.n_main) return;
+    if (mbid >= a.n_main) {
+        if (w == 0) count_launch(a, launch_no(a));
+        return;
+    }
     const int t0 = g * a.rows, T = min(a.rows, a.T - t0);
     int p = 0;
     if constexpr (!PAIR) {
@@ -500,6 +526,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
 
     // wave 0 plans the batch (its loads go ahead of the weights')
     PlanLoads ld = PlanLoads{0, 0, -1};
+    unsigned no = 0;
     if (w == 0 && a.act_max > 0) ld = dec_plan_loads(a, t0, T);
     // Expand turn: 4 octets of the adapters in use (lane group lg takes
     // octet lg; tokens of other adapters see zeros, which cost no traffic:
@@ -540,6 +567,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
             for (int i = 0; i < 3; ++i) acc[rb][cb] = mfma(b, z.z[rb][i], acc[rb][cb]);
     };
     auto pre = [&]() __attribute__((always_inline)) {
+        if (w == 0) no = launch_no(a);
         if (w == 0 && a.act_max > 0) {
             const Plan pl = dec_plan(a, ld, T);
             s_vid[l] = pl.vid;
@@ -584,7 +612,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         if (w == 0) {
             // (the two projections of a pair have their shrink workgroups side by side)
             const int i0 = a.shrink_base[p], i1 = p + (PAIR ? 2 : 1) < a.n_proj ? a.shrink_base[p + (PAIR ? 2 : 1)] : a.n_shrink;
-            const bool ok = wait_flags(a, g * a.n_shrink + i0, i1 - i0);
+            const bool ok = wait_flags(a, g * a.n_shrink + i0, i1 - i0, no);
             if (l == 0) s_info[1] = ok;
         }
         __syncthreads();
@@ -638,6 +666,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
             }
         }
     }
+    if (w == 0) count_launch(a, no);
     // the K-parts meet: fragment (w, rb, cb) in lane order, added in part order
     __syncthreads();                                  // every wave is past its X buffer, which red overlays
 #pragma unroll
@@ -668,12 +697,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
 }
 
 template <int MB, int NW>
-static hipError_t launch_mb(const DecArgs& a, bool q4, hipStream_t s) {
+static hipError_t launch_mb(DecArgs& a, bool q4, hipStream_t s) {
     // column blocks of a wave in different slices
     bool zs = false;
     for (int i = 0; i < a.n_proj; ++i)
         for (int q = 1; q < a.p[i].n_slices; ++q) zs = zs || a.p[i].slice_col[q] % (16 * kDecNB) != 0;
     const dim3 grid(a.groups * (a.n_shrink + (a.groups == 1 ? a.n_main : (a.n_main + 7) / 8 * 8)));
+    if ((long long)grid.x > a.counts) return hipErrorInvalidValue;
+    a.count_share = (a.counts - (int)grid.x + (int)grid.x - 1) / (int)grid.x;
 #define BDL_DEC_CASE(Q, R, Z) hipLaunchKernelGGL((dec_main_kernel<NW, MB, kDecNB, Q, R, Z>), grid, dim3(64 * NW), 0, s, a)
     if (a.pair) {
         if (q4) BDL_DEC_CASE(true, true, true); else BDL_DEC_CASE(false, true, true);
@@ -686,9 +717,9 @@ static hipError_t launch_mb(const DecArgs& a, bool q4, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_dec_main(const DecArgs& a, int mb, hipStream_t s) {
+hipError_t launch_dec_main(DecArgs& a, int mb, hipStream_t s) {
     if (a.n_main <= 0 || a.n_shrink < 1 || a.T < 1 || a.rows > mb * 16 || a.rows > kDecodeMaxT ||
-        a.groups != (a.T + a.rows - 1) / a.rows || !a.flags) return hipErrorInvalidValue;
+        a.groups != (a.T + a.rows - 1) / a.rows || !a.flags || !a.count) return hipErrorInvalidValue;
     bool q4 = false;
     for (int i = 0; i < a.n_proj; ++i) {
         q4 = q4 || a.p[i].Ws != nullptr;

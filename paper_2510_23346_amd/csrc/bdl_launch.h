@@ -171,6 +171,9 @@ struct DecArgs {
     int pair;                 // gated MLP: projections 0 and 1 share the tiles of 0, H = silu(0) * 1
     unsigned wait_ticks;      // longest wait for a producer (100 MHz ticks), then its work is done here
     unsigned long long* flags;   // [groups][n_shrink] launch tags (bdl_decode.hip, launch_tag)
+    unsigned* count;          // [counts] launches on these flags so far, a word per workgroup (counts: at
+    int counts;               // least the workgroups of any launch on them)
+    int count_share;          // words past the launch's workgroups per workgroup (set by launch_dec_main)
     const int* ids;           // [T] per-token slot ids, or null: the segments below
     const int* loaded;        // [max_slots] nonzero: the slot holds an adapter
     const int* r8;            // [max_slots] padded rank of each slot
@@ -187,7 +190,7 @@ struct DecArgs {
 static_assert(sizeof(DecArgs) <= 4096, "kernel arguments");
 
 // Host-side launchers (bdl_kernels.hip, bdl_prep.hip, bdl_decode.hip).
-hipError_t launch_dec_main(const DecArgs& a, int mb, hipStream_t s);
+hipError_t launch_dec_main(DecArgs& a, int mb, hipStream_t s);
 hipError_t launch_prep(const PrepArgs& a, hipStream_t s);
 hipError_t launch_shrink(const FwdArgs& a, int mb, int nb, hipStream_t s);
 // column blocks of the shrink's chunks for a projection of cols = n_slices * r8max columns (shape mb x nb)

@@ -7,8 +7,7 @@
 
 namespace bdl {
 
-hipError_t launch_dec_main(const DecArgs&, int, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_dec_epi(const DecArgs&, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_dec_main(DecArgs&, int, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_prep(const PrepArgs&, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_shrink(const FwdArgs&, int, int, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_gemm(const FwdArgs&, int, int, hipStream_t) { return hipErrorNotSupported; }

@@ -13,6 +13,8 @@ Tolerance: the sums are fp32 and the output is rounded once to bf16, half a
 unit in the last place, 2^-9 of the value; 2^-8 of max(value, rms) leaves the
 same again for the fp32 sums and the exact split of Z.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -53,15 +55,82 @@ def test_decode_tile_edges(torch_cuda, T, ids_kind):
     load_adapters(pool, spec, range(len(ranks)), cache=layer.adapters)
     dl = DeviceLayer(layer)
     refs = bdlora.layer_forward(layer)
-    for rep in range(3):                     # (the later calls find the first one's Z and flags)
+    # the same tokens in another order: the later calls find another call's Z and flags
+    for rep, order in enumerate((np.arange(T), rng.permutation(T), np.arange(T)[::-1].copy())):
+        at = torch.from_numpy(order).cuda()
         for o in dl.out:
             o.fill_(float("nan"))
-        pool.forward_layer([0, 1, 2], dl.X, dl.W, dl.out, dl.ids)
+        pool.forward_layer([0, 1, 2], [x[at].contiguous() for x in dl.X], dl.W, dl.out, dl.ids[at].contiguous())
         torch.cuda.synchronize()
         for p, y in enumerate(dl.outputs()):
-            e = bdlora.rel_errors(y, refs[p])
+            e = bdlora.rel_errors(y, refs[p][order])
             assert e["pointwise"] <= TOL, f"T={T} {ids_kind} call {rep} {spec.projs[p].name}: {e}"
     assert pool.last_path() == "decode" and pool.device_error() == 0
+    pool.close()
+
+
+def _launches(bd, pool):
+    """The pool's launch counts and flags."""
+    f = bd.lib().bdlora_internal_launches
+    f.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.POINTER(ctypes.c_int64), ctypes.c_void_p,
+                  ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)]
+    nc, nf = ctypes.c_int64(), ctypes.c_int64()
+    assert f(pool.handle, None, 0, ctypes.byref(nc), None, 0, ctypes.byref(nf)) == 0
+    count, flags = np.zeros(nc.value, np.uint32), np.zeros(nf.value, np.uint64)
+    assert f(pool.handle, count.ctypes.data, nc.value, ctypes.byref(nc), flags.ctypes.data, nf.value, ctypes.byref(nf)) == 0
+    return count, flags
+
+
+def test_every_launch_has_a_number_of_its_own(torch_cuda):
+    # eager calls of several sizes, row groups, the MLP and replays of a graph,
+    # on streams made and destroyed in between: after each launch all
+    # workgroups' counts agree, one higher than before, also those that the
+    # launch has no workgroup for; and the flags that it raised carry its
+    # number, so that none of an earlier launch can be taken for one of its own
+    torch = torch_cuda
+    import paper_2510_23346_amd as bd
+    projs = [wl.ProjSpec("gate", "column", 640, (384,)), wl.ProjSpec("up", "column", 640, (384,)),
+             wl.ProjSpec("down", "row", 384, (192,))]
+    T, ranks = 200, [8, 32, 16]
+    ids = np.random.default_rng(1).integers(0, 3, size=T)
+    spec = wl.custom_workload("launch-no", projs, T, ranks, ids=ids, seed=5)
+    layer = wl.draw_layer(spec, slots=range(3))
+    pool = make_pool(spec)
+    load_adapters(pool, spec, range(3), cache=layer.adapters)
+    dl = DeviceLayer(layer)
+    hip = ctypes.CDLL("libamdhip64.so")
+
+    def layer_call(t, s=None):
+        pool.forward_layer([0, 1, 2], [x[:t] for x in dl.X], dl.W, [o[:t] for o in dl.out], dl.ids[:t], stream=s)
+
+    def mlp_call(t, s=None):
+        pool.forward_mlp(bd.ACT_SILU_MUL, [0, 1], 2, dl.X[0][:t], dl.W[:2], dl.W[2], dl.out[2][:t], dl.ids[:t], stream=s)
+    layer_call(1)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            layer_call(64)
+    calls = [(1, lambda s: layer_call(1, s)), (1, lambda s: layer_call(16, s)), (2, lambda s: mlp_call(33, s)),
+             (1, lambda s: layer_call(200, s)), (1, lambda s: layer_call(5, s)), (2, lambda s: mlp_call(130, s))]
+    n, seen = 1, set()
+    for rep in range(3):
+        for k, call in calls + [(1, None)]:
+            if call is None:
+                g.replay()
+            else:
+                s = ctypes.c_void_p()
+                assert hip.hipStreamCreateWithFlags(ctypes.byref(s), 1) == 0
+                call(s.value)
+                assert hip.hipStreamSynchronize(s) == 0 and hip.hipStreamDestroy(s) == 0
+            torch.cuda.synchronize()
+            n += k
+            count, flags = _launches(bd, pool)
+            assert count.min() == count.max() == n
+            mine = set(flags[(flags >> np.uint64(32)) == n].tolist())
+            assert len(mine) == 1 and not mine & seen, f"flags of launch {n}"
+            seen |= mine
+    assert pool.device_error() == 0
     pool.close()
 
 
