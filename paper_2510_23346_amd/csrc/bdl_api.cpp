@@ -214,6 +214,7 @@ struct bdlora_pool {
     int prof_left = 0;
     int prof_used = 0;
     int last_path = 0;        // BDLORA_PATH_* of the last forward
+    unsigned wait_ticks = 20000;          // decode launch: DecArgs::wait_ticks (200 us)
     hipError_t static_err = hipSuccess;   // taking the static scratch's address at creation
     std::vector<hipEvent_t> prof_ev;      // kProfEvents per recorded call
 };
@@ -858,7 +859,7 @@ static int forward_decode(bdlora_pool_t P, int n, const int32_t* projs, const vo
     da.n_main = tiles;
     if (shrinks == 0)
         for (int q = 1; q < n; ++q) da.shrink_base[q] = 1;        // its one workgroup only checks the ids
-    da.wait_ticks = 20000;                                        // 200 us
+    da.wait_ticks = P->wait_ticks;
     da.flags = P->d_flags;
     da.count = P->d_count;
     da.counts = (int)L.dec_counts;
@@ -1581,7 +1582,15 @@ int bdlora_last_path(bdlora_pool_t P, int32_t* path) {
     return BDLORA_OK;
 }
 
-// For tests, outside the header: this pool's launch counts and flags (DecArgs).
+// For tests, outside the header: the longest wait of this pool's decode
+// launches for their shrink workgroups (100 MHz ticks; 0: every main workgroup
+// computes what it waits for), and the launch counts and flags (DecArgs).
+int bdlora_internal_set_wait(bdlora_pool_t P, uint32_t ticks) {
+    if (!P) return fail(BDLORA_ERR_INVALID_ARG, "null pool");
+    P->wait_ticks = ticks;
+    return BDLORA_OK;
+}
+
 int bdlora_internal_launches(bdlora_pool_t P, uint32_t* count, int64_t max_count, int64_t* n_count, uint64_t* flags,
                              int64_t max_flags, int64_t* n_flags) {
     if (!P || !n_count || !n_flags) return fail(BDLORA_ERR_INVALID_ARG, "null argument");

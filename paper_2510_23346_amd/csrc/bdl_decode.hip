@@ -61,6 +61,7 @@ __device__ __forceinline__ void raise_flag(const DecArgs& a, int i, unsigned no)
 
 // one wave: wait for flags i0 .. i0 + n - 1; false when the time limit passed
 __device__ __forceinline__ bool wait_flags(const DecArgs& a, int i0, int n, unsigned no) {
+    if (a.wait_ticks == 0) return false;
     const int l = threadIdx.x & 63;
     const unsigned long long tag = launch_tag(no), t0 = __builtin_amdgcn_s_memrealtime();
     for (int i = 0; i < n;) {

@@ -169,7 +169,7 @@ struct DecArgs {
     int max_slots;
     int r8max;
     int pair;                 // gated MLP: projections 0 and 1 share the tiles of 0, H = silu(0) * 1
-    unsigned wait_ticks;      // longest wait for a producer (100 MHz ticks), then its work is done here
+    unsigned wait_ticks;      // longest wait for a producer (100 MHz ticks; 0: none), then its work is done here
     unsigned long long* flags;   // [groups][n_shrink] launch tags (bdl_decode.hip, launch_tag)
     unsigned* count;          // [counts] launches on these flags so far, a word per workgroup (counts: at
     int counts;               // least the workgroups of any launch on them)

@@ -134,6 +134,59 @@ def test_every_launch_has_a_number_of_its_own(torch_cuda):
     pool.close()
 
 
+@pytest.mark.parametrize("fmt", ["bf16", "int4_g128"])
+@pytest.mark.parametrize("T", [1, 17, 33, 64, 150])
+def test_a_wait_that_gives_up(torch_cuda, T, fmt):
+    # with no time to wait, every main workgroup computes what its shrink
+    # workgroups do (and writes it beside them): the same bits.  A layer of
+    # projections with one and several slices, the gated MLP, the static
+    # scratch, row groups.
+    torch = torch_cuda
+    import paper_2510_23346_amd as bd
+    projs = [wl.ProjSpec("gate", "column", 640, (384,)), wl.ProjSpec("up", "column", 640, (384,)),
+             wl.ProjSpec("down", "row", 384, (192,)), wl.ProjSpec("qkv", "column", 256, (16, 48, 16, 48))]
+    ranks = [8, 128, 0, 24, 16, 5]
+    ids = np.random.default_rng(T).integers(-1, len(ranks), size=T)
+    spec = wl.custom_workload(f"gives-up-{T}", projs, T, ranks, ids=ids, seed=90 + T, weight_format=fmt)
+    layer = wl.draw_layer(spec, slots=range(len(ranks)))
+    pool = make_pool(spec)
+    load_adapters(pool, spec, range(len(ranks)), cache=layer.adapters)
+    dl = DeviceLayer(layer)
+    set_wait = bd.lib().bdlora_internal_set_wait
+    set_wait.argtypes = [ctypes.c_void_p, ctypes.c_uint32]
+
+    def results(at):
+        X, i = [x[at].contiguous() for x in dl.X], dl.ids[at].contiguous()
+        got = []
+        for call in (pool.forward_layer, pool.forward_layer_static) if T <= bd.DECODE_MAX_T else (pool.forward_layer,):
+            for o in dl.out:
+                o.fill_(float("nan"))
+            call([0, 1, 2, 3], X, dl.W, dl.out, i)
+            torch.cuda.synchronize()
+            got += [y.view(np.uint32).copy() for y in dl.outputs()]
+        dl.out[2].fill_(float("nan"))
+        pool.forward_mlp(bd.ACT_SILU_MUL, [0, 1], 2, X[0], dl.W[:2], dl.W[2], dl.out[2], i)
+        torch.cuda.synchronize()
+        return got + [dl.outputs()[2].view(np.uint32).copy()]
+    rng = np.random.default_rng(2)
+    for rep in range(3):
+        at = torch.from_numpy(rng.permutation(T)).cuda()
+        want = results(at)
+        other = results(torch.flip(at, [0]))               # another call's Z and flags in between
+        assert set_wait(pool.handle, 0) == 0
+        got = results(at)
+        assert set_wait(pool.handle, 20000) == 0
+        assert len(got) == len(want) == len(other)
+        for k, (a, b) in enumerate(zip(got, want)):
+            assert np.array_equal(a, b), f"T={T} {fmt} call {rep} output {k}"
+    refs = (quant.layer_forward_w4 if fmt != "bf16" else bdlora.layer_forward)(layer)
+    for p in range(4):
+        e = bdlora.rel_errors(got[p].view(np.float32), refs[p][at.cpu().numpy()])
+        assert e["pointwise"] <= TOL, f"T={T} {fmt} {projs[p].name}: {e}"
+    assert pool.device_error() == 0
+    pool.close()
+
+
 @pytest.mark.parametrize("T", [5, 30, 64, 130])
 def test_decode_int4_and_bf16_projections_in_one_call(torch_cuda, T):
     # one launch over an INT4 and a bf16 projection, and the gated MLP with
