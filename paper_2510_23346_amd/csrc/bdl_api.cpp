@@ -755,6 +755,13 @@ static int loaded_adapters(bdlora_pool_t P) {
     return n;
 }
 
+// the largest padded rank among them
+static int loaded_rank8(bdlora_pool_t P) {
+    int r = 0;
+    for (int v : P->h_r8) r = std::max(r, v);
+    return r;
+}
+
 // Row groups of a batch in the decode launch: the fewest, of nearly equal size.
 static int dec_groups(int T) { return (T + bdl::kDecodeMaxT - 1) / bdl::kDecodeMaxT; }
 
@@ -827,8 +834,9 @@ static int forward_decode(bdlora_pool_t P, int n, const int32_t* projs, const vo
     for (int i = 0; i < n; ++i) order[i] = i;
     if (!da.pair)
         std::stable_sort(order, order + n, [&](int x, int y) { return L.proj[projs[x]].K > L.proj[projs[y]].K; });
-    const int waves = bdl::dec_waves((da.rows + 15) / 16);
-    int tiles = 0, shrinks = 0;
+    const int waves = bdl::dec_waves((da.rows + 15) / 16), n_loaded = loaded_adapters(P), rank8 = loaded_rank8(P);
+    int tiles = 0, shrinks = 0, blocksA = 0;
+    for (int q = 0; q < n; ++q) blocksA += (L.proj[projs[q]].S * L.r8max + 15) / 16;
     for (int q = 0; q < n; ++q) {
         const int i = order[q];
         const ProjInfo& pi = L.proj[projs[i]];
@@ -846,8 +854,22 @@ static int forward_decode(bdlora_pool_t P, int n, const int32_t* projs, const vo
         d.b_off = pi.b_off;
         d.nbA = (pi.S * L.r8max + 15) / 16;
         da.shrink_base[q] = shrinks;
-        // (adapter, 16 tokens) items: sum of ceil(tokens / 16) over the adapters in use
-        shrinks += (da.act_max > 0 ? da.act_max + (da.rows - 1) / 16 : 0) * d.nbA;
+        // (adapter, 16 tokens) items, sum of ceil(tokens / 16) over the adapters
+        // in use, times blocks of A^T: a workgroup for each that the adapters
+        // loaded now can make.  Replays after larger or more adapters were
+        // loaded may have more, which the workgroups then take in turns; two
+        // per CU, as far as the pool's sizes can make as many, bound the turns.
+        // (By the pool's sizes alone an 8B layer of 256 tokens with one adapter
+        // of rank 8, in a pool of 64 slots of rank 128, launched 15000 of them:
+        // 102.6 us against 50.4; 37 tokens over adapters of ranks 8 and 64: 33
+        // against 30)
+        d.n_shrink = 1;
+        if (da.act_max > 0) {
+            const int more = (da.rows - 1) / 16, share = (2 * P->n_cu * d.nbA + da.groups * blocksA - 1) / (da.groups * blocksA);
+            const int now = (std::min(da.rows, n_loaded) + more) * ((pi.S * rank8 + 15) / 16);
+            d.n_shrink = std::min((da.act_max + more) * d.nbA, std::max(now, share));
+            shrinks += d.n_shrink;
+        }
         const int KS = pi.K / 32;
         // about 16 k-steps per part, as far as the workgroup's waves go
         d.kparts = std::min(waves, KS >= 64 ? 8 : KS >= 32 ? 4 : KS >= 16 ? 2 : 1);

@@ -59,9 +59,9 @@ __device__ __forceinline__ void raise_flag(const DecArgs& a, int i, unsigned no)
     __hip_atomic_store(a.flags + i, launch_tag(no), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// one wave: wait for flags i0 .. i0 + n - 1; false when the time limit passed
-__device__ __forceinline__ bool wait_flags(const DecArgs& a, int i0, int n, unsigned no) {
-    if (a.wait_ticks == 0) return false;
+// one wave: wait for flags i0 .. i0 + n - 1; false when the time limit, ticks, passed
+__device__ __forceinline__ bool wait_flags(const DecArgs& a, int i0, int n, unsigned no, unsigned long long ticks) {
+    if (ticks == 0) return false;
     const int l = threadIdx.x & 63;
     const unsigned long long tag = launch_tag(no), t0 = __builtin_amdgcn_s_memrealtime();
     for (int i = 0; i < n;) {
@@ -70,7 +70,7 @@ __device__ __forceinline__ bool wait_flags(const DecArgs& a, int i0, int n, unsi
         if (__all(f == tag)) {
             i += 64;
         } else {
-            if (__builtin_amdgcn_s_memrealtime() - t0 > a.wait_ticks) return false;
+            if (__builtin_amdgcn_s_memrealtime() - t0 > ticks) return false;
             __builtin_amdgcn_s_sleep(1);
         }
     }
@@ -466,16 +466,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         for (int q = 1; q < kMaxProjs; ++q)
             if (q < a.n_proj && sb >= a.shrink_base[q]) p = q;
         const DecProj& P = a.p[p];
-        const int idx = sb - a.shrink_base[p], item = idx / P.nbA, c = idx - item * P.nbA;
-        // items are numbered group after group
-        const int nit = dec_items(pl, s_cnt[w]), incl = wave_incl_scan(nit);
-        const unsigned long long after = __ballot(incl > item);
-        if (after) {
-            const int ai = __ffsll((long long)after) - 1;
-            const int rb = item - (__builtin_amdgcn_readlane(incl, ai) - __builtin_amdgcn_readlane(nit, ai));
-            if (c * 16 < P.n_slices * __builtin_amdgcn_readlane(pl.gr, ai)) {
-                dec_shrink<NW>(a, P, pl, ai, rb, c, P.X + (size_t)t0 * P.K, dec_z(a, P, g), T, lds);
-            }
+        // what there is to do, adapter after adapter: its items (16 tokens) times
+        // its blocks of A^T.  Mostly one each; the host counts the workgroups by
+        // the adapters that it knows
+        const int nb = (P.n_slices * pl.gr + 15) >> 4, units = dec_items(pl, s_cnt[w]) * nb, incl = wave_incl_scan(units);
+        for (int u = sb - a.shrink_base[p]; u < wave_total(incl); u += P.n_shrink) {
+            const int ai = __ffsll((long long)__ballot(incl > u)) - 1, nba = __builtin_amdgcn_readlane(nb, ai);
+            const int k = u - (__builtin_amdgcn_readlane(incl, ai) - __builtin_amdgcn_readlane(units, ai)), rb = k / nba;
+            dec_shrink<NW>(a, P, pl, ai, rb, k - rb * nba, P.X + (size_t)t0 * P.K, dec_z(a, P, g), T, lds);
         }
         if (threadIdx.x == 0) raise_flag(a, bid, no);
         if (w == 0) count_launch(a, no);
@@ -613,7 +611,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         if (w == 0) {
             // (the two projections of a pair have their shrink workgroups side by side)
             const int i0 = a.shrink_base[p], i1 = p + (PAIR ? 2 : 1) < a.n_proj ? a.shrink_base[p + (PAIR ? 2 : 1)] : a.n_shrink;
-            const bool ok = wait_flags(a, g * a.n_shrink + i0, i1 - i0, no);
+            // (a limit for each of the turns that the shrink workgroups take: adapters
+            // in use have s_info[0] octets of ranks, S / 2 blocks of A^T each)
+            const bool ok = wait_flags(a, g * a.n_shrink + i0, i1 - i0, no,
+                                       (unsigned long long)a.wait_ticks * (1 + P.n_slices * s_info[0] / (2 * P.n_shrink)));
             if (l == 0) s_info[1] = ok;
         }
         __syncthreads();

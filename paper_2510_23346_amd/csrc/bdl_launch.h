@@ -151,7 +151,8 @@ struct DecProj {
     int slice_col[kMaxSlices + 1];
     long long a_off, b_off;
     int nbA;                  // A^T_cat blocks of an adapter of the pool's largest rank
-    int kparts;               // parts of K per column group of a main workgroup (1, 2 or 4)
+    int n_shrink;             // shrink workgroups (of each row group; at least one)
+    int kparts;               // parts of K per column group of a main workgroup (1, 2, 4 or 8)
 };
 
 struct DecArgs {
@@ -169,7 +170,7 @@ struct DecArgs {
     int max_slots;
     int r8max;
     int pair;                 // gated MLP: projections 0 and 1 share the tiles of 0, H = silu(0) * 1
-    unsigned wait_ticks;      // longest wait for a producer (100 MHz ticks; 0: none), then its work is done here
+    unsigned wait_ticks;      // longest wait for a producer (100 MHz ticks a turn; 0: none), then its work is done here
     unsigned long long* flags;   // [groups][n_shrink] launch tags (bdl_decode.hip, launch_tag)
     unsigned* count;          // [counts] launches on these flags so far, a word per workgroup (counts: at
     int counts;               // least the workgroups of any launch on them)

@@ -475,3 +475,42 @@ def test_int4_sums_are_as_exact_as_the_64_row_kernel(torch_cuda, T, N, path, mea
     assert rms[TB] > 0
     assert rms[T] <= rms[TB], f"rounding {rms[T]:.3e}, 64-row kernel {rms[TB]:.3e}"
     pool.close()
+
+
+@pytest.mark.parametrize("T", [60, 100, 250])
+def test_replay_with_more_to_shrink_than_at_capture(torch_cuda, T):
+    # the launch counts its shrink workgroups by the adapters loaded when it is
+    # captured: adapters of rank 128 in every slot afterwards make several
+    # times as many units, which they take in turns
+    torch = torch_cuda
+    n, few = 48, 60 if T <= 64 else 1
+    n = max(n, few)
+    ranks = [128 if s else 120 for s in range(n)]
+    projs = [wl.ProjSpec("qkv", "column", 160, (32, 32, 32, 32)), wl.ProjSpec("o", "row", 96, (144,)),
+             wl.ProjSpec("up", "column", 160, (64,))]
+    ids = np.random.default_rng(T).integers(-1, n, size=T)
+    spec = wl.custom_workload(f"more-{T}", projs, T, ranks, ids=ids, seed=T)
+    layer = wl.draw_layer(spec, slots=range(n))
+    pool = make_pool(spec)
+    zero = lambda r: ([[np.zeros((p.d_in, r), np.uint16) for _ in p.slices] for p in projs],  # noqa: E731
+                      [[np.zeros((r, o), np.uint16) for o in p.slices] for p in projs])
+    for s in range(few):
+        pool.load_adapter(s, 8, 1.0, *zero(8))
+    dl = DeviceLayer(layer)
+    with torch.cuda.stream(torch.cuda.Stream()):
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            pool.forward_layer([0, 1, 2], dl.X, dl.W, dl.out, dl.ids)
+    load_adapters(pool, spec, range(n), cache=layer.adapters)
+    refs = bdlora.layer_forward(layer)
+    for rep in range(3):
+        for o in dl.out:
+            o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        for p, y in enumerate(dl.outputs()):
+            e = bdlora.rel_errors(y, refs[p])
+            assert e["pointwise"] <= TOL, f"T={T} replay {rep} {projs[p].name}: {e}"
+    assert pool.device_error() == 0
+    pool.close()
