@@ -835,8 +835,17 @@ static int forward_decode(bdlora_pool_t P, int n, const int32_t* projs, const vo
     if (!da.pair)
         std::stable_sort(order, order + n, [&](int x, int y) { return L.proj[projs[x]].K > L.proj[projs[y]].K; });
     const int waves = bdl::dec_waves((da.rows + 15) / 16), n_loaded = loaded_adapters(P), rank8 = loaded_rank8(P);
-    int tiles = 0, shrinks = 0, blocksA = 0;
-    for (int q = 0; q < n; ++q) blocksA += (L.proj[projs[q]].S * L.r8max + 15) / 16;
+    int tiles = 0, shrinks = 0, blocksA = 0, units = 0;
+    const int turns = std::min(da.rows, n_loaded) * rank8 / 32;
+    const int more = (da.rows - 1) / 16, items = std::min(da.rows, n_loaded) + more;
+    for (int q = 0; q < n; ++q) {
+        blocksA += (L.proj[projs[q]].S * L.r8max + 15) / 16;
+        units += da.groups * items * ((L.proj[projs[q]].S * rank8 + 15) / 16);
+    }
+    // more shrink workgroups of one block of A^T than are resident at once
+    // (1B layer, 64 tokens, 128 adapters of rank 64: 110 -> 94 us; 16 tokens, 16
+    // such adapters: 39.6 -> 32.1)
+    da.merge = units > P->n_cu * (waves == 8 ? 1 : 2);
     for (int q = 0; q < n; ++q) {
         const int i = order[q];
         const ProjInfo& pi = L.proj[projs[i]];
@@ -861,18 +870,20 @@ static int forward_decode(bdlora_pool_t P, int n, const int32_t* projs, const vo
         // per CU, as far as the pool's sizes can make as many, bound the turns.
         // (By the pool's sizes alone an 8B layer of 256 tokens with one adapter
         // of rank 8, in a pool of 64 slots of rank 128, launched 15000 of them:
-        // 102.6 us against 50.4; 37 tokens over adapters of ranks 8 and 64: 33
-        // against 30)
+        // 102.6 us against 50.4)
         d.n_shrink = 1;
         if (da.act_max > 0) {
-            const int more = (da.rows - 1) / 16, share = (2 * P->n_cu * d.nbA + da.groups * blocksA - 1) / (da.groups * blocksA);
-            const int now = (std::min(da.rows, n_loaded) + more) * ((pi.S * rank8 + 15) / 16);
-            d.n_shrink = std::min((da.act_max + more) * d.nbA, std::max(now, share));
+            const int share = (2 * P->n_cu * d.nbA + da.groups * blocksA - 1) / (da.groups * blocksA);
+            const int now = (pi.S * rank8 + 15) / 16, per = da.merge ? 4 : 1;
+            d.n_shrink = std::min((da.act_max + more) * ((d.nbA + per - 1) / per), std::max(items * ((now + per - 1) / per), share));
             shrinks += d.n_shrink;
         }
         const int KS = pi.K / 32;
         // about 16 k-steps per part, as far as the workgroup's waves go
-        d.kparts = std::min(waves, KS >= 64 ? 8 : KS >= 32 ? 4 : KS >= 16 ? 2 : 1);
+        // (a short K is split further for the expand's sake, whose turns, 4 octets
+        // of the adapters' ranks each, the parts share: 1B layer, whose o has 8
+        // k-steps, 64 tokens, 64 adapters of rank 64: 81 -> 53 us)
+        d.kparts = std::min(waves, KS >= 64 || turns >= 16 ? 8 : KS >= 32 ? 4 : KS >= 16 ? 2 : 1);
         const int blocks = waves / d.kparts * (da.pair ? 1 : bdl::kDecNB);
         da.tile_base[q] = tiles;
         if (!(da.pair && q == 1)) tiles += (pi.N / 16 + blocks - 1) / blocks;

@@ -59,9 +59,10 @@ __device__ __forceinline__ void raise_flag(const DecArgs& a, int i, unsigned no)
     __hip_atomic_store(a.flags + i, launch_tag(no), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// one wave: wait for flags i0 .. i0 + n - 1; false when the time limit, ticks, passed
-__device__ __forceinline__ bool wait_flags(const DecArgs& a, int i0, int n, unsigned no, unsigned long long ticks) {
-    if (ticks == 0) return false;
+// one wave: wait for flags i0 .. i0 + n - 1, whose workgroups have about `units`
+// to do per `share` of them; false when the time limit for that passed
+__device__ __forceinline__ bool wait_flags(const DecArgs& a, int i0, int n, unsigned no, int units, int share) {
+    if (a.wait_ticks == 0) return false;
     const int l = threadIdx.x & 63;
     const unsigned long long tag = launch_tag(no), t0 = __builtin_amdgcn_s_memrealtime();
     for (int i = 0; i < n;) {
@@ -70,7 +71,7 @@ __device__ __forceinline__ bool wait_flags(const DecArgs& a, int i0, int n, unsi
         if (__all(f == tag)) {
             i += 64;
         } else {
-            if (__builtin_amdgcn_s_memrealtime() - t0 > ticks) return false;
+            if ((__builtin_amdgcn_s_memrealtime() - t0) * share > (unsigned long long)a.wait_ticks * (share + units)) return false;
             __builtin_amdgcn_s_sleep(1);
         }
     }
@@ -206,17 +207,21 @@ __device__ __forceinline__ uint16_t* dec_z(const DecArgs& a, const DecProj& P, i
     return P.Z + (size_t)g * P.nbA * a.rows * kDecZLine;
 }
 
-// Z of row block c of A^T for 16 tokens (row block rb) of group ai, stored as
-// one 128-byte line per (c, token): three planes of 16 bf16 numbers.  The
-// workgroup's waves split K, a wave's operand loads (kShrinkChunk pairs of
-// k-steps) are in flight together; the tokens are the MFMA's columns.
-constexpr int kShrinkChunk = 8;
+// Z of row blocks c0 .. c0 + nb - 1 (nb <= NBA) of A^T for 16 tokens (row block
+// rb) of group ai, stored as one 128-byte line per (block, token): three planes
+// of 16 bf16 numbers.  The workgroup's waves split K; a wave's loads run
+// through a ring of D pairs of k-steps; the tokens are the MFMA's columns.
+// One block a workgroup gives the shortest launch while the workgroups are
+// resident at once, four read X once for all and are a fourth as many (see
+// DecArgs::merge).
+constexpr int kShrinkMerge = 4;
 
-template <int NW>
-__device__ __forceinline__ void dec_shrink(const DecArgs& a, const DecProj& P, const Plan& pl, int ai, int rb, int c,
-                                           const uint16_t* X, uint16_t* Z, int T, u32x4* lds) {
+template <int NW, int NBA>
+__device__ __forceinline__ void dec_shrink(const DecArgs& a, const DecProj& P, const Plan& pl, int ai, int rb, int c0,
+                                           int nb, const uint16_t* X, uint16_t* Z, int T, u32x4* lds) {
+    constexpr int D = NBA == 1 ? 8 : 4;
     const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lg = l >> 4;
-    const int r8s = __builtin_amdgcn_readlane(pl.gr, ai), slot = __builtin_amdgcn_readlane(pl.gs, ai);
+    const int slot = __builtin_amdgcn_readlane(pl.gs, ai);
     const float sc = a.scale[slot];
     // the adapter's tokens in ascending order: lane i gets the i-th
     const unsigned long long m = __ballot(pl.mine == ai), lt = (1ull << l) - 1ull;
@@ -225,44 +230,65 @@ __device__ __forceinline__ void dec_shrink(const DecArgs& a, const DecProj& P, c
     const int t = __shfl(toks, min(rb * 16 + lr, cnt - 1));      // the token of this lane's MFMA column
 
     const int KS = P.K >> 5, NP = (KS + 1) >> 1, g0 = NP * w / NW, n = NP * (w + 1) / NW - g0;
-    const __amdgpu_buffer_rsrc_t ra =
-        buf_rsrc(a.pool + (size_t)slot * a.slot_stride + P.a_off + frag_index(c, 0, KS), KS * 1024u);
+    __amdgpu_buffer_rsrc_t ra[NBA];                               // (blocks past nb: of no size)
+#pragma unroll
+    for (int b = 0; b < NBA; ++b)
+        ra[b] = buf_rsrc(a.pool + (size_t)slot * a.slot_stride + P.a_off + frag_index(c0 + min(b, nb - 1), 0, KS),
+                         b < nb ? KS * 1024u : 0u);
     XRows<1> x;
     x.init(X, P.K, T, lds + w * 128, [=](int r) { return __shfl(toks, min(rb * 16 + r, cnt - 1)); });
-    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int i = 0; i < n; i += kShrinkChunk) {
-        u32x4 av[kShrinkChunk][2], xv[kShrinkChunk][1][2];
+    f32x4 acc[NBA];
 #pragma unroll
-        for (int j = 0; j < kShrinkChunk; ++j) {
-            const unsigned g = g0 + i + j;
-            const bool ok = i + j < n;
+    for (int b = 0; b < NBA; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    u32x4 av[D][2][NBA], xv[D][1][2];
+    auto load = [&](int d, int i) __attribute__((always_inline)) {
+        const bool ok = i < n;
 #pragma unroll
-            for (int e = 0; e < 2; ++e) av[j][e] = buf16(ra, ok ? (2 * g + e) * 1024u + l * 16u : kOob);
-            x.load(xv[j], g, ok);
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int b = 0; b < NBA; ++b)
+                av[d][e][b] = buf16(ra[b], ok ? (unsigned)(2 * (g0 + i) + e) * 1024u + l * 16u : kOob);
+        x.load(xv[d], g0 + i, ok);
+    };
+    auto comp = [&](int d, int i) __attribute__((always_inline)) {
+        x.put(xv[d]);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            if (2 * (g0 + i) + e >= KS) continue;    // an odd K's last pair holds one k-step
+            const u32x4 xf = x.get(0, e);
+#pragma unroll
+            for (int b = 0; b < NBA; ++b) acc[b] = mfma(av[d][e][b], xf, acc[b]);
         }
-        __builtin_amdgcn_sched_barrier(0);            // every load above is in flight before the first MFMA
+    };
 #pragma unroll
-        for (int j = 0; j < kShrinkChunk; ++j) {
-            x.put(xv[j]);
-            if (i + j < n) {
-                acc = mfma(av[j][0], x.get(0, 0), acc);
-                if (2 * (g0 + i + j) + 1 < KS) acc = mfma(av[j][1], x.get(0, 1), acc);
-            }
+    for (int d = 0; d < D; ++d) load(d, d);
+    __builtin_amdgcn_sched_barrier(0);                // every load above is in flight before the first MFMA
+    int i = 0;
+    for (; i + D < n; i += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            comp(d, i + d);
+            load(d, i + d + D);
         }
     }
-    f32x4* const red = reinterpret_cast<f32x4*>(lds) + NW * 128;
-    red[w * 64 + l] = acc;
-    __syncthreads();
-    // lane = 4 consecutive rows of A^T (ranks of one octet) of one token
-    if (w == 0) {
-        f32x4 v = red[l];
 #pragma unroll
-        for (int q = 1; q < NW; ++q) v += red[q * 64 + l];
+    for (int d = 0; d < D; ++d)
+        if (i + d < n) comp(d, i + d);
+    f32x4* const red = reinterpret_cast<f32x4*>(lds) + (NBA == 1 ? NW * 128 : 0);
+    if (NBA > 1) __syncthreads();                     // every wave is past its X buffer, which red overlays
+#pragma unroll
+    for (int b = 0; b < NBA; ++b) red[(b * NW + w) * 64 + l] = acc[b];
+    __syncthreads();
+    // wave b, block b: lane = 4 consecutive rows of A^T (ranks of one octet) of one token
+    if (w < nb) {
+        f32x4 v = red[w * NW * 64 + l];
+#pragma unroll
+        for (int q = 1; q < NW; ++q) v += red[(w * NW + q) * 64 + l];
         if (rb * 16 + lr < cnt) {
             uint32_t b[4][3];
 #pragma unroll
             for (int e = 0; e < 4; ++e) split3(sc * v[e], b[e]);
-            uint16_t* z = Z + ((size_t)c * a.rows + t) * kDecZLine + 4 * lg;
+            uint16_t* z = Z + ((size_t)(c0 + w) * a.rows + t) * kDecZLine + 4 * lg;
 #pragma unroll
             for (int q = 0; q < 3; ++q)
                 __hip_atomic_store(reinterpret_cast<unsigned long long*>(z + 16 * q),
@@ -446,13 +472,14 @@ template <int NW, int MB, int NB, bool Q4, bool PAIR, bool ZS>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void dec_main_kernel(DecArgs) {
     const DecArgs& a = kernel_args<DecArgs>();
     static_assert(!PAIR || (NB == 2 && ZS), "gate and up");
-    constexpr int XB = NW * MB * 128, RB = NW * MB * NB * 64, SB = NW * (128 + 64);   // the waves' X buffers; their sums; shrink
+    constexpr int XB = NW * MB * 128, RB = NW * MB * NB * 64, SB = NW * 64 * kShrinkMerge;   // the waves' X buffers; their sums; shrink
     __shared__ u32x4 lds[XB > RB ? (XB > SB ? XB : SB) : (RB > SB ? RB : SB)];
     f32x4* const red = reinterpret_cast<f32x4*>(lds);
     __shared__ int s_cnt[NW][64];
     __shared__ int s_vid[64];
-    __shared__ int s_oct[kDecodeMaxT * kMaxRank8 / 8 + 4];   // slot << 12 | r8 << 4 | octet, -1 padded to whole turns
-    __shared__ int s_info[2];                                // octets; outcome of the wait
+    // row block << 25 | slot << 12 | r8 << 4 | octet, -1 padded to whole turns (a token has one adapter)
+    __shared__ int s_oct[kDecodeMaxT * kMaxRank8 / 8 + 4 * MB];
+    __shared__ int s_info[3];                                // turns; outcome of the wait; turns of one row block each
     const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lg = l >> 4;
     const int bid = blockIdx.x;
 
@@ -467,13 +494,19 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
             if (q < a.n_proj && sb >= a.shrink_base[q]) p = q;
         const DecProj& P = a.p[p];
         // what there is to do, adapter after adapter: its items (16 tokens) times
-        // its blocks of A^T.  Mostly one each; the host counts the workgroups by
-        // the adapters that it knows
-        const int nb = (P.n_slices * pl.gr + 15) >> 4, units = dec_items(pl, s_cnt[w]) * nb, incl = wave_incl_scan(units);
+        // its blocks of A^T (times four of them, merged).  Mostly one each; the
+        // host counts the workgroups by the adapters that it knows
+        const int nb = (P.n_slices * pl.gr + 15) >> 4, ng = a.merge ? (nb + kShrinkMerge - 1) / kShrinkMerge : nb;
+        const int units = dec_items(pl, s_cnt[w]) * ng, incl = wave_incl_scan(units);
         for (int u = sb - a.shrink_base[p]; u < wave_total(incl); u += P.n_shrink) {
-            const int ai = __ffsll((long long)__ballot(incl > u)) - 1, nba = __builtin_amdgcn_readlane(nb, ai);
-            const int k = u - (__builtin_amdgcn_readlane(incl, ai) - __builtin_amdgcn_readlane(units, ai)), rb = k / nba;
-            dec_shrink<NW>(a, P, pl, ai, rb, k - rb * nba, P.X + (size_t)t0 * P.K, dec_z(a, P, g), T, lds);
+            const int ai = __ffsll((long long)__ballot(incl > u)) - 1, nga = __builtin_amdgcn_readlane(ng, ai);
+            const int k = u - (__builtin_amdgcn_readlane(incl, ai) - __builtin_amdgcn_readlane(units, ai)), rb = k / nga, c = k - rb * nga;
+            if (a.merge)
+                dec_shrink<NW, kShrinkMerge>(a, P, pl, ai, rb, c * kShrinkMerge,
+                                             min(__builtin_amdgcn_readlane(nb, ai) - c * kShrinkMerge, kShrinkMerge),
+                                             P.X + (size_t)t0 * P.K, dec_z(a, P, g), T, lds);
+            else
+                dec_shrink<NW, 1>(a, P, pl, ai, rb, c, 1, P.X + (size_t)t0 * P.K, dec_z(a, P, g), T, lds);
         }
         if (threadIdx.x == 0) raise_flag(a, bid, no);
         if (w == 0) count_launch(a, no);
@@ -496,7 +529,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
             if (q < a.n_proj && mbid >= a.tile_base[q]) p = q;
     }
     const DecProj P = a.p[p], P1 = a.p[PAIR ? 1 : p];
-    const int kparts = P.kparts, ncg = NW / kparts, cg = w / kparts, kq = w - cg * kparts;
+    const int kparts = P.kparts, ncg = NW >> __builtin_ctz(kparts), cg = w >> __builtin_ctz(kparts), kq = w - cg * kparts;
     const int KS = P.K >> 5, nWb = P.N >> 4, tile = mbid - (PAIR ? 0 : a.tile_base[p]);
     // this wave's column blocks (clamped at the projection's edge; not stored)
     int blk[NB];
@@ -529,8 +562,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     if (w == 0 && a.act_max > 0) ld = dec_plan_loads(a, t0, T);
     // Expand turn: 4 octets of the adapters in use (lane group lg takes
     // octet lg; tokens of other adapters see zeros, which cost no traffic:
-    // their loads are past the end of Z).  Turns past the list multiply
-    // zeros.  The first two turns' B^T are loaded during the K loop.
+    // their loads are past the end of Z).  Either the octets of all adapters,
+    // each turn for every row block; or, row block after row block, those of
+    // the adapters that have tokens there (`own`), which is less where most
+    // adapters have tokens in few row blocks (1B layer, 64 tokens, 64 adapters of
+    // rank 64: 170 -> 86 us).  The first turns' B^T are loaded during the K loop.
+    constexpr int NZ = ZS ? NB : 1;                   // Z's of a turn
+    constexpr int E = ZS ? 2 : 3;                     // turns in flight, one row block each
     struct TurnB {
         u32x4 b[NB];
         int cd;
@@ -538,26 +576,37 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     struct TurnZ {
         u32x4 z[MB][3];
     };
-    TurnB b0, b1;
-    TurnZ z0, z1;
+    struct TurnO {
+        u32x4 z[NZ][3];
+        int rb;
+    };
+    TurnB tb[E];
     int turns = 0;
+    bool own = false;
     auto load_b = [&](TurnB& t, int e) __attribute__((always_inline)) {
         t.cd = e < turns ? s_oct[4 * e + lg] : -1;
-        const int slot = max(t.cd >> 12, 0), r8s = t.cd >= 0 ? (t.cd >> 4) & 0xff : 0, j0 = t.cd >= 0 ? (t.cd & 15) * 8 : 0;
+        const int slot = t.cd >= 0 ? (t.cd >> 12) & 0x1fff : 0, r8s = t.cd >= 0 ? (t.cd >> 4) & 0xff : 0, j0 = t.cd >= 0 ? (t.cd & 15) * 8 : 0;
 #pragma unroll
         for (int cb = 0; cb < NB; ++cb)
             t.b[cb] = ld16(a.pool + (size_t)slot * a.slot_stride + Pc[cb]->b_off + (size_t)(blk[cb] * 16 + lr) * r8s + j0);
     };
-    auto load_z = [&](TurnZ& t, int cd, int q) __attribute__((always_inline)) {
-        const int slot = cd >> 12, vr = sig[q] * ((cd >> 4) & 0xff) + (cd & 15) * 8;   // row of A^T
+    // Z of block q's projection and slice, for the tokens of row block rb
+    auto load_z3 = [&](u32x4 (&z)[3], int cd, int q, int rb) __attribute__((always_inline)) {
+        const int vr = sig[q] * ((cd >> 4) & 0xff) + (cd & 15) * 8;              // row of A^T
         const __amdgpu_buffer_rsrc_t rz = buf_rsrc(dec_z(a, *Pc[q], g), (unsigned)(Pc[q]->nbA * a.rows * kDecZLine * 2));
+        const unsigned zo = (unsigned)(((vr >> 4) * a.rows + rb * 16 + lr) * kDecZLine + (vr & 15)) * 2u;
+        const bool mine = cd >= 0 && s_vid[rb * 16 + lr] == ((cd >> 12) & 0x1fff);
 #pragma unroll
-        for (int rb = 0; rb < MB; ++rb) {
-            const unsigned zo = (unsigned)(((vr >> 4) * a.rows + rb * 16 + lr) * kDecZLine + (vr & 15)) * 2u;
-            const bool own = cd >= 0 && s_vid[rb * 16 + lr] == slot;
+        for (int i = 0; i < 3; ++i) z[i] = buf16(rz, mine ? zo + i * 32u : kOob);
+    };
+    auto load_z = [&](TurnZ& t, int cd, int q) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < 3; ++i) t.z[rb][i] = buf16(rz, own ? zo + i * 32u : kOob);
-        }
+        for (int rb = 0; rb < MB; ++rb) load_z3(t.z[rb], cd, q, rb);
+    };
+    auto load_zo = [&](TurnO& t, int cd) __attribute__((always_inline)) {
+        t.rb = max(__builtin_amdgcn_readfirstlane(cd) >> 25, 0);                 // (lane 0 has the turn's first octet)
+#pragma unroll
+        for (int q = 0; q < NZ; ++q) load_z3(t.z[q], cd, q, t.rb);
     };
     auto use = [&](const u32x4& b, const TurnZ& z, int cb) __attribute__((always_inline)) {
 #pragma unroll
@@ -565,25 +614,80 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
             for (int i = 0; i < 3; ++i) acc[rb][cb] = mfma(b, z.z[rb][i], acc[rb][cb]);
     };
+    auto use_own = [&](const TurnB& b, const TurnO& z) __attribute__((always_inline)) {
+#pragma unroll
+        for (int rb = 0; rb < MB; ++rb)
+            if (MB == 1 || z.rb == rb) {
+#pragma unroll
+                for (int cb = 0; cb < NB; ++cb)
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) acc[rb][cb] = mfma(b.b[cb], z.z[ZS ? cb : 0][i], acc[rb][cb]);
+            }
+    };
     auto pre = [&]() __attribute__((always_inline)) {
         if (w == 0) no = launch_no(a);
         if (w == 0 && a.act_max > 0) {
             const Plan pl = dec_plan(a, ld, T);
             s_vid[l] = pl.vid;
-            const int c = pl.gr >> 3, incl = wave_incl_scan(c), total = wave_total(incl);
-            for (int j = 0; j < c; ++j) s_oct[incl - c + j] = (pl.gs << 12) | (pl.gr << 4) | j;
-            if (l < 4) s_oct[total + l] = -1;
-            if (l == 0) s_info[0] = total;
+            const int c = pl.gr >> 3;
+            const int incl = wave_incl_scan(c), total = wave_total(incl);
+            int at = 0, ow = MB == 1;
+            // (few turns are not worth the count: 8B, 50 tokens a row group over 8
+            // adapters, a microsecond a launch)
+            if (MB > 1 && total > 64) {
+                // lane g: the row blocks that hold tokens of its adapter, and octets
+                // before its own in each of them (two 16-bit sums a scan)
+                s_cnt[0][l] = 0;
+                __builtin_amdgcn_wave_barrier();
+                if (pl.mine >= 0) atomicOr(&s_cnt[0][pl.mine], 1 << (l >> 4));
+                __builtin_amdgcn_wave_barrier();
+                const int in = s_cnt[0][l];
+                int sum[(MB + 1) / 2], tot[(MB + 1) / 2], first[MB], n = 0;
+#pragma unroll
+                for (int h = 0; h < (MB + 1) / 2; ++h) {
+                    const int v = ((in >> (2 * h)) & 1 ? c : 0) | ((in >> (2 * h + 1)) & 1 ? c << 16 : 0);
+                    sum[h] = wave_incl_scan(v);
+                    tot[h] = wave_total(sum[h]);
+                    sum[h] -= v;
+                }
+#pragma unroll
+                for (int rb = 0; rb < MB; ++rb) {
+                    first[rb] = n;
+                    n += (((tot[rb >> 1] >> (16 * (rb & 1))) & 0xffff) + 3) >> 2;
+                }
+                // (loads of a turn)
+                ow = n * (NB + 3 * NZ) < ((total + 3) >> 2) * (NB + 3 * NZ * MB);
+                if (ow) {
+#pragma unroll
+                    for (int rb = 0; rb < MB; ++rb) {
+                        const int o = 4 * first[rb] + ((sum[rb >> 1] >> (16 * (rb & 1))) & 0xffff);
+                        const int end = (tot[rb >> 1] >> (16 * (rb & 1))) & 0xffff;
+                        if ((in >> rb) & 1)
+                            for (int j = 0; j < c; ++j) s_oct[o + j] = (rb << 25) | (pl.gs << 12) | (pl.gr << 4) | j;
+                        if (l < ((-end) & 3)) s_oct[4 * first[rb] + end + l] = -1;
+                    }
+                    at = n;
+                }
+            }
+            if (MB == 1 || !ow) {
+                for (int j = 0; j < c; ++j) s_oct[incl - c + j] = (pl.gs << 12) | (pl.gr << 4) | j;
+                if (l < 4) s_oct[total + l] = -1;
+                at = (total + 3) >> 2;
+            }
+            if (l == 0) {
+                s_info[0] = at;
+                s_info[2] = ow;
+            }
         }
     };
     auto mid = [&]() __attribute__((always_inline)) {
         if (a.act_max > 0) {
             __syncthreads();
-            turns = (s_info[0] + 3) >> 2;
-            if (turns > 0) {
-                load_b(b0, kq);
-                load_b(b1, kq + kparts);
-            }
+            turns = s_info[0];
+            own = MB == 1 || s_info[2];
+#pragma unroll
+            for (int d = 0; d < E; ++d)
+                if (kq + d * kparts < turns && (d < 2 || own)) load_b(tb[d], kq + d * kparts);
         }
     };
     auto none = []() {};
@@ -611,10 +715,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         if (w == 0) {
             // (the two projections of a pair have their shrink workgroups side by side)
             const int i0 = a.shrink_base[p], i1 = p + (PAIR ? 2 : 1) < a.n_proj ? a.shrink_base[p + (PAIR ? 2 : 1)] : a.n_shrink;
-            // (a limit for each of the turns that the shrink workgroups take: adapters
-            // in use have s_info[0] octets of ranks, S / 2 blocks of A^T each)
-            const bool ok = wait_flags(a, g * a.n_shrink + i0, i1 - i0, no,
-                                       (unsigned long long)a.wait_ticks * (1 + P.n_slices * s_info[0] / (2 * P.n_shrink)));
+            // (a limit for each unit that a shrink workgroup takes: an expand turn's
+            // 4 octets of ranks are 2 blocks of A^T a slice)
+            const bool ok = wait_flags(a, g * a.n_shrink + i0, i1 - i0, no, 2 * P.n_slices * turns, P.n_shrink);
             if (l == 0) s_info[1] = ok;
         }
         __syncthreads();
@@ -628,42 +731,73 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
                     const int nb = (Q.n_slices * __builtin_amdgcn_readlane(mine.gr, ai) + 15) >> 4;
                     const int items = __builtin_amdgcn_readlane(nit, ai);
                     for (int rb = 0; rb < items; ++rb)
-                        for (int c = 0; c < nb; ++c) 
-                            dec_shrink<NW>(a, Q, mine, ai, rb, c, Q.X + (size_t)t0 * Q.K, dec_z(a, Q, g), T, lds);
+                        for (int c = 0; c < nb; ++c)
+                            dec_shrink<NW, 1>(a, Q, mine, ai, rb, c, 1, Q.X + (size_t)t0 * Q.K, dec_z(a, Q, g), T, lds);
                 }
             }
         }
         asm volatile("" ::: "memory");
-        if constexpr (ZS) {
-            // a Z of each block, one after the other
-            static_assert(NB == 2, "block 0 and block 1");
-            load_z(z0, b0.cd, 0);
-            for (int e = kq; e < turns; e += kparts) {
-                load_z(z1, b0.cd, 1);
-                use(b0.b[0], z0, 0);
-                load_z(z0, b1.cd, 0);                 // of the next turn (none: zeros)
-                use(b0.b[1], z1, 1);
-                b0 = b1;
-                if (e + 2 * kparts < turns) load_b(b1, e + 2 * kparts);
-            }
-        } else {
-            auto use_all = [&](const TurnB& b, const TurnZ& z) __attribute__((always_inline)) {
+        const int nt = (turns - kq + kparts - 1) >> __builtin_ctz(kparts);      // this wave's turns (kparts: a power of 2)
+        if (nt > 0 && own) {
+            TurnO to[E];
 #pragma unroll
-                for (int cb = 0; cb < NB; ++cb) use(b.b[cb], z, cb);
-            };
-            load_z(z0, b0.cd, 0);
-            load_z(z1, b1.cd, 0);
-            for (int e = kq; e < turns; e += 2 * kparts) {
-                use_all(b0, z0);
-                if (e + 2 * kparts < turns) {
-                    load_b(b0, e + 2 * kparts);
-                    load_z(z0, b0.cd, 0);
+            for (int d = 0; d < E; ++d)
+                if (d < nt) load_zo(to[d], tb[d].cd);
+            int i = 0;
+            for (; i + 2 * E <= nt; i += E) {
+#pragma unroll
+                for (int d = 0; d < E; ++d) {
+                    use_own(tb[d], to[d]);
+                    load_b(tb[d], kq + (i + d + E) * kparts);
+                    load_zo(to[d], tb[d].cd);
                 }
-                if (e + kparts >= turns) break;
-                use_all(b1, z1);
-                if (e + 3 * kparts < turns) {
-                    load_b(b1, e + 3 * kparts);
-                    load_z(z1, b1.cd, 0);
+            }
+#pragma unroll
+            for (int d = 0; d < E; ++d)
+                if (i + d < nt) {
+                    use_own(tb[d], to[d]);
+                    if (i + d + E < nt) {
+                        load_b(tb[d], kq + (i + d + E) * kparts);
+                        load_zo(to[d], tb[d].cd);
+                    }
+                }
+#pragma unroll
+            for (int d = 0; d < E; ++d)
+                if (i + E + d < nt) use_own(tb[d], to[d]);
+        } else if (MB > 1 && nt > 0) {
+            TurnZ z0, z1;
+            if (nt < 2) load_b(tb[1], turns);
+            if constexpr (ZS) {
+                // a Z of each block, one after the other
+                static_assert(NB == 2, "block 0 and block 1");
+                load_z(z0, tb[0].cd, 0);
+                for (int e = kq; e < turns; e += kparts) {
+                    load_z(z1, tb[0].cd, 1);
+                    use(tb[0].b[0], z0, 0);
+                    load_z(z0, tb[1].cd, 0);              // of the next turn (none: zeros)
+                    use(tb[0].b[1], z1, 1);
+                    tb[0] = tb[1];
+                    if (e + 2 * kparts < turns) load_b(tb[1], e + 2 * kparts);
+                }
+            } else {
+                auto use_all = [&](const TurnB& b, const TurnZ& z) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int cb = 0; cb < NB; ++cb) use(b.b[cb], z, cb);
+                };
+                load_z(z0, tb[0].cd, 0);
+                load_z(z1, tb[1].cd, 0);
+                for (int e = kq; e < turns; e += 2 * kparts) {
+                    use_all(tb[0], z0);
+                    if (e + 2 * kparts < turns) {
+                        load_b(tb[0], e + 2 * kparts);
+                        load_z(z0, tb[0].cd, 0);
+                    }
+                    if (e + kparts >= turns) break;
+                    use_all(tb[1], z1);
+                    if (e + 3 * kparts < turns) {
+                        load_b(tb[1], e + 3 * kparts);
+                        load_z(z1, tb[1].cd, 0);
+                    }
                 }
             }
         }
@@ -725,7 +859,7 @@ hipError_t launch_dec_main(DecArgs& a, int mb, hipStream_t s) {
     bool q4 = false;
     for (int i = 0; i < a.n_proj; ++i) {
         q4 = q4 || a.p[i].Ws != nullptr;
-        if (a.p[i].kparts < 1 || dec_waves(mb) % a.p[i].kparts) return hipErrorInvalidValue;
+        if (a.p[i].kparts < 1 || (a.p[i].kparts & (a.p[i].kparts - 1)) || dec_waves(mb) % a.p[i].kparts) return hipErrorInvalidValue;
     }
     switch (mb) {
         case 1: return launch_mb<1, dec_waves(1)>(a, q4, s);

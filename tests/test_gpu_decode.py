@@ -514,3 +514,63 @@ def test_replay_with_more_to_shrink_than_at_capture(torch_cuda, T):
             assert e["pointwise"] <= TOL, f"T={T} replay {rep} {projs[p].name}: {e}"
     assert pool.device_error() == 0
     pool.close()
+
+
+@pytest.mark.parametrize("ranks,order", [("16", "blocks"), ("16", "spread"), ("mixed", "blocks"), ("mixed", "spread")])
+@pytest.mark.parametrize("T", [16, 17, 32, 33, 48, 64, 150])
+def test_many_adapters(torch_cuda, T, ranks, order):
+    # forty adapters (eighteen in row groups): the expand row block by row block (each adapter's tokens
+    # in few of them) or for all row blocks at once (spread over them); of rank
+    # 16, and of ranks up to 128, whose shrink workgroups take four blocks of
+    # A^T; a layer of projections with one and several slices, inputs of one
+    # and of an odd number of k-steps, and the gated MLP
+    torch = torch_cuda
+    import paper_2510_23346_amd as bd
+    n, few = (40, 12) if T <= 64 else (18, 6)              # (more, and 150 tokens take the medium-batch launches)
+    projs = [wl.ProjSpec("gate", "column", 96, (160,)), wl.ProjSpec("up", "column", 96, (160,)),
+             wl.ProjSpec("down", "row", 160, (80,)), wl.ProjSpec("qkv", "column", 96, (16, 48, 32, 32)),
+             wl.ProjSpec("o", "row", 32, (1040,))]
+    some = (128, 64, 8, 120, 0, 33) if T <= 64 else (128, 120, 64)
+    rank = [16] * n if ranks == "16" else [some[i % len(some)] for i in range(n)]
+    rng = np.random.default_rng(T)
+    ids = rng.integers(-1, n, size=T)
+    ids = np.sort(ids) if order == "blocks" else np.where(ids < 0, -1, np.arange(T) % few + few * (np.arange(T) // 64))
+    spec = wl.custom_workload(f"many-{T}-{ranks}-{order}", projs, T, rank, ids=ids, seed=40 + T)
+    layer = wl.draw_layer(spec, slots=range(n))
+    pool = make_pool(spec)
+    load_adapters(pool, spec, range(n), cache=layer.adapters)
+    dl = DeviceLayer(layer)
+    set_wait = bd.lib().bdlora_internal_set_wait
+    set_wait.argtypes = [ctypes.c_void_p, ctypes.c_uint32]
+    seen = []
+    for ticks in (20000, 20000, 0):                     # (0: the main workgroups compute Z themselves)
+        assert set_wait(pool.handle, ticks) == 0
+        for o in dl.out:
+            o.fill_(float("nan"))
+        pool.forward_layer([0, 1, 2, 3, 4], dl.X, dl.W, dl.out, dl.ids)
+        torch.cuda.synchronize()
+        got = [y.copy() for y in dl.outputs()]
+        pool.forward_mlp(bd.ACT_SILU_MUL, [0, 1], 2, dl.X[0], dl.W[:2], dl.W[2], dl.out[2], dl.ids)
+        torch.cuda.synchronize()
+        seen.append(got + [dl.outputs()[2].copy()])
+    for other in seen[1:]:
+        assert all(np.array_equal(a.view(np.uint32), b.view(np.uint32)) for a, b in zip(seen[0], other))
+    refs = bdlora.layer_forward(layer)
+    for p in range(len(projs)):
+        e = bdlora.rel_errors(seen[0][p], refs[p])
+        assert e["pointwise"] <= TOL, f"{projs[p].name}: {e}"
+
+    def ref(i, x):
+        y = x @ layer.projs[i].W.astype(np.float64)
+        for t, a in enumerate(ids):
+            if a >= 0 and rank[a]:
+                ad = layer.adapters[int(a)]
+                y[t] += ad.scale * (x[t] @ ad.A[i][0].astype(np.float64)) @ ad.B[i][0].astype(np.float64)
+        return y
+    x0 = layer.projs[0].X.astype(np.float64)
+    g, u = ref(0, x0), ref(1, x0)
+    h = wl.bf16_round((g / (1.0 + np.exp(-g)) * u).astype(np.float32))[1].astype(np.float64)
+    e = bdlora.rel_errors(seen[0][5], ref(2, h))
+    assert e["pointwise"] <= 2 * TOL, f"mlp: {e}"          # (H may round the other way, as above)
+    assert pool.last_path() == ("decode" if T <= 64 else "tile64") and pool.device_error() == 0
+    pool.close()
