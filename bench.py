@@ -84,7 +84,7 @@ def algorithmic_flops(spec, ids, ranks):
 
 
 KERNEL_SOURCES = ("bdl_prep.hip", "bdl_decode.hip", "bdl_kernels.hip", "bdl_gemm.hip", "bdl_device.h",
-                  "bdl_launch.h", "bdl_api.cpp")
+                  "bdl_launch.h", "bdl_xaddr.h", "bdl_api.cpp")
 
 
 def kernel_source_hash():
@@ -449,10 +449,11 @@ def measure(index, K, warmup, rotate=0, eager=False):
             sums[k] += ms[k] * n
         cnt += n
     k_ms = [v / max(1, cnt) for v in sums]
-    if decode:
-        # one launch: plan, shrink, base product and expand
-        names = ("", "main")
-        dom, dom_name = 1, "bdl::dec_main_kernel"
+    if decode or (path == "tile64" and spec.T <= 256):
+        # one launch: plan, shrink, base product and expand (above the decode
+        # size in row groups, timed as the third interval)
+        names = ("", "main") if decode else ("", "", "main")
+        dom, dom_name = len(names) - 1, "bdl::dec_main_kernel"
         algo = step_bytes
         achieved = algo / (k_ms[dom] * 1e-3) / 1e9
         roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -471,8 +472,8 @@ def measure(index, K, warmup, rotate=0, eager=False):
                 "frac": round(achieved / HBM_PEAK_GBS, 4)}
     else:
         names = ("prep", "shrink", "gemm")
-        # the library's base GEMM: the 256 x 256 LDS-staged kernel for bf16
-        # weights above 256 tokens, the 64-row kernel otherwise
+        # the library's base GEMM above 256 tokens: the 256 x 256 LDS-staged
+        # kernels, the 64-row kernel for what they do not take
         dom, dom_name = 2, ("bdl::gemm_kernel" if path != "large" else
                               "bdl::gemm_big_kernel" if spec.weight_format == "bf16" else "bdl::gemm_big_int4_kernel")
         algo = g_flops

@@ -75,11 +75,10 @@ extern "C" {
  * medium batches on large layers base partials and an epilogue; see
  * bdlora_last_path). */
 #define BDLORA_DECODE_MAX_T 64
-/* Sizes of small decode batches: T <= 16, or T <=
- * BDLORA_DECODE_PLAN_IN_MAIN_T and T x (the sum of d_in over the call's
- * projections) x 2 bytes <= BDLORA_DECODE_PLAN_IN_MAIN_BYTES.  (Every decode
- * batch now plans inside its one launch; the bounds stay for callers that
- * read them.) */
+/* Deprecated: these bounds (T <= 16, or T <= BDLORA_DECODE_PLAN_IN_MAIN_T and
+ * T x (the sum of d_in over the call's projections) x 2 bytes <=
+ * BDLORA_DECODE_PLAN_IN_MAIN_BYTES) select nothing; every decode batch plans
+ * inside its one launch.  They stay for callers that read them. */
 #define BDLORA_DECODE_PLAN_IN_MAIN_T 32
 #define BDLORA_DECODE_PLAN_IN_MAIN_BYTES 1572864
 /* Largest number of segments a bdlora_segments batch may have (the segments
@@ -311,11 +310,13 @@ int bdlora_forward_layer(bdlora_pool_t pool, int32_t n, const int32_t* projs,
  * lives in a static device array of BDLORA_STATIC_SCRATCH_BYTES that the library holds on every GPU it
  * runs on until the process ends, instead of in the pool's workspace.  The
  * call allocates nothing (no hipMalloc, no allocating library routine); the
- * pool still holds the adapters, their tables and the error flag.  Same
- * arguments, kernels, launch geometry and results (bit for bit) as
+ * pool still holds the adapters, their tables, the error flag, and the decode
+ * launch's flags and counts (so calls on one pool stay on one stream, in turn).
+ * Same arguments, kernels, launch geometry and results (bit for bit) as
  * bdlora_forward_layer.  Every call on one GPU shares that GPU's array:
  * calls that overlap on one GPU (other streams, other pools, other threads)
- * race and must be serialized by the caller.  Nothing in the array has to
+ * race and must be serialized by the caller.  An X that an out shares memory
+ * with is copied into the array.  Nothing in the array has to
  * start at zero: every word a call reads was written earlier in that call.
  * Errors: as bdlora_forward_layer; SHAPE for T above BDLORA_DECODE_MAX_T or a
  * call that exceeds BDLORA_STATIC_SCRATCH_BYTES, counting plan tables, the
@@ -406,8 +407,9 @@ int bdlora_pool_bytes(bdlora_pool_t pool, int64_t* bytes);
 /* Timing hooks.  bdlora_profile_begin(pool, n) makes the next n forward
  * calls record HIP events around each of their launches on the caller's
  * stream, in four intervals: for a decode batch (BDLORA_PATH_DECODE)
- * nothing, its one launch, nothing, nothing; for a larger batch plan and
- * packing, shrink, base product (with the fused
+ * nothing, its one launch, nothing, nothing; for a batch of row groups
+ * (BDLORA_PATH_TILE64 up to 256 tokens) nothing, nothing, its one launch,
+ * nothing; for other larger batches plan and packing, shrink, base product (with the fused
  * expand, or for BDLORA_PATH_MEDIUM the partials), and for
  * BDLORA_PATH_MEDIUM its epilogue (partials plus expand), else nothing.
  * bdlora_profile_end waits for them and writes the mean duration in

@@ -25,15 +25,15 @@ __all__ = [
 
 COLUMN, ROW = 0, 1
 MAX_SLICES = 4
-DECODE_MAX_T = 64       # BDLORA_DECODE_MAX_T: largest batch that takes the decode launches
+DECODE_MAX_T = 64       # BDLORA_DECODE_MAX_T: largest batch that always takes the decode launch
 DECODE_PLAN_IN_MAIN_T = 32            # BDLORA_DECODE_PLAN_IN_MAIN_T
 DECODE_PLAN_IN_MAIN_BYTES = 1572864    # BDLORA_DECODE_PLAN_IN_MAIN_BYTES
 
 
 def decode_plans_in_main(T, d_ins):
-    """Whether a decode call of T tokens over projections with inputs
-    ``d_ins`` is a small one (the sizes stated in bdlora.h; every decode call
-    plans inside its one launch)."""
+    """Deprecated: whether a decode call of T tokens over projections with inputs
+    ``d_ins`` is within the bounds stated in bdlora.h, which select nothing
+    (every decode call plans inside its one launch)."""
     act = 2 * T * sum(int(k) for k in d_ins)
     return 1 <= T <= 16 or (T <= DECODE_PLAN_IN_MAIN_T and act <= DECODE_PLAN_IN_MAIN_BYTES)
 MAX_SEGMENTS = 256      # BDLORA_MAX_SEGMENTS: most segments of a batch given as segments

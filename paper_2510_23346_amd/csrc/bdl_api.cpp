@@ -699,11 +699,11 @@ struct Shapes {
 // activations) that still leaves enough workgroups to occupy the chip.
 static Shapes pick_shapes(int T, long long col_blocks = 0, int r8max = bdl::kMaxRank8) {
     Shapes k;
-    // Shrink items: BDL_SH rows x the columns of a projection's slices at the
-    // pool's rank
+    // Shrink items: 16 smb rows x chunks of up to 16 snb columns of a
+    // projection's slices at the pool's rank
     const bool wide = T > 512;
     k.snb = r8max <= 16 ? 3 : r8max <= 32 ? 6 : 4;
-    k.smb = !wide ? 1 : r8max > 32 && T > 512 ? 4 : 2;
+    k.smb = !wide ? 1 : r8max > 32 ? 4 : 2;
     k.gmb = T <= 16 ? 1 : (T <= 32 ? 2 : 4);
     const long long row_tiles = (T + 16 * k.gmb - 1) / (16 * k.gmb);
     const long long blocks = col_blocks * row_tiles;
@@ -822,7 +822,6 @@ static int forward_decode(bdlora_pool_t P, int n, const int32_t* projs, const vo
     std::memset(&da, 0, sizeof(da));
     da.n_proj = n;
     da.T = T;
-    da.r8max = L.r8max;
     da.groups = dec_groups(T);
     da.rows = (T + da.groups - 1) / da.groups;
     // (a captured forward above the decode size must hold for adapters loaded later)

@@ -24,10 +24,6 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // word 3 of a raw buffer resource on gfx950 (32-bit untyped data)
 constexpr int kRawBufferWord3 = 0x00020000;
 
-// cache policy of buffer loads and stores at agent scope (sc1): past the caches
-// that are not coherent between XCDs
-constexpr int kAgentScope = 16;
-
 constexpr int kWaves = 8;                 // waves per workgroup (split K)
 constexpr int kThreads = kWaves * 64;
 

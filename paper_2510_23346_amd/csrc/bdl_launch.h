@@ -168,7 +168,6 @@ struct DecArgs {
     int act_max;              // adapter positions of the launch: the host's bound on the adapters in
                               // use; the plan treats those past it (slot order) as none and raises *err
     int max_slots;
-    int r8max;
     int merge;                // shrink workgroups take four blocks of A^T (else one)
     int pair;                 // gated MLP: projections 0 and 1 share the tiles of 0, H = silu(0) * 1
     unsigned wait_ticks;      // longest wait for a producer (100 MHz ticks a turn; 0: none), then its work is done here

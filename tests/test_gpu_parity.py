@@ -439,26 +439,25 @@ def test_decode_variants_parity(torch_cuda, index):
     pool.close()
 
 
-@pytest.mark.parametrize("model,T,in_main", [("llama-3.1-8b", 32, True), ("llama-3.1-70b", 24, True),
-                                             ("llama-3.1-70b", 32, False), ("llama-3.1-70b", 17, True)])
-def test_decode_plan_in_main_boundary(torch_cuda, model, T, in_main):
-    # decode batches of two row blocks plan inside the K-split launch while
-    # their activations stay small (the 8B layer shard at 32 tokens, the 70B
-    # one up to about 26) and take the plan launch above that; both forms
-    # are compared with the oracle on every row
+@pytest.mark.parametrize("model,T", [("llama-3.1-8b", 16), ("llama-3.1-70b", 17), ("llama-3.1-70b", 24), ("llama-3.1-8b", 32),
+                                     ("llama-3.1-70b", 32), ("llama-3.1-8b", 33), ("llama-3.1-8b", 48), ("llama-3.1-8b", 49),
+                                     ("llama-3.1-8b", 64), ("llama-3.1-8b", 65)])
+def test_decode_row_block_boundaries(torch_cuda, model, T):
+    # the decode launch's row blocks of 16 tokens (each count is a kernel of its
+    # own, from two on with four waves) and its largest batch, above which the
+    # 8B layer takes it in two row groups: the model shapes, every row
+    # compared with the oracle
     torch = torch_cuda
-    import paper_2510_23346_amd as bd
     ranks = [16, 8, 32, 64, 16, 8]
     base = wl.workload(3) if model == "llama-3.1-70b" else wl.workload(1)
     spec = dataclasses.replace(base, name=f"boundary-{model}-{T}", T=T, n_slots=len(ranks), ranks=ranks,
                                scales=[2.0, 1.0, 0.5, 1.5, 1.0, 0.75], seed=700 + T)
-    assert bd.decode_plans_in_main(T, [p.d_in for p in spec.projs]) == in_main
     slots = list(range(len(ranks)))
     layer = wl.draw_layer(spec, slots=slots)
     pool = make_pool(spec, max_tokens=T)
     load_adapters(pool, spec, slots, cache=layer.adapters)
     dl, ys = _run_layer(torch, spec, layer, pool)
-    assert pool.last_path() == "decode"
+    assert pool.last_path() == ("decode" if T <= 64 else "tile64")
     yb = _base_only(torch, spec, dl, pool)
     refs = bdlora.layer_forward(layer)
     rbase = _oracle_base(layer)
