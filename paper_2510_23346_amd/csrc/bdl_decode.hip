@@ -2,7 +2,8 @@
 //
 // Workgroups, in launch order:
 //   shrink  Z = scale * X A for each token's own adapter (step "Z <- X A" of
-//           Alg. 1 / Alg. 2), one 16-row block of A^T and 16 tokens each;
+//           Alg. 1 / Alg. 2), one or four 16-row blocks of A^T and 16 tokens
+//           at a time;
 //   main    out = X W_s + Z B: each owns some columns over the whole K (its
 //           waves split K and meet in LDS), adds the expand (steps "Y_adapter
 //           <- Z B", "Y <- Y + Y_adapter") as extra MFMA k-steps and stores
@@ -456,11 +457,11 @@ __device__ __forceinline__ void dec_k_int4(f32x4 (&acc)[MB][NB], const DecProj* 
 // kernel trace, against the three launches this replaces (plan and packing;
 // split-K sums of 11.9 MB in fp32 partial tiles; epilogue), which took one
 // tile of 64 columns through memory between them:
-//   1 token, 1 adapter                  25.2 -> 13.9 us (54.5 MB of weights: 3.9 TB/s)
+//   1 token, 1 adapter                  25.2 -> 12.8 us (54.5 MB of weights: 4.3 TB/s)
 //   16 tokens, 8 adapters of rank 16           17.2 us
-//   37 tokens, ranks 8 and 64           44.1 -> 30.8 us
-//   64 tokens, 26 adapters of rank 16   39.8 -> 29.7 us (75.4 MB: 2.5 TB/s)
-//   the same on an INT4 base            40.2 -> 24.4 us
+//   37 tokens, ranks 8 and 64           44.1 -> 31.4 us
+//   64 tokens, 26 adapters of rank 16   39.8 -> 30.4 us (75.4 MB: 2.5 TB/s)
+//   the same on an INT4 base            40.2 -> 24.6 us
 // At 64 tokens a workgroup moves 2 bytes of activations per byte of weight
 // through its CU; two pairs of k-steps in flight per wave are what the
 // registers hold (three waves per SIMD instead of two spill: 126 us).  One

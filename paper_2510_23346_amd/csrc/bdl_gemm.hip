@@ -569,7 +569,7 @@ __global__ __launch_bounds__(128 * (16 / RB)) void gemm_big_kernel(FwdArgs a) {
 // take 210 vector instructions, in the gaps of those 80.
 // Waits: every load in flight in the loop is a copy into LDS, and all of them
 // belong to the group that the barrier waits for.
-// 8B layer shard, 1001 tokens: 85 us and 13 of the fix-up launch; the 64-row
+// 8B layer shard, 1001 tokens: 82 us and 20 of the fix-up launch; the 64-row
 // kernel 154.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(512) void gemm_big_int4_kernel(FwdArgs) {
