@@ -98,7 +98,7 @@ def test_every_launch_has_a_number_of_its_own(torch_cuda):
     pool = make_pool(spec)
     load_adapters(pool, spec, range(3), cache=layer.adapters)
     dl = DeviceLayer(layer)
-    hip = ctypes.CDLL("libamdhip64.so")
+    hip = bd.lib()                           # (the HIP runtime that the library uses)
 
     def layer_call(t, s=None):
         pool.forward_layer([0, 1, 2], [x[:t] for x in dl.X], dl.W, [o[:t] for o in dl.out], dl.ids[:t], stream=s)
@@ -426,10 +426,18 @@ def test_out_may_share_memory_with_x(torch_cuda, T, fmt, entry, path):
             X = [mem[0].view(T, 256), mem[0].view(T, 256), mem[2][:T * 128].view(T, 128)]
             at = T * 64                                       # half way into the third X
             out = [mem[0].view(T, 256), mem[1].view(T, 192), mem[2][at:at + T * 320].view(T, 320)]
+        if rep == 2:                                          # the last one as a replay
+            with torch.cuda.stream(torch.cuda.Stream()):
+                graph = torch.cuda.CUDAGraph()
+                with torch.cuda.graph(graph):
+                    call(idx, X, W, out, ids)
         for x, v in zip(X, x0):
             x.copy_(v)
         torch.cuda.synchronize()
-        call(idx, X, W, out, ids)
+        if rep == 2:
+            graph.replay()
+        else:
+            call(idx, X, W, out, ids)
         torch.cuda.synchronize()
         assert pool.last_path() == path
         for i in idx:
